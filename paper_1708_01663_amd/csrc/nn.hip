@@ -39,6 +39,14 @@ __host__ __device__ __forceinline__ bf16_t f2bf(float f) {
 }
 __host__ __device__ __forceinline__ float bf2f(bf16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
 
+// Orders a wave's own LDS stores and reads (its DS operations complete in
+// order; only the compiler must keep them).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ------------------------------------------------------------------ conv forward
 constexpr int CV_BK = 32, CV_PAD = 8;
 
@@ -190,12 +198,15 @@ __global__ void __launch_bounds__(256) k_conv3x3(const bf16_t *__restrict__ x, c
 //   TOUT_U0   u0 = u_in + (y0 + i y1) written as complex values, as
 //             k_net_output does (channels 0 and 1 of the first channel block)
 enum { TIN_X = 0, TIN_POOL = 1, TIN_NET = 2 };
-enum { TOUT_BF16 = 0, TOUT_F32 = 1, TOUT_U0 = 2 };
+//   TOUT_MASK  y in NHWC, zero where io.mask is not positive (the data gradient
+//   through the ReLU of the layer below)
+enum { TOUT_BF16 = 0, TOUT_F32 = 1, TOUT_U0 = 2, TOUT_MASK = 3 };
 struct TileIO {
   const float *f = nullptr;   // TIN_NET: [B, H W]
   const cf *uin = nullptr;    // TIN_NET, TOUT_U0: [B, H W]
   const cf *ub = nullptr;     // TIN_NET: [B, H W] or null (zeros)
   cf *u0 = nullptr;           // TOUT_U0: [B, H W]
+  const bf16_t *mask = nullptr;   // TOUT_MASK: the layer's input activation, laid out as y
 };
 
 // Registers of one halo piece before it is formed: the piece itself, the four
@@ -401,23 +412,59 @@ __global__ void __launch_bounds__(256) k_conv3x3_tile(const bf16_t *__restrict__
         }
       return;
     }
+    if constexpr (TOUT == TOUT_F32) {
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        const int co = co0 + j * 32 + (lane & 31);
+        const float bb = bias ? bias[co] : 0.0f;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const size_t P = pixel(wave * MI + i, 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3));
+            float v = acc[i][j][r] + bb;
+            if (RELU) v = fmaxf(v, 0.0f);
+            reinterpret_cast<float *>(y)[P * Co + co] = v;
+          }
+        }
+      }
+      return;
+    }
+    // bf16: 32 channels at a time through the wave's own rows of the halo's LDS
+    // (no wave reads the halo any more), so that a lane stores, and masks, 16
+    // bytes instead of two (the 128^2 x 16 network forward: 222 -> 214 us)
+    static_assert(128 * MI <= HH * HW2, "the tile's outputs are staged in the halo's LDS");
+    bf16_t (*out)[CV_BK + CV_PAD] = Ah + wave * MI * 32;
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
-      const int co = co0 + j * 32 + (lane & 31);
-      const float bb = bias ? bias[co] : 0.0f;
+      const float bb = bias ? bias[co0 + j * 32 + (lane & 31)] : 0.0f;
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const size_t P = pixel(wave * MI + i, 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3));
           float v = acc[i][j][r] + bb;
           if (RELU) v = fmaxf(v, 0.0f);
-          if constexpr (TOUT == TOUT_F32)
-            reinterpret_cast<float *>(y)[P * Co + co] = v;
-          else
-            reinterpret_cast<bf16_t *>(y)[P * Co + co] = f2bf(v);
+          out[i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)][lane & 31] = f2bf(v);
         }
       }
+      wave_lds_order();
+#pragma unroll
+      for (int k = 0; k < 2 * MI; ++k) {
+        const int q = (lane >> 2) + 16 * k;   // pixel of the wave's 32 MI
+        const size_t P = pixel(wave * MI, q) * Co + co0 + j * 32 + (lane & 3) * 8;
+        u32x4 v = *reinterpret_cast<const u32x4 *>(&out[q][(lane & 3) * 8]);
+        if constexpr (TOUT == TOUT_MASK) {
+          const u32x4 m = *reinterpret_cast<const u32x4 *>(io.mask + P);
+#pragma unroll
+          for (int d = 0; d < 4; ++d) {   // positive bf16: sign clear, and not zero (NaN is not positive either)
+            const uint32_t lo = m[d] << 16, hi = m[d] & 0xffff0000u;
+            if (!(__builtin_bit_cast(float, lo) > 0.0f)) v[d] &= 0xffff0000u;
+            if (!(__builtin_bit_cast(float, hi) > 0.0f)) v[d] &= 0x0000ffffu;
+          }
+        }
+        *reinterpret_cast<u32x4 *>(reinterpret_cast<bf16_t *>(y) + P) = v;
+      }
+      wave_lds_order();
     }
   };
   int bimg, y0, x0;
@@ -457,9 +504,10 @@ __global__ void __launch_bounds__(256) k_conv3x3_tile(const bf16_t *__restrict__
       }
       clear();
       mfma_slice();
+      __syncthreads();   // every wave is done with this tile's halo
       store_out(bimg, y0, x0);
       if (t + 1 < TPB) {
-        __syncthreads();   // every wave is done with this tile's halo
+        __syncthreads();   // and with the outputs staged there
         store_halo(hr);
         __syncthreads();
         bimg = nb;
@@ -504,89 +552,240 @@ __global__ void k_conv_splitk_reduce(const float *__restrict__ part, int splits,
 }
 
 // ------------------------------------------------------------------ conv weight gradient
-// part[s][tap][co][ci] = sum over the pixels of split s of dy[p][co] x[shift(p, tap)][ci]
-constexpr int WG_PIX = 64, WG_PAD = 8;
-__global__ void __launch_bounds__(256) k_conv3x3_wgrad(const bf16_t *__restrict__ x, const bf16_t *__restrict__ dy,
-                                                       float *__restrict__ part, int H, int W, int Ci, int Co,
-                                                       int pix_per_split, int M) {
-  __shared__ __attribute__((aligned(16))) bf16_t Ds[32][WG_PIX + WG_PAD];   // [co][pixel]
-  __shared__ __attribute__((aligned(16))) bf16_t Xs[32][WG_PIX + WG_PAD];   // [ci][pixel]
-  __shared__ float red[4][32][33];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int ci0 = blockIdx.x * 32, co0 = (blockIdx.y % (Co / 32)) * 32, tap = blockIdx.y / (Co / 32);
-  const int split = blockIdx.z;
-  const int dyy = tap / 3 - 1, dxx = tap % 3 - 1;
-  const int HW = H * W;
-  const int p_begin = split * pix_per_split, p_end = min(M, p_begin + pix_per_split);
-  f32x16 acc = {0};
-  for (int p0 = p_begin; p0 < p_end; p0 += WG_PIX) {
-    {
-      const int px = tid >> 2, seg = tid & 3;   // 64 pixels x 4 segments of 8 channels
-      const int P = p0 + px;
-      uint4 dv = make_uint4(0, 0, 0, 0), xv = make_uint4(0, 0, 0, 0);
-      if (P < p_end) {
-        dv = *reinterpret_cast<const uint4 *>(dy + (size_t)P * Co + co0 + seg * 8);
-        const int b = P / HW, rem = P - b * HW, yy = rem / W + dyy, xx = rem % W + dxx;
-        if (yy >= 0 && yy < H && xx >= 0 && xx < W)
-          xv = *reinterpret_cast<const uint4 *>(x + ((size_t)(b * H + yy) * W + xx) * Ci + ci0 + seg * 8);
-      }
-      const bf16_t *d8 = reinterpret_cast<const bf16_t *>(&dv);
-      const bf16_t *x8 = reinterpret_cast<const bf16_t *>(&xv);
+// part[split][tap][co][ci] = sum over the pixels of a split of dy[p][co] x[shift(p, tap)][ci],
+// and with bpart the bias gradient bpart[split][co] = sum dy[p][co].
+// A GEMM with the pixels as its long inner dimension, whose operands lie with
+// the channels contiguous.  A block of eight waves owns 32 output x 32 input
+// channels and all nine taps (nine 32x32 accumulators per wave), so x and dy
+// are staged once instead of once per tap; each wave walks its own 16-pixel
+// wide strips down the image (a task is rh rows of one strip) and needs no
+// block barrier until the eight waves' sums are added at the end.  Per row it
+// stages 18 x pixels (one of halo on each side) and 16 dy pixels in its part
+// of the LDS as they lie in memory ([pixel][32 channels], 64 bytes a pixel, no
+// bank conflicts) and reads MFMA operands, eight consecutive pixels of one
+// channel per lane, with the transposing LDS read (four 16-bit values of a
+// column per lane; 16 lanes cover 4 pixels x 16 channels).  A tap's horizontal
+// shift is a pixel offset of that read and its vertical shift one of the last
+// three rows, which stay in registers: nine MFMAs per row for four reads'
+// worth of fresh operands.  The next two rows are fetched into registers
+// meanwhile.  With x2 set the input is [x (C1 channels) | up2(x2)] as in the
+// forward convolution.  Pixels outside the image are zeros, so any width runs
+// (a strip past the edge is cut).
+// Bound by launch and fill latency at the network's sizes (256 blocks, one
+// per CU): the 15 layers of a 128^2 x 16 batch take 265 us against
+// 986 us for one tap per block with element-wise transposing LDS stores.
+constexpr int WG_RB = 2;                                // rows per batch
+constexpr int WG_WAVES = 8;
+constexpr int WG_XP = 18, WG_DP = 16;                   // staged pixels per row
+constexpr int WG_XROW = WG_XP * 32, WG_DROW = WG_DP * 32;   // bf16 elements per staged row
+constexpr int WG_STAGE = (WG_RB + 2) * WG_XROW + WG_RB * WG_DROW;
+constexpr int WG_RED = WG_WAVES * 1024;                 // floats of one tap's eight wave sums
+struct WgArgs {
+  const bf16_t *x, *dy, *x2;
+  float *part, *bpart;
+  int H, W, Ci, Co, C1, rh, segs, strips, tasks;
+};
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+// Eight consecutive pixels of one channel: lane l takes channel l % 32, pixels
+// 8 (l / 32) .. + 8 of a staged row ([pixel][32]) that starts at p.
+__device__ __forceinline__ bf16x8 tr_frag(const bf16_t *p) {
+  typedef __attribute__((address_space(3))) s16x4 *lds4;
+  const int l = threadIdx.x & 63;
+  const bf16_t *q = p + (8 * (l >> 5) + ((l & 15) >> 2)) * 32 + 16 * ((l >> 4) & 1) + 4 * (l & 3);
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)q);
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(q + 4 * 32));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+__global__ void __launch_bounds__(64 * WG_WAVES, 2) k_conv3x3_wgrad(WgArgs a) {
+  constexpr int XB = (WG_RB * WG_XP * 4 + 63) / 64;   // x pieces (16 bytes) per lane and batch
+  constexpr int XP = (2 * WG_XP * 4 + 63) / 64;       // of the two rows above a task's first batch
+  __shared__ __attribute__((aligned(16))) bf16_t stage[WG_WAVES][WG_STAGE];
+  static_assert(sizeof(stage) >= sizeof(float) * WG_RED, "the sums are added in the staging area");
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int ci0 = blockIdx.x * 32, co0 = blockIdx.y * 32;
+  const int H = a.H, W = a.W;
+  const bool up = a.x2 && ci0 >= a.C1;
+  const int Cx = up ? a.Ci - a.C1 : (a.x2 ? a.C1 : a.Ci), cx0 = up ? ci0 - a.C1 : ci0;
+  const bf16_t *xs = up ? a.x2 : a.x;
+  const int sh = up ? 1 : 0, Hs = H >> sh, Ws = W >> sh;
+  bf16_t *sx = stage[wave], *sd = sx + (WG_RB + 2) * WG_XROW;
+  f32x16 acc[9];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        Ds[seg * 8 + j][px] = d8[j];
-        Xs[seg * 8 + j][px] = x8[j];
-      }
+  for (int t = 0; t < 9; ++t) acc[t] = f32x16{0};
+  float bsum = 0.0f;
+  const bool bias = a.bpart && ci0 == 0;
+  int x0 = 0, y1 = 0;
+  const bf16_t *xi = nullptr, *di = nullptr;   // the image's x and dy from channel cx0, co0 on
+  // piece i of nr consecutive x rows from row yy on (zero outside the image)
+  auto load_x = [&](int i, int nr, int yy) -> u32x4 {
+    const int row = i / (WG_XP * 4), rem = i - row * (WG_XP * 4);
+    const int y = yy + row, xx = x0 - 1 + (rem >> 2);
+    u32x4 v = u32x4{0, 0, 0, 0};
+    if (row < nr && y >= 0 && y < H && xx >= 0 && xx < W)
+      v = *reinterpret_cast<const u32x4 *>(xi + (unsigned)(((y >> sh) * Ws + (xx >> sh)) * Cx + (rem & 3) * 8));
+    return v;
+  };
+  u32x4 rx[XB], rd[WG_RB];
+  auto load_batch = [&](int yb) {   // x rows yb + 1 .. yb + WG_RB, dy rows yb .. (zero past the task)
+#pragma unroll
+    for (int k = 0; k < XB; ++k) rx[k] = load_x(lane + 64 * k, WG_RB, yb + 1);
+#pragma unroll
+    for (int k = 0; k < WG_RB; ++k) {
+      const int xx = x0 + (lane >> 2);
+      rd[k] = u32x4{0, 0, 0, 0};
+      if (yb + k < y1 && xx < W)
+        rd[k] = *reinterpret_cast<const u32x4 *>(di + (unsigned)(((yb + k) * W + xx) * a.Co + (lane & 3) * 8));
     }
-    __syncthreads();
-    // wave w contracts pixels [16 w, 16 w + 16)
-    const int kk = wave * 16;
-    const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&Ds[lane & 31][kk + 8 * (lane >> 5)]);
-    const bf16x8 bv = *reinterpret_cast<const bf16x8 *>(&Xs[lane & 31][kk + 8 * (lane >> 5)]);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bv, acc, 0, 0, 0);
-    __syncthreads();
-  }
+  };
+  for (int task = blockIdx.z * WG_WAVES + wave; task < a.tasks; task += gridDim.z * WG_WAVES) {
+    const int seg = task % a.segs, rest = task / a.segs;
+    x0 = (rest % a.strips) * 16;
+    const int img = rest / a.strips;
+    xi = xs + (size_t)img * Hs * Ws * Cx + cx0;
+    di = a.dy + (size_t)img * H * W * a.Co + co0;
+    const int y0 = seg * a.rh;
+    y1 = min(y0 + a.rh, H);
+    u32x4 rp[XP];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) red[wave][8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)][lane & 31] = acc[r];
-  __syncthreads();
-  for (int e = tid; e < 32 * 32; e += 256) {
-    const int co = e / 32, ci = e % 32;
-    const float s = red[0][co][ci] + red[1][co][ci] + red[2][co][ci] + red[3][co][ci];
-    part[(((size_t)split * 9 + tap) * Co + co0 + co) * Ci + ci0 + ci] = s;
+    for (int k = 0; k < XP; ++k) rp[k] = load_x(lane + 64 * k, 2, y0 - 1);
+    load_batch(y0);
+#pragma unroll
+    for (int k = 0; k < XP; ++k)
+      if (lane + 64 * k < 2 * WG_XP * 4) *reinterpret_cast<u32x4 *>(sx + (lane + 64 * k) * 8) = rp[k];
+    wave_lds_order();
+    bf16x8 f0[3], f1[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      f0[d] = tr_frag(sx + d * 32);
+      f1[d] = tr_frag(sx + WG_XROW + d * 32);
+    }
+    for (int yb = y0; yb < y1; yb += WG_RB) {
+#pragma unroll
+      for (int k = 0; k < XB; ++k)
+        if (lane + 64 * k < WG_RB * WG_XP * 4)
+          *reinterpret_cast<u32x4 *>(sx + 2 * WG_XROW + (lane + 64 * k) * 8) = rx[k];
+#pragma unroll
+      for (int k = 0; k < WG_RB; ++k) *reinterpret_cast<u32x4 *>(sd + k * WG_DROW + lane * 8) = rd[k];
+      wave_lds_order();
+      if (yb + WG_RB < y1) load_batch(yb + WG_RB);
+#pragma unroll
+      for (int r = 0; r < WG_RB; ++r) {
+        const bf16x8 d = tr_frag(sd + r * WG_DROW);
+        bf16x8 f2[3];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) f2[s] = tr_frag(sx + (2 + r) * WG_XROW + s * 32);
+        if (bias) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) bsum += (float)d[j];
+        }
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d, f0[s], acc[s], 0, 0, 0);
+          acc[3 + s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d, f1[s], acc[3 + s], 0, 0, 0);
+          acc[6 + s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d, f2[s], acc[6 + s], 0, 0, 0);
+        }
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          f0[s] = f1[s];
+          f1[s] = f2[s];
+        }
+      }
+      wave_lds_order();
+    }
   }
-}
-
-__global__ void k_sum_splits(const float *part, float *out, size_t n, int splits) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    float s = 0.0f;
-    for (int k = 0; k < splits; ++k) s += part[(size_t)k * n + i];
-    out[i] = s;
-  }
-}
-
-// bias gradient: db[c] = sum_p dy[p][c]
-__global__ void k_bias_grad(const bf16_t *dy, float *db, int M, int C) {
-  const int c = blockIdx.x;
-  float s = 0.0f;
-  for (int p = threadIdx.x; p < M; p += blockDim.x) s += bf2f(dy[(size_t)p * C + c]);
-  __shared__ float sh[256];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+  // the waves' sums, one tap at a time, added in wave order
+  float *red = reinterpret_cast<float *>(&stage[0][0]);
+#pragma unroll
+  for (int t = 0; t < 9; ++t) {
     __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      red[wave * 1024 + (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 32 + (lane & 31)] = acc[t][r];
+    __syncthreads();
+    for (int e = threadIdx.x; e < 1024; e += 64 * WG_WAVES) {
+      float s = red[e];
+#pragma unroll
+      for (int w = 1; w < WG_WAVES; ++w) s += red[w * 1024 + e];
+      a.part[(((size_t)blockIdx.z * 9 + t) * a.Co + co0 + e / 32) * a.Ci + ci0 + e % 32] = s;
+    }
   }
-  if (threadIdx.x == 0) db[c] = sh[0];
+  if (!bias) return;
+  __syncthreads();
+  red[threadIdx.x] = bsum;
+  __syncthreads();
+  if (threadIdx.x < 32) {
+    float s = 0.0f;
+    for (int w = 0; w < 2 * WG_WAVES; ++w) s += red[w * 32 + threadIdx.x];
+    a.bpart[(size_t)blockIdx.z * a.Co + co0 + threadIdx.x] = s;
+  }
 }
 
-// w'[tap][ci][co] = w[8 - tap][co][ci]   (data gradient = forward conv with w')
-__global__ void k_flip_transpose(const bf16_t *w, bf16_t *wt, int Ci, int Co) {
-  const size_t n = (size_t)9 * Ci * Co;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int tap = (int)(i / ((size_t)Ci * Co));
-    const int rem = (int)(i % ((size_t)Ci * Co));
-    const int ci = rem / Co, co = rem % Co;
-    wt[i] = w[((size_t)(8 - tap) * Co + co) * Ci + ci];
+// out[i] = sum of the `splits` partials part[k][i] of several arrays in one
+// launch (a launch per layer and array would cost more than the sums).  A
+// block owns 32 consecutive 16-byte groups of one array; eight lanes a group
+// sum every eighth split, and the lanes are added in order.
+constexpr int RED_ITEMS = 32;
+struct RedItem {
+  const float *part;
+  float *out;
+  unsigned n;        // elements, a multiple of 4
+  int splits;
+  unsigned block0;   // first block of the array
+};
+struct RedList {
+  RedItem it[RED_ITEMS];
+  int count = 0;
+  unsigned blocks = 0;
+  void add(const float *part, float *out, size_t n, int splits) {
+    it[count++] = RedItem{part, out, (unsigned)n, splits, blocks};
+    blocks += (unsigned)((n + 127) / 128);
+  }
+};
+__global__ void __launch_bounds__(256) k_sum_splits(RedList l) {
+  __shared__ float4 sh[8][32];
+  int k = 0;
+  while (k + 1 < l.count && blockIdx.x >= l.it[k + 1].block0) ++k;
+  const RedItem it = l.it[k];
+  const int c = threadIdx.x & 31, z0 = threadIdx.x >> 5;
+  const unsigned g = (blockIdx.x - it.block0) * 32 + c;
+  float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  if (4 * g < it.n) {
+    for (int z = z0; z < it.splits; z += 8) {
+      const float4 v = reinterpret_cast<const float4 *>(it.part + (size_t)z * it.n)[g];
+      s.x += v.x;
+      s.y += v.y;
+      s.z += v.z;
+      s.w += v.w;
+    }
+  }
+  sh[z0][c] = s;
+  __syncthreads();
+  if (z0 || 4 * g >= it.n) return;
+#pragma unroll
+  for (int z = 1; z < 8; ++z) {
+    s.x += sh[z][c].x;
+    s.y += sh[z][c].y;
+    s.z += sh[z][c].z;
+    s.w += sh[z][c].w;
+  }
+  reinterpret_cast<float4 *>(it.out)[g] = s;
+}
+
+// w'[tap][ci][co] = w[8 - tap][co][ci] of every layer (the data gradient is
+// the forward convolution with w'); wt has the layout of the parameter vector.
+struct FlipList {
+  struct { unsigned woff; int Ci, Co; } l[16];
+  int count = 0;
+};
+__global__ void k_flip_transpose(const bf16_t *w, bf16_t *wt, FlipList f) {
+  const unsigned off = f.l[blockIdx.y].woff;
+  const unsigned Ci = f.l[blockIdx.y].Ci, Co = f.l[blockIdx.y].Co, n = 9 * Ci * Co;
+  for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const unsigned tap = i / (Ci * Co), rem = i % (Ci * Co), ci = rem / Co, co = rem % Co;
+    wt[off + i] = w[off + ((8 - tap) * Co + co) * Ci + ci];
   }
 }
 
@@ -622,62 +821,61 @@ __global__ void k_avgpool(const bf16_t *x, bf16_t *y, int B, int H, int W, int C
     *reinterpret_cast<uint4 *>(y + p * C + c) = o;
   }
 }
-// dx (+)= dy / 4 broadcast (accumulate when add != 0)
-__global__ void k_avgpool_bwd(const bf16_t *dy, bf16_t *dx, int B, int H, int W, int C, int add) {
-  const size_t n = (size_t)B * H * W * C;
-  const int Ho = H / 2, Wo = W / 2;
+// Eight bf16 values of one 16-byte piece.
+__device__ __forceinline__ void unpack8(const uint4 &v, float (&o)[8]) {
+  const bf16_t *e = reinterpret_cast<const bf16_t *>(&v);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) o[j] = bf2f(e[j]);
+}
+// Rounds v to bf16, zero where the activation y is not positive (ReLU), and
+// stores the eight values.
+__device__ __forceinline__ void store8_masked(bf16_t *dst, const float (&v)[8], const bf16_t *y) {
+  float m[8];
+  unpack8(*reinterpret_cast<const uint4 *>(y), m);
+  uint4 o;
+  bf16_t *e = reinterpret_cast<bf16_t *>(&o);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) e[j] = m[j] > 0.0f ? f2bf(v[j]) : (bf16_t)0;
+  *reinterpret_cast<uint4 *>(dst) = o;
+}
+// Gradient at an encoder level's output y [B][H][W][C], its ReLU applied: the
+// pooled path dyp / 4 ([B][H/2][W/2][C]) plus the skip part, the first C of the
+// Ct channels of the decoder's input gradient gc.
+__global__ void k_pool_skip_bwd(const bf16_t *dyp, const bf16_t *gc, const bf16_t *y, bf16_t *dx, int B, int H, int W,
+                                int C, int Ct) {
+  const int C8 = C / 8, Ho = H / 2, Wo = W / 2;
+  const size_t n = (size_t)B * H * W * C8;
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int c = i % C;
-    const size_t p = i / C;
+    const int c = (int)(i % C8) * 8;
+    const size_t p = i / C8;
     const int xx = p % W, yy = (p / W) % H, b = (int)(p / ((size_t)W * H));
-    float v = 0.25f * bf2f(dy[((size_t)(b * Ho + yy / 2) * Wo + xx / 2) * C + c]);
-    if (add) v += bf2f(dx[i]);
-    dx[i] = f2bf(v);
+    float v[8], g[8];
+    unpack8(*reinterpret_cast<const uint4 *>(dyp + ((size_t)(b * Ho + yy / 2) * Wo + xx / 2) * C + c), v);
+    unpack8(*reinterpret_cast<const uint4 *>(gc + p * Ct + c), g);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = 0.25f * v[j] + g[j];
+    store8_masked(dx + p * C + c, v, y + p * C + c);
   }
 }
-__global__ void k_upsample(const bf16_t *x, bf16_t *y, int B, int H, int W, int C) {   // H, W: output size
-  const size_t n = (size_t)B * H * W * C;
+// Gradient at the output y [B][H][W][C] of the level below a decoder level,
+// its ReLU applied: the sum over each 2x2 block of the last C of the Ct
+// channels of the decoder's input gradient gc ([B][2H][2W][Ct]).
+__global__ void k_upsample_bwd(const bf16_t *gc, const bf16_t *y, bf16_t *dx, int B, int H, int W, int C, int Ct) {
+  const int C8 = C / 8;
+  const size_t n = (size_t)B * H * W * C8, row = (size_t)2 * W * Ct;
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int c = i % C;
-    const size_t p = i / C;
+    const int c = (int)(i % C8) * 8;
+    const size_t p = i / C8;
     const int xx = p % W, yy = (p / W) % H, b = (int)(p / ((size_t)W * H));
-    y[i] = x[((size_t)(b * (H / 2) + yy / 2) * (W / 2) + xx / 2) * C + c];
-  }
-}
-__global__ void k_upsample_bwd(const bf16_t *dy, bf16_t *dx, int B, int H, int W, int C) {   // H, W: input size
-  const size_t n = (size_t)B * H * W * C;
-  const int W2 = 2 * W;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int c = i % C;
-    const size_t p = i / C;
-    const int xx = p % W, yy = (p / W) % H, b = (int)(p / ((size_t)W * H));
-    const size_t base = ((size_t)(b * 2 * H + 2 * yy) * W2 + 2 * xx) * C + c;
-    const float s = bf2f(dy[base]) + bf2f(dy[base + C]) + bf2f(dy[base + (size_t)W2 * C]) +
-                    bf2f(dy[base + (size_t)W2 * C + C]);
-    dx[i] = f2bf(s);
-  }
-}
-// out[p] = [a[p] (Ca channels) | b[p] (Cb channels)]
-__global__ void k_concat(const bf16_t *a, const bf16_t *b, bf16_t *out, size_t P, int Ca, int Cb) {
-  const int C = Ca + Cb;
-  const size_t n = P * C;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const size_t p = i / C;
-    const int c = i % C;
-    out[i] = c < Ca ? a[p * Ca + c] : b[p * Cb + c - Ca];
-  }
-}
-// ga = g[:, :Ca] ; gb = g[:, Ca:]
-__global__ void k_split_bwd(const bf16_t *g, bf16_t *ga, bf16_t *gb, size_t P, int Ca, int Cb) {
-  const int C = Ca + Cb;
-  const size_t n = P * C;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const size_t p = i / C;
-    const int c = i % C;
-    if (c < Ca)
-      ga[p * Ca + c] = g[i];
-    else
-      gb[p * Cb + c - Ca] = g[i];
+    const bf16_t *src = gc + ((size_t)(b * 2 * H + 2 * yy) * 2 * W + 2 * xx) * Ct + Ct - C + c;
+    float v[8], g[3][8];
+    unpack8(*reinterpret_cast<const uint4 *>(src), v);
+    unpack8(*reinterpret_cast<const uint4 *>(src + Ct), g[0]);
+    unpack8(*reinterpret_cast<const uint4 *>(src + row), g[1]);
+    unpack8(*reinterpret_cast<const uint4 *>(src + row + Ct), g[2]);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = v[j] + g[0][j] + g[1][j] + g[2][j];
+    store8_masked(dx + p * C + c, v, y + p * C + c);
   }
 }
 
@@ -706,38 +904,53 @@ __global__ void k_net_output(const float *out, const cf *uin, cf *u0, size_t n) 
 }
 // Relative L2 loss per sample, averaged over the batch:
 //   L = (1/B) sum_b ||out_b - (u_b - uin_b)||^2 / ||u_b - uin_b||^2
-// One block per sample; writes the per-sample loss and the output gradient (bf16, 32 channels).
-__global__ void k_rel_l2(const float *out, const cf *uin, const cf *u, bf16_t *dout, double *loss_b, int N, int B) {
-  const int b = blockIdx.x;
-  double e2 = 0.0, t2 = 0.0;
-  for (int q = threadIdx.x; q < N; q += blockDim.x) {
+// k_rel_l2_part sums both norms over LOSS_PARTS parts of a sample (one block
+// each: a block per sample left 240 CUs idle), k_rel_l2 adds the parts and
+// writes the per-sample loss and the output gradient (bf16, 32 channels).
+constexpr int LOSS_PARTS = 32;
+__global__ void __launch_bounds__(256) k_rel_l2_part(const float *out, const cf *uin, const cf *u, double *part,
+                                                     int N) {
+  __shared__ double scratch[2 * 16];
+  const int b = blockIdx.y;
+  double acc[2] = {0.0, 0.0};
+  for (int q = blockIdx.x * 256 + threadIdx.x; q < N; q += LOSS_PARTS * 256) {
     const size_t i = (size_t)b * N + q;
+    const float2 o = *reinterpret_cast<const float2 *>(out + i * 32);
     const double tr = (double)u[i].x - uin[i].x, ti = (double)u[i].y - uin[i].y;
-    const double er = out[i * 32] - tr, ei = out[i * 32 + 1] - ti;
-    e2 += er * er + ei * ei;
-    t2 += tr * tr + ti * ti;
+    const double er = o.x - tr, ei = o.y - ti;
+    acc[0] += er * er + ei * ei;
+    acc[1] += tr * tr + ti * ti;
   }
-  __shared__ double s1[256], s2[256];
-  s1[threadIdx.x] = e2;
-  s2[threadIdx.x] = t2;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) {
-      s1[threadIdx.x] += s1[threadIdx.x + o];
-      s2[threadIdx.x] += s2[threadIdx.x + o];
-    }
-    __syncthreads();
+  block_sum<2>(acc, scratch);
+  if (threadIdx.x == 0) {
+    part[2 * (b * LOSS_PARTS + blockIdx.x)] = acc[0];
+    part[2 * (b * LOSS_PARTS + blockIdx.x) + 1] = acc[1];
   }
-  const double tt = fmax(s2[0], 1e-30);
-  if (threadIdx.x == 0) loss_b[b] = s1[0] / tt;
+}
+__global__ void __launch_bounds__(256) k_rel_l2(const float *out, const cf *uin, const cf *u, const double *part,
+                                                bf16_t *dout, double *loss_b, int N, int B) {
+  const int b = blockIdx.y;
+  double e2 = 0.0, t2 = 0.0;
+  for (int k = 0; k < LOSS_PARTS; ++k) {
+    e2 += part[2 * (b * LOSS_PARTS + k)];
+    t2 += part[2 * (b * LOSS_PARTS + k) + 1];
+  }
+  const double tt = fmax(t2, 1e-30);
+  if (blockIdx.x == 0 && threadIdx.x == 0) loss_b[b] = e2 / tt;
   const float scale = (float)(2.0 / (tt * B));
-  for (int q = threadIdx.x; q < N; q += blockDim.x) {
+  // four threads a pixel, eight of its 32 channels each
+  const int seg = threadIdx.x & 3;
+  for (int q = blockIdx.x * 64 + (threadIdx.x >> 2); q < N; q += gridDim.x * 64) {
     const size_t i = (size_t)b * N + q;
-    const float tr = u[i].x - uin[i].x, ti = u[i].y - uin[i].y;
-    bf16_t *o = dout + i * 32;
-    o[0] = f2bf(scale * (out[i * 32] - tr));
-    o[1] = f2bf(scale * (out[i * 32 + 1] - ti));
-    for (int c = 2; c < 32; ++c) o[c] = 0;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (seg == 0) {
+      const float2 o = *reinterpret_cast<const float2 *>(out + i * 32);
+      bf16_t *e = reinterpret_cast<bf16_t *>(&v);
+      const float tr = u[i].x - uin[i].x, ti = u[i].y - uin[i].y;
+      e[0] = f2bf(scale * (o.x - tr));
+      e[1] = f2bf(scale * (o.y - ti));
+    }
+    *reinterpret_cast<uint4 *>(dout + i * 32 + seg * 8) = v;
   }
 }
 
@@ -869,6 +1082,8 @@ static bool conv_tile_t(hipStream_t s, const bf16_t *x, const bf16_t *w, const f
       TILE_L(true, TOUT_BF16, TIN_X);
     else
       TILE_L(false, TOUT_BF16, TIN_X);
+  } else if (tin == TIN_X && tout == TOUT_MASK && !relu) {
+    TILE_L(false, TOUT_MASK, TIN_X);
   } else if (tin == TIN_X && tout == TOUT_F32) {
     if (relu)
       TILE_L(true, TOUT_F32, TIN_X);
@@ -986,18 +1201,27 @@ static int conv_fwd(hipStream_t s, const bf16_t *x, const bf16_t *w, const float
   return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
 }
 
-static int conv_wgrad(hipStream_t s, const bf16_t *x, const bf16_t *dy, float *part, float *dw, int B, int H, int W,
-                      int Ci, int Co, int max_splits) {
-  const int M = B * H * W;
-  int splits = std::max(1, std::min(max_splits, M / 1024));
-  int pps = (M + splits - 1) / splits;
-  pps = (pps + WG_PIX - 1) / WG_PIX * WG_PIX;
-  splits = (M + pps - 1) / pps;
-  dim3 g(Ci / 32, 9 * (Co / 32), splits);
-  hipLaunchKernelGGL(k_conv3x3_wgrad, g, dim3(256), 0, s, x, dy, part, H, W, Ci, Co, pps, M);
-  const size_t n = (size_t)9 * Co * Ci;
-  hipLaunchKernelGGL(k_sum_splits, grid1(n), dim3(256), 0, s, part, dw, n, splits);
-  return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
+// Partial weight (and, with bpart, bias) gradients of one layer into at most
+// max_splits partials of 9 Co Ci (Co) elements; returns the number written.
+// One block per CU over all channel pairs, and tasks of as many rows as still
+// give every wave one: longer tasks read less halo, more of them keep the
+// CUs busy.
+constexpr int WG_BLOCKS = 256;
+static int conv_wgrad(hipStream_t s, const bf16_t *x, const bf16_t *dy, float *part, float *bpart, int B, int H,
+                      int W, int Ci, int Co, int max_splits, const bf16_t *x2 = nullptr, int C1 = 0) {
+  WgArgs a{};
+  a.x = x, a.dy = dy, a.x2 = x2, a.part = part, a.bpart = bpart;
+  a.H = H, a.W = W, a.Ci = Ci, a.Co = Co, a.C1 = C1;
+  a.strips = (W + 15) / 16;
+  const int pairs = (Ci / 32) * (Co / 32);
+  int splits = std::max(1, std::min(max_splits, WG_BLOCKS / pairs));
+  for (a.rh = 32; a.rh > 4; a.rh /= 2)
+    if ((long long)B * a.strips * ((H + a.rh - 1) / a.rh) >= (long long)splits * WG_WAVES) break;
+  a.segs = (H + a.rh - 1) / a.rh;
+  a.tasks = B * a.strips * a.segs;
+  splits = std::min(splits, (a.tasks + WG_WAVES - 1) / WG_WAVES);
+  hipLaunchKernelGGL(k_conv3x3_wgrad, dim3(Ci / 32, Co / 32, splits), dim3(64 * WG_WAVES), 0, s, a);
+  return splits;
 }
 
 // ------------------------------------------------------------------ the network
@@ -1016,18 +1240,17 @@ struct Net {
   size_t nparams = 0;
   float *params = nullptr, *grads = nullptr, *adam_m = nullptr, *adam_v = nullptr;
   bf16_t *wb = nullptr;      // bf16 copy of the parameter vector (weights used by the kernels)
-  bf16_t *wt = nullptr;      // scratch: flipped/transposed weights of one layer
+  bf16_t *wt = nullptr;      // flipped/transposed weights, at the parameter vector's offsets
   float *wg_part = nullptr;  // weight-gradient split partials
   size_t wg_part_elems = 0;
   float *kws = nullptr;      // split-K partials of the forward convolutions
   size_t kws_elems = 0;
-  int max_splits = 64;
   long long adam_t = 0;
   // activations (bf16, NHWC) and gradients, allocated for max_batch
   std::vector<bf16_t *> act, gact;
   std::vector<size_t> act_elems;
   float *out = nullptr;      // head output, fp32 [B][H][W][32]
-  double *loss_b = nullptr;
+  double *loss_b = nullptr, *loss_part = nullptr;   // per-sample loss, partial norms of k_rel_l2_part
   double *gn_part = nullptr; // gradient-norm partials [GN_BLOCKS]
   float *gscale = nullptr;   // clipping factor applied by Adam
   std::vector<void *> allocs;
@@ -1035,11 +1258,11 @@ struct Net {
 
 // activation slots
 enum {
-  A_X0, A_E1A, A_E1B, A_P1, A_E2A, A_E2B, A_P2, A_E3A, A_E3B, A_P3, A_BA, A_BB, A_U3, A_C3, A_D3A, A_D3B, A_U2, A_C2,
-  A_D2A, A_D2B, A_U1, A_C1, A_D1A, A_D1B, A_COUNT
+  A_X0, A_E1A, A_E1B, A_P1, A_E2A, A_E2B, A_P2, A_E3A, A_E3B, A_P3, A_BA, A_BB, A_D3A, A_D3B, A_D2A, A_D2B, A_D1A,
+  A_D1B, A_COUNT
 };
-// gradient-only slots reuse the same indexing; extra skip gradient slots
-enum { G_SKIP1 = A_COUNT, G_SKIP2, G_SKIP3, G_OUT, G_COUNT };
+// gradients: the same slots, the decoder inputs' [skip | upsampled] and the head's output
+enum { G_C3 = A_COUNT, G_C2, G_C1, G_OUT, G_COUNT };
 
 template <typename T> static int nn_alloc(Net &n, T *&p, size_t elems) {
   void *q = nullptr;
@@ -1069,22 +1292,18 @@ static int net_build(Net &n) {
   }
   n.nparams = off;
   const size_t B = n.max_batch, P1 = (size_t)n.H * n.W, P2 = P1 / 4, P3 = P1 / 16, P4 = P1 / 64;
-  const size_t sizes[A_COUNT] = {B * P1 * 32, B * P1 * c1, B * P1 * c1, B * P2 * c1, B * P2 * c2, B * P2 * c2,
+  const size_t sizes[G_COUNT] = {B * P1 * 32, B * P1 * c1, B * P1 * c1, B * P2 * c1, B * P2 * c2, B * P2 * c2,
                                  B * P3 * c2, B * P3 * c3, B * P3 * c3, B * P4 * c3, B * P4 * c4, B * P4 * c4,
-                                 B * P3 * c4, B * P3 * (c3 + c4), B * P3 * c3, B * P3 * c3, B * P2 * c3,
-                                 B * P2 * (c2 + c3), B * P2 * c2, B * P2 * c2, B * P1 * c2, B * P1 * (c1 + c2),
-                                 B * P1 * c1, B * P1 * c1};
+                                 B * P3 * c3, B * P3 * c3, B * P2 * c2, B * P2 * c2, B * P1 * c1, B * P1 * c1,
+                                 B * P3 * (c3 + c4), B * P2 * (c2 + c3), B * P1 * (c1 + c2), B * P1 * 32};
   n.act.assign(A_COUNT, nullptr);
   n.gact.assign(G_COUNT, nullptr);
   n.act_elems.assign(sizes, sizes + A_COUNT);
   int rc;
-  for (int i = 0; i < A_COUNT; ++i) {
-    if ((rc = nn_alloc(n, n.act[i], sizes[i]))) return rc;
+  for (int i = 0; i < G_COUNT; ++i) {
+    if (i < A_COUNT && (rc = nn_alloc(n, n.act[i], sizes[i]))) return rc;
     if ((rc = nn_alloc(n, n.gact[i], sizes[i]))) return rc;
   }
-  if ((rc = nn_alloc(n, n.gact[G_SKIP1], B * P1 * c1)) || (rc = nn_alloc(n, n.gact[G_SKIP2], B * P2 * c2)) ||
-      (rc = nn_alloc(n, n.gact[G_SKIP3], B * P3 * c3)) || (rc = nn_alloc(n, n.gact[G_OUT], B * P1 * 32)))
-    return rc;
   // split-K workspace: the largest need of any forward layer at max_batch
   const int lev[15] = {1, 1, 2, 2, 4, 4, 8, 8, 4, 4, 2, 2, 1, 1, 1};
   for (int l = 0; l < (int)n.L.size(); ++l) {
@@ -1097,22 +1316,25 @@ static int net_build(Net &n) {
   if ((rc = nn_alloc(n, n.params, n.nparams)) || (rc = nn_alloc(n, n.grads, n.nparams)) ||
       (rc = nn_alloc(n, n.adam_m, n.nparams)) || (rc = nn_alloc(n, n.adam_v, n.nparams)) ||
       (rc = nn_alloc(n, n.wb, n.nparams)) || (rc = nn_alloc(n, n.out, B * P1 * 32)) ||
-      (rc = nn_alloc(n, n.loss_b, B)) || (rc = nn_alloc(n, n.gn_part, GN_BLOCKS)) ||
+      (rc = nn_alloc(n, n.loss_b, B)) || (rc = nn_alloc(n, n.loss_part, 2 * LOSS_PARTS * B)) || (rc = nn_alloc(n, n.gn_part, GN_BLOCKS)) ||
       (rc = nn_alloc(n, n.gscale, 1)))
     return rc;
-  size_t maxw = 0;
-  for (auto &l : n.L) maxw = std::max(maxw, (size_t)9 * l.Ci * l.Co);
-  if ((rc = nn_alloc(n, n.wt, maxw))) return rc;
-  n.wg_part_elems = maxw * n.max_splits;
-  if ((rc = nn_alloc(n, n.wg_part, n.wg_part_elems))) return rc;
+  // split partials of every layer's weight and bias gradients at once: a
+  // layer has at most WG_BLOCKS blocks of 9 x 32 x 32 weights
+  for (auto &l : n.L) {
+    const size_t pairs = (size_t)(l.Ci / 32) * (l.Co / 32), splits = std::max<size_t>(1, WG_BLOCKS / pairs);
+    n.wg_part_elems += splits * ((size_t)9 * l.Ci * l.Co + l.Co);
+  }
+  if ((rc = nn_alloc(n, n.wt, n.nparams)) || (rc = nn_alloc(n, n.wg_part, n.wg_part_elems))) return rc;
   return CISOR_OK;
 }
 
 static const bf16_t *wptr(const Net &n, int l) { return n.wb + n.L[l].woff; }
 static const float *bptr(const Net &n, int l) { return n.params + n.L[l].boff; }
 
-// fused: the decoder convolutions read the skip tensor and the low-resolution
-// tensor in place (inference); otherwise the upsampled concatenations are
+// The decoder convolutions read the skip tensor and the low-resolution tensor
+// in place.  fused (inference): the network input and the pooled tensors are
+// formed inside the convolutions that read them too; otherwise they are
 // materialised, as the weight gradients of training read them.
 static int net_forward(Net &n, const float *f, const cf *uin, const cf *ub, int B, bool fused, cf *u0 = nullptr) {
   hipStream_t s = n.stream;
@@ -1158,38 +1380,17 @@ static int net_forward(Net &n, const float *f, const cf *uin, const cf *ub, int 
   }
 #undef FUSED_IN
   CONV(7, A[A_BA], A[A_BB], H / 8, W / 8);
-  if (fused) {
-    if ((rc = conv_fwd(s, A[A_E3B], wptr(n, 8), bptr(n, 8), A[A_D3A], B, H / 4, W / 4, n.L[8].Ci, n.L[8].Co,
-                       n.L[8].relu, false, 0, A[A_BB], c3, n.kws, n.kws_elems)))
-      return rc;
-  } else {
-    hipLaunchKernelGGL(k_upsample, grid1(n.act_elems[A_U3]), dim3(256), 0, s, A[A_BB], A[A_U3], B, H / 4, W / 4, c4);
-    hipLaunchKernelGGL(k_concat, grid1(n.act_elems[A_C3]), dim3(256), 0, s, A[A_E3B], A[A_U3], A[A_C3],
-                       (size_t)B * N / 16, c3, c4);
-    CONV(8, A[A_C3], A[A_D3A], H / 4, W / 4);
-  }
+  if ((rc = conv_fwd(s, A[A_E3B], wptr(n, 8), bptr(n, 8), A[A_D3A], B, H / 4, W / 4, n.L[8].Ci, n.L[8].Co, n.L[8].relu,
+                     false, 0, A[A_BB], c3, n.kws, n.kws_elems)))
+    return rc;
   CONV(9, A[A_D3A], A[A_D3B], H / 4, W / 4);
-  if (fused) {
-    if ((rc = conv_fwd(s, A[A_E2B], wptr(n, 10), bptr(n, 10), A[A_D2A], B, H / 2, W / 2, n.L[10].Ci, n.L[10].Co,
-                       n.L[10].relu, false, 0, A[A_D3B], c2, n.kws, n.kws_elems)))
-      return rc;
-  } else {
-    hipLaunchKernelGGL(k_upsample, grid1(n.act_elems[A_U2]), dim3(256), 0, s, A[A_D3B], A[A_U2], B, H / 2, W / 2, c3);
-    hipLaunchKernelGGL(k_concat, grid1(n.act_elems[A_C2]), dim3(256), 0, s, A[A_E2B], A[A_U2], A[A_C2],
-                       (size_t)B * N / 4, c2, c3);
-    CONV(10, A[A_C2], A[A_D2A], H / 2, W / 2);
-  }
+  if ((rc = conv_fwd(s, A[A_E2B], wptr(n, 10), bptr(n, 10), A[A_D2A], B, H / 2, W / 2, n.L[10].Ci, n.L[10].Co, n.L[10].relu,
+                     false, 0, A[A_D3B], c2, n.kws, n.kws_elems)))
+    return rc;
   CONV(11, A[A_D2A], A[A_D2B], H / 2, W / 2);
-  if (fused) {
-    if ((rc = conv_fwd(s, A[A_E1B], wptr(n, 12), bptr(n, 12), A[A_D1A], B, H, W, n.L[12].Ci, n.L[12].Co,
-                       n.L[12].relu, false, 0, A[A_D2B], c1, n.kws, n.kws_elems)))
-      return rc;
-  } else {
-    hipLaunchKernelGGL(k_upsample, grid1(n.act_elems[A_U1]), dim3(256), 0, s, A[A_D2B], A[A_U1], B, H, W, c2);
-    hipLaunchKernelGGL(k_concat, grid1(n.act_elems[A_C1]), dim3(256), 0, s, A[A_E1B], A[A_U1], A[A_C1],
-                       (size_t)B * N, c1, c2);
-    CONV(12, A[A_C1], A[A_D1A], H, W);
-  }
+  if ((rc = conv_fwd(s, A[A_E1B], wptr(n, 12), bptr(n, 12), A[A_D1A], B, H, W, n.L[12].Ci, n.L[12].Co, n.L[12].relu,
+                     false, 0, A[A_D2B], c1, n.kws, n.kws_elems)))
+    return rc;
   CONV(13, A[A_D1A], A[A_D1B], H, W);
 #undef CONV
   // head: with u0 set (inference), fused, u0 = u_in + (y0 + i y1) written by
@@ -1206,65 +1407,88 @@ static int net_forward(Net &n, const float *f, const cf *uin, const cf *ub, int 
   return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
 }
 
-// backward through one conv layer: gy is the gradient at the layer output
-// (post-activation); writes the weight/bias gradients and, if gx != null, the
-// input gradient.
-static int layer_bwd(Net &n, int l, const bf16_t *x, const bf16_t *y, bf16_t *gy, bf16_t *gx, int B, int h, int w) {
-  hipStream_t s = n.stream;
+// Data gradient of layer l: gx = conv(gy, w') with w' the flipped weights,
+// and, with mask, the ReLU of the layer that produced its input.
+static int layer_dgrad(Net &n, int l, const bf16_t *gy, bf16_t *gx, const bf16_t *mask, int B, int h, int w) {
   const ConvLayer &L = n.L[l];
-  const size_t ny = (size_t)B * h * w * L.Co;
-  if (L.relu) hipLaunchKernelGGL(k_relu_bwd, grid1(ny), dim3(256), 0, s, gy, y, gy, ny);
-  int rc;
-  if ((rc = conv_wgrad(s, x, gy, n.wg_part, n.grads + L.woff, B, h, w, L.Ci, L.Co, n.max_splits))) return rc;
-  hipLaunchKernelGGL(k_bias_grad, dim3(L.Co), dim3(256), 0, s, gy, n.grads + L.boff, B * h * w, L.Co);
-  if (gx) {
-    hipLaunchKernelGGL(k_flip_transpose, grid1((size_t)9 * L.Ci * L.Co), dim3(256), 0, s, wptr(n, l), n.wt, L.Ci, L.Co);
-    if ((rc = conv_fwd(s, gy, n.wt, nullptr, gx, B, h, w, L.Co, L.Ci, false, false))) return rc;
-  }
+  TileIO io;
+  io.mask = mask;
+  if (conv_fwd_tiled(n.stream, gy, n.wt + L.woff, nullptr, gx, B, h, w, L.Co, L.Ci, false,
+                     mask ? TOUT_MASK : TOUT_BF16, TIN_X, nullptr, 0, io))
+    return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
+  if (int rc = conv_fwd(n.stream, gy, n.wt + L.woff, nullptr, gx, B, h, w, L.Co, L.Ci, false, false)) return rc;
+  const size_t nx = (size_t)B * h * w * L.Ci;
+  if (mask) hipLaunchKernelGGL(k_relu_bwd, grid1(nx), dim3(256), 0, n.stream, gx, mask, gx, nx);
   return CISOR_OK;
 }
 
+// Every buffer named G[...] of a convolution's output holds the gradient
+// before that convolution's ReLU: the kernels that produce it apply the mask.
 static int net_backward(Net &n, int B) {
   hipStream_t s = n.stream;
   const int H = n.H, W = n.W;
   const int c1 = n.base, c2 = 2 * n.base, c3 = 4 * n.base, c4 = 8 * n.base;
   auto &A = n.act;
   auto &G = n.gact;
-  const size_t N = (size_t)H * W;
-  int rc;
-#define BWD(l, xin, yout, gy, gx, h, w) \
-  if ((rc = layer_bwd(n, l, xin, yout, gy, gx, B, h, w))) return rc;
-  BWD(14, A[A_D1B], nullptr, G[G_OUT], G[A_D1B], H, W);
-  BWD(13, A[A_D1A], A[A_D1B], G[A_D1B], G[A_D1A], H, W);
-  BWD(12, A[A_C1], A[A_D1A], G[A_D1A], G[A_C1], H, W);
-  hipLaunchKernelGGL(k_split_bwd, grid1(n.act_elems[A_C1]), dim3(256), 0, s, G[A_C1], G[G_SKIP1], G[A_U1],
-                     (size_t)B * N, c1, c2);
-  hipLaunchKernelGGL(k_upsample_bwd, grid1(n.act_elems[A_D2B]), dim3(256), 0, s, G[A_U1], G[A_D2B], B, H / 2, W / 2, c2);
-  BWD(11, A[A_D2A], A[A_D2B], G[A_D2B], G[A_D2A], H / 2, W / 2);
-  BWD(10, A[A_C2], A[A_D2A], G[A_D2A], G[A_C2], H / 2, W / 2);
-  hipLaunchKernelGGL(k_split_bwd, grid1(n.act_elems[A_C2]), dim3(256), 0, s, G[A_C2], G[G_SKIP2], G[A_U2],
-                     (size_t)B * N / 4, c2, c3);
-  hipLaunchKernelGGL(k_upsample_bwd, grid1(n.act_elems[A_D3B]), dim3(256), 0, s, G[A_U2], G[A_D3B], B, H / 4, W / 4, c3);
-  BWD(9, A[A_D3A], A[A_D3B], G[A_D3B], G[A_D3A], H / 4, W / 4);
-  BWD(8, A[A_C3], A[A_D3A], G[A_D3A], G[A_C3], H / 4, W / 4);
-  hipLaunchKernelGGL(k_split_bwd, grid1(n.act_elems[A_C3]), dim3(256), 0, s, G[A_C3], G[G_SKIP3], G[A_U3],
-                     (size_t)B * N / 16, c3, c4);
-  hipLaunchKernelGGL(k_upsample_bwd, grid1(n.act_elems[A_BB]), dim3(256), 0, s, G[A_U3], G[A_BB], B, H / 8, W / 8, c4);
-  BWD(7, A[A_BA], A[A_BB], G[A_BB], G[A_BA], H / 8, W / 8);
-  BWD(6, A[A_P3], A[A_BA], G[A_BA], G[A_P3], H / 8, W / 8);
-  // encoder 3: gradient = skip part + pooled path
-  hipLaunchKernelGGL(k_avgpool_bwd, grid1(n.act_elems[A_E3B]), dim3(256), 0, s, G[A_P3], G[G_SKIP3], B, H / 4, W / 4,
-                     c3, 1);
-  BWD(5, A[A_E3A], A[A_E3B], G[G_SKIP3], G[A_E3A], H / 4, W / 4);
-  BWD(4, A[A_P2], A[A_E3A], G[A_E3A], G[A_P2], H / 4, W / 4);
-  hipLaunchKernelGGL(k_avgpool_bwd, grid1(n.act_elems[A_E2B]), dim3(256), 0, s, G[A_P2], G[G_SKIP2], B, H / 2, W / 2,
-                     c2, 1);
-  BWD(3, A[A_E2A], A[A_E2B], G[G_SKIP2], G[A_E2A], H / 2, W / 2);
-  BWD(2, A[A_P1], A[A_E2A], G[A_E2A], G[A_P1], H / 2, W / 2);
-  hipLaunchKernelGGL(k_avgpool_bwd, grid1(n.act_elems[A_E1B]), dim3(256), 0, s, G[A_P1], G[G_SKIP1], B, H, W, c1, 1);
-  BWD(1, A[A_E1A], A[A_E1B], G[G_SKIP1], G[A_E1A], H, W);
-  BWD(0, A[A_X0], A[A_E1A], G[A_E1A], nullptr, H, W);
-#undef BWD
+  FlipList flip;
+  for (auto &l : n.L) flip.l[flip.count++] = {(unsigned)l.woff, l.Ci, l.Co};
+  hipLaunchKernelGGL(k_flip_transpose, dim3(64, flip.count), dim3(256), 0, s, n.wb, n.wt, flip);
+  RedList red;
+  float *part = n.wg_part;
+  int rc = CISOR_OK;
+  // weight and bias gradients of layer l (input xin, or [xin (C1) | up2(xup)])
+  auto wgrad = [&](int l, const bf16_t *xin, const bf16_t *gy, int h, int w, const bf16_t *xup = nullptr, int C1 = 0) {
+    const ConvLayer &L = n.L[l];
+    const size_t nw = (size_t)9 * L.Ci * L.Co;
+    const int most = std::max(1, WG_BLOCKS / ((L.Ci / 32) * (L.Co / 32)));
+    float *bpart = part + (size_t)most * nw;
+    const int splits = conv_wgrad(s, xin, gy, part, bpart, B, h, w, L.Ci, L.Co, most, xup, C1);
+    red.add(part, n.grads + L.woff, nw, splits);
+    red.add(bpart, n.grads + L.boff, L.Co, splits);
+    part = bpart + (size_t)most * L.Co;
+  };
+  auto dgrad = [&](int l, const bf16_t *gy, bf16_t *gx, const bf16_t *mask, int h, int w) {
+    if (rc == CISOR_OK) rc = layer_dgrad(n, l, gy, gx, mask, B, h, w);
+  };
+  // a decoder level (layers l + 1 and l): from G[b] to the gradient gc of its input
+  auto decoder = [&](int l, int b, int a, const bf16_t *skip, int Cs, const bf16_t *low, bf16_t *gc, int h, int w) {
+    wgrad(l + 1, A[a], G[b], h, w);
+    dgrad(l + 1, G[b], G[a], A[a], h, w);
+    wgrad(l, skip, G[a], h, w, low, Cs);
+    dgrad(l, G[a], gc, nullptr, h, w);
+  };
+  auto up_bwd = [&](const bf16_t *gc, int slot, int h, int w, int C, int Ct) {   // h, w: the lower level's size
+    hipLaunchKernelGGL(k_upsample_bwd, grid1((size_t)B * h * w * C / 8), dim3(256), 0, s, gc, A[slot], G[slot], B, h, w,
+                       C, Ct);
+  };
+  auto pool_bwd = [&](const bf16_t *gp, const bf16_t *gc, int slot, int h, int w, int C, int Ct) {
+    hipLaunchKernelGGL(k_pool_skip_bwd, grid1((size_t)B * h * w * C / 8), dim3(256), 0, s, gp, gc, A[slot], G[slot], B,
+                       h, w, C, Ct);
+  };
+  wgrad(14, A[A_D1B], G[G_OUT], H, W);
+  dgrad(14, G[G_OUT], G[A_D1B], A[A_D1B], H, W);
+  decoder(12, A_D1B, A_D1A, A[A_E1B], c1, A[A_D2B], G[G_C1], H, W);
+  up_bwd(G[G_C1], A_D2B, H / 2, W / 2, c2, c1 + c2);
+  decoder(10, A_D2B, A_D2A, A[A_E2B], c2, A[A_D3B], G[G_C2], H / 2, W / 2);
+  up_bwd(G[G_C2], A_D3B, H / 4, W / 4, c3, c2 + c3);
+  decoder(8, A_D3B, A_D3A, A[A_E3B], c3, A[A_BB], G[G_C3], H / 4, W / 4);
+  up_bwd(G[G_C3], A_BB, H / 8, W / 8, c4, c3 + c4);
+  // an encoder level (layers l + 1 and l) from G[b] to the gradient of its pooled input
+  auto encoder = [&](int l, int b, int a, int in, int h, int w) {
+    wgrad(l + 1, A[a], G[b], h, w);
+    dgrad(l + 1, G[b], G[a], A[a], h, w);
+    wgrad(l, A[in], G[a], h, w);
+    if (l) dgrad(l, G[a], G[in], nullptr, h, w);
+  };
+  encoder(6, A_BB, A_BA, A_P3, H / 8, W / 8);
+  pool_bwd(G[A_P3], G[G_C3], A_E3B, H / 4, W / 4, c3, c3 + c4);
+  encoder(4, A_E3B, A_E3A, A_P2, H / 4, W / 4);
+  pool_bwd(G[A_P2], G[G_C2], A_E2B, H / 2, W / 2, c2, c2 + c3);
+  encoder(2, A_E2B, A_E2A, A_P1, H / 2, W / 2);
+  pool_bwd(G[A_P1], G[G_C1], A_E1B, H, W, c1, c1 + c2);
+  encoder(0, A_E1B, A_E1A, A_X0, H, W);
+  if (rc) return rc;
+  hipLaunchKernelGGL(k_sum_splits, dim3(red.blocks), dim3(256), 0, s, red);
   return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
 }
 
@@ -1375,8 +1599,11 @@ int cisor_net_loss_grad(cisor_net *h, const float *f, const void *u_in, const vo
   if (((size_t)batch * n.H * n.W) % 8192) return CISOR_E_ARG;
   int rc = net_forward(n, f, (const cf *)u_in, (const cf *)u_born, batch, false);
   if (rc) return rc;
-  hipLaunchKernelGGL(k_rel_l2, dim3(batch), dim3(256), 0, n.stream, n.out, (const cf *)u_in, (const cf *)u,
-                     n.gact[G_OUT], n.loss_b, n.H * n.W, batch);
+  const int N = n.H * n.W;
+  hipLaunchKernelGGL(k_rel_l2_part, dim3(LOSS_PARTS, batch), dim3(256), 0, n.stream, n.out, (const cf *)u_in,
+                     (const cf *)u, n.loss_part, N);
+  hipLaunchKernelGGL(k_rel_l2, dim3(64, batch), dim3(256), 0, n.stream, n.out, (const cf *)u_in, (const cf *)u,
+                     (const double *)n.loss_part, n.gact[G_OUT], n.loss_b, N, batch);
   if ((rc = net_backward(n, batch))) return rc;
   if (loss) {
     std::vector<double> lb(batch);
@@ -1426,8 +1653,12 @@ int cisor_nn_conv3x3_ex(const void *x, const void *x2, int C1, const void *w, co
 int cisor_nn_conv3x3_wgrad(const void *x, const void *dy, float *dw, float *scratch, int B, int H, int W, int Ci,
                            int Co, int max_splits, void *stream) {
   if (!x || !dy || !dw || !scratch || Ci % 32 || Co % 32 || max_splits < 1) return CISOR_E_ARG;
-  return conv_wgrad((hipStream_t)stream, (const bf16_t *)x, (const bf16_t *)dy, scratch, dw, B, H, W, Ci, Co,
-                    max_splits);
+  const int splits = conv_wgrad((hipStream_t)stream, (const bf16_t *)x, (const bf16_t *)dy, scratch, nullptr, B, H, W,
+                                Ci, Co, max_splits);
+  RedList l;
+  l.add(scratch, dw, (size_t)9 * Co * Ci, splits);
+  hipLaunchKernelGGL(k_sum_splits, dim3(l.blocks), dim3(256), 0, (hipStream_t)stream, l);
+  return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
 }
 
 }  // extern "C"
