@@ -9,66 +9,129 @@
 // and a second kernel sums the partials in FP64 in a fixed order.  The FP32
 // path runs on the matrix cores (v_mfma_f32_32x32x2_f32) as a real GEMM on
 // the interleaved complex operands, with Gauss's three real products per
-// complex product (four without); the FP64 path uses plain FMA.
-#include <vector>
+// complex product (four without); the FP64 path on v_mfma_f64_16x16x4_f64.
+#include <type_traits>
 
 #include "internal.hpp"
 
 namespace cisor {
 
 constexpr int PJ_KCHUNK = PROJ_KCHUNK;  // pixels per split-K chunk
-constexpr int PJ_MT = 32;        // receivers per block tile
-constexpr int PJ_TT = 64;        // transmitters per block tile
 
-// ---------------------------------------------------------------- generic (FMA) projection
-// Block: 256 threads; tile = 32 receivers x up to 64 transmitters, one K chunk.
-// Each thread accumulates 8 (m, t) pairs.
-template <typename R>
-__global__ void __launch_bounds__(256) k_project_fma(const cplx_t<R> *H, const R *f, const cplx_t<R> *u, cd *part,
-                                                     int M, int N, int T) {
+// ---------------------------------------------------------------- FP64 projection
+// Complex128 contexts, and complex64 ones with more than 64 transmitters:
+// every product and sum in FP64 on v_mfma_f64_16x16x4_f64 (four real products
+// per complex one).  Lane l supplies A[l%16][l/16] and B[l/16][l%16] and holds
+// C[4 r + l/16][l%16] in accumulator register r.  A block of eight waves owns
+// MA x TB tiles of 16 receivers x 16 transmitters over one K chunk; each wave
+// contracts an eighth of the chunk and the waves' sums are added in wave order
+// at the end, so that a small problem still has waves on many SIMDs.  Operands go from
+// global memory to registers as they are: within a group of 16 pixels lane
+// group l/16 takes the four consecutive pixels 4 (l/16) .. + 4, one per
+// MFMA step (the order of the sum is free), 256 contiguous bytes a row.
+// Rows past M or T repeat the last one and are not stored; pixels past the
+// chunk are zeros.
+// Bound by the FP64 matrix rate and the fields' bytes about equally at 36 x
+// 98304 x 81.  Against one thread per receiver with eight FMA sums on operands
+// staged in LDS: 260 -> 123 us at 36 x 98304 x 81, and 160 -> 10.7 us at 32 x
+// 1024 x 8, where that left two blocks.
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+constexpr int PD_WAVES = 8;
+
+template <typename R, int MA, int TB>
+__global__ void __launch_bounds__(64 * PD_WAVES, 2) k_project_f64(const cplx_t<R> *H, const R *f, const cplx_t<R> *u,
+                                                                  cd *part, int M, int N, int T) {
   using C = cplx_t<R>;
-  constexpr int KS = 32;  // pixels staged per step
-  __shared__ C sh[PJ_MT][KS + 1];
-  __shared__ C su[PJ_TT][KS + 1];
-  const int m0 = blockIdx.x * PJ_MT, t0 = blockIdx.y * PJ_TT, kc = blockIdx.z;
-  const int k0 = kc * PJ_KCHUNK;
-  const int kend = min(k0 + PJ_KCHUNK, N);
-  const int tm = threadIdx.x % PJ_MT;     // receiver within tile
-  const int tg = threadIdx.x / PJ_MT;     // 0..7: transmitter group
-  double accr[8] = {0}, acci[8] = {0};
-  for (int kb = k0; kb < kend; kb += KS) {
-    for (int i = threadIdx.x; i < PJ_MT * KS; i += 256) {
-      const int mm = i / KS, kk = i % KS;
-      const int m = m0 + mm, k = kb + kk;
-      sh[mm][kk] = (m < M && k < kend) ? H[(size_t)m * N + k] : mk<C>(0, 0);
-    }
-    for (int i = threadIdx.x; i < PJ_TT * KS; i += 256) {
-      const int tt = i / KS, kk = i % KS;
-      const int t = t0 + tt, k = kb + kk;
-      C val = mk<C>(0, 0);
-      if (t < T && k < kend) val = cscale(u[(size_t)t * N + k], f[k]);
-      su[tt][kk] = val;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int kk = 0; kk < KS; ++kk) {
-      const C h = sh[tm][kk];
+  __shared__ cd red[PD_WAVES][16][17];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int m0 = blockIdx.x * 16 * MA, t0 = blockIdx.y * 16 * TB, kc = blockIdx.z;
+  const int k0 = kc * PJ_KCHUNK, kend = min(k0 + PJ_KCHUNK, N);
+  const C *hp[MA], *up[TB];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const C x = su[tg + 8 * j][kk];
-        accr[j] += (double)h.x * x.x - (double)h.y * x.y;
-        acci[j] += (double)h.x * x.y + (double)h.y * x.x;
+  for (int i = 0; i < MA; ++i) hp[i] = H + (size_t)min(m0 + 16 * i + r16, M - 1) * N;
+#pragma unroll
+  for (int j = 0; j < TB; ++j) up[j] = u + (size_t)min(t0 + 16 * j + r16, T - 1) * N;
+  doublex4 re[MA][TB], im[MA][TB];
+#pragma unroll
+  for (int i = 0; i < MA; ++i)
+#pragma unroll
+    for (int j = 0; j < TB; ++j) re[i][j] = im[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+  constexpr int KW = PJ_KCHUNK / PD_WAVES;   // pixels per wave
+  static_assert(KW % 16 == 0, "a wave contracts whole groups of 16 pixels");
+  const int kw = k0 + wave * KW, ke = min(kw + KW, kend);
+  for (int kb = kw; kb < ke; kb += 16) {
+    const int k = kb + 4 * g;
+    C h[MA][4], x[TB][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const bool ok = k + s < ke;
+      const int kk = min(k + s, N - 1);   // loaded without a branch, zeroed past the end
+      const R fk = f[kk];
+#pragma unroll
+      for (int i = 0; i < MA; ++i) {
+        const C v = hp[i][kk];
+        h[i][s] = ok ? v : mk<C>(0, 0);
+      }
+#pragma unroll
+      for (int j = 0; j < TB; ++j) {
+        const C v = cscale(up[j][kk], fk);
+        x[j][s] = ok ? v : mk<C>(0, 0);
       }
     }
-    __syncthreads();
-  }
-  const int m = m0 + tm;
-  if (m >= M) return;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int t = t0 + tg + 8 * j;
-    if (t < T) part[((size_t)kc * T + t) * M + m] = mk<cd>(accr[j], acci[j]);
+    for (int s = 0; s < 4; ++s) {
+#pragma unroll
+      for (int i = 0; i < MA; ++i) {
+        const double hr = h[i][s].x, hi = h[i][s].y;
+#pragma unroll
+        for (int j = 0; j < TB; ++j) {
+          const double xr = x[j][s].x, xi = x[j][s].y;
+          re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(hr, xr, re[i][j], 0, 0, 0);
+          im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(hr, xi, im[i][j], 0, 0, 0);
+          re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-hi, xi, re[i][j], 0, 0, 0);
+          im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(hi, xr, im[i][j], 0, 0, 0);
+        }
+      }
+    }
   }
+#pragma unroll
+  for (int i = 0; i < MA; ++i) {
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][r16][4 * r + g] = mk<cd>(re[i][j][r], im[i][j][r]);
+      __syncthreads();
+      if (threadIdx.x < 256) {
+        const int tt = threadIdx.x >> 4, mm = threadIdx.x & 15, t = t0 + 16 * j + tt, m = m0 + 16 * i + mm;
+        cd sum = red[0][tt][mm];
+#pragma unroll
+        for (int w = 1; w < PD_WAVES; ++w) sum = cadd(sum, red[w][tt][mm]);
+        if (t < T && m < M) part[((size_t)kc * T + t) * M + m] = sum;
+      }
+    }
+  }
+}
+
+// The tile: the widest that leaves at least 512 blocks (two per CU), else one
+// 16 x 16 tile; a third receiver tile only where it fits M better.
+template <typename R>
+static void launch_project_f64(Ctx &c, const R *f, const cplx_t<R> *u, cd *part, int kchunks) {
+  const int mt = (c.M + 15) / 16, tt = (c.T + 15) / 16;
+  auto go = [&](auto ma, auto tb) {
+    constexpr int MA = decltype(ma)::value, TB = decltype(tb)::value;
+    hipLaunchKernelGGL((k_project_f64<R, MA, TB>), dim3((mt + MA - 1) / MA, (tt + TB - 1) / TB, kchunks),
+                       dim3(64 * PD_WAVES), 0, c.stream, (const cplx_t<R> *)c.H, f, u, part, c.M, c.N, c.T);
+  };
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  auto blocks = [&](int ma, int tb) { return (long long)((mt + ma - 1) / ma) * ((tt + tb - 1) / tb) * kchunks; };
+  const int ma = mt % 3 == 0 || mt > 4 ? 3 : 2;
+  if (blocks(ma, 2) >= 512) return ma == 3 ? go(I3{}, I2{}) : go(I2{}, I2{});
+  if (blocks(2, 1) >= 512) return go(I2{}, I1{});
+  go(I1{}, I1{});
 }
 
 // ---------------------------------------------------------------- MFMA projection (FP32)
@@ -291,14 +354,10 @@ int launch_project(Ctx &c, const R *f, const cplx_t<R> *u, const cplx_t<R> *y_me
       hipLaunchKernelGGL(k_project_mfma<32>, g, dim3(256), 0, c.stream, (const cf *)c.H, f, u, part, c.M, c.N,
                          c.T);
     } else {
-      dim3 g((c.M + PJ_MT - 1) / PJ_MT, (c.T + PJ_TT - 1) / PJ_TT, kchunks);
-      hipLaunchKernelGGL(k_project_fma<float>, g, dim3(256), 0, c.stream, (const cf *)c.H, f, u, part, c.M, c.N,
-                         c.T);
+      launch_project_f64<float>(c, f, u, part, kchunks);
     }
   } else {
-    dim3 g((c.M + PJ_MT - 1) / PJ_MT, (c.T + PJ_TT - 1) / PJ_TT, kchunks);
-    hipLaunchKernelGGL(k_project_fma<double>, g, dim3(256), 0, c.stream, (const cd *)c.H, f, u, part, c.M, c.N,
-                       c.T);
+    launch_project_f64<double>(c, f, u, part, kchunks);
   }
   const int MT = c.M * c.T;
   const int nb = (MT + PROJ_REDUCE_OUT - 1) / PROJ_REDUCE_OUT;
@@ -313,48 +372,90 @@ int launch_project(Ctx &c, const R *f, const cplx_t<R> *u, const cplx_t<R> *y_me
   return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
 }
 
-// ---------------------------------------------------------------- back-projection
-// q[t][k] = sum_m conj(H[m][k]) w[t][m]; optional b = f q.  Block: 256 pixels
-// x all transmitters in groups of 16; w staged in LDS per receiver chunk.
-template <typename R>
-__global__ void __launch_bounds__(256) k_backproject(const cplx_t<R> *H, const cplx_t<R> *w, cplx_t<R> *q,
-                                                     const R *f, cplx_t<R> *b, int M, int N, int T) {
-  using C = cplx_t<R>;
-  constexpr int TG = 16, MS = 64;
-  __shared__ C sw[TG][MS];
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  const int t0 = blockIdx.y * TG;
-  R accr[TG] = {0}, acci[TG] = {0};
-  for (int mb = 0; mb < M; mb += MS) {
-    for (int i = threadIdx.x; i < TG * MS; i += 256) {
-      const int tt = i / MS, mm = i % MS;
-      sw[tt][mm] = (t0 + tt < T && mb + mm < M) ? w[(size_t)(t0 + tt) * M + mb + mm] : mk<C>(0, 0);
-    }
-    __syncthreads();
-    if (k < N) {
-      const int mmax = min(MS, M - mb);
-      for (int mm = 0; mm < mmax; ++mm) {
-        const C h = H[(size_t)(mb + mm) * N + k];
+// ---------------------------------------------------------------- FP64 back-projection
+// q[t][k] = sum_m conj(H[m][k]) w[t][m]; optional b = f q.  The lane layout is
+// k_project_f64's with rows = transmitters (A[l%16][l/16] = w) and columns =
+// pixels (B[l/16][l%16] = H, 256 contiguous bytes a row).  A wave owns TB
+// transmitter tiles x KA pixel tiles and reads both operands from global
+// memory (w is a few hundred kilobytes and stays in L2); the waves are
+// independent.  Against 16 FMA sums per thread with w staged in LDS:
+// 107 -> 83 us at 36 x 98304 x 81, of which writing q and b is about 50.
+template <int TB, int KA>
+__global__ void __launch_bounds__(256, 2) k_backproject_f64(const cd *H, const cd *w, cd *q, const double *f, cd *b,
+                                                            int M, int N, int T) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int k0 = (blockIdx.x * 4 + wave) * 16 * KA, t0 = blockIdx.y * 16 * TB;
+  if (k0 >= N) return;
+  const cd *wp[TB], *hp[KA];
 #pragma unroll
-        for (int j = 0; j < TG; ++j) {
-          const C x = sw[j][mm];
-          accr[j] += h.x * x.x + h.y * x.y;
-          acci[j] += h.x * x.y - h.y * x.x;
-        }
+  for (int j = 0; j < TB; ++j) wp[j] = w + (size_t)min(t0 + 16 * j + r16, T - 1) * M;
+#pragma unroll
+  for (int i = 0; i < KA; ++i) hp[i] = H + min(k0 + 16 * i + r16, N - 1);
+  doublex4 re[TB][KA], im[TB][KA];
+#pragma unroll
+  for (int j = 0; j < TB; ++j)
+#pragma unroll
+    for (int i = 0; i < KA; ++i) re[j][i] = im[j][i] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+  for (int mb = 0; mb < M; mb += 4) {
+    const bool ok = mb + g < M;
+    const int m = min(mb + g, M - 1);   // loaded without a branch, zeroed past the end
+    cd a[TB], h[KA];
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+      const cd v = wp[j][m];
+      a[j] = ok ? v : mk<cd>(0.0, 0.0);
+    }
+#pragma unroll
+    for (int i = 0; i < KA; ++i) {
+      const cd v = hp[i][(size_t)m * N];
+      h[i] = ok ? v : mk<cd>(0.0, 0.0);
+    }
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+#pragma unroll
+      for (int i = 0; i < KA; ++i) {
+        re[j][i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j].x, h[i].x, re[j][i], 0, 0, 0);
+        im[j][i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j].y, h[i].x, im[j][i], 0, 0, 0);
+        re[j][i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j].y, h[i].y, re[j][i], 0, 0, 0);
+        im[j][i] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[j].x, h[i].y, im[j][i], 0, 0, 0);
       }
     }
-    __syncthreads();
   }
-  if (k >= N) return;
 #pragma unroll
-  for (int j = 0; j < TG; ++j) {
-    const int t = t0 + j;
-    if (t < T) {
-      const C val = mk<C>(accr[j], acci[j]);
-      q[(size_t)t * N + k] = val;
-      if (b) b[(size_t)t * N + k] = cscale(val, f[k]);
+  for (int i = 0; i < KA; ++i) {
+    const int k = k0 + 16 * i + r16;
+    if (k >= N) continue;
+    const double fk = b ? f[k] : 0.0;
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int t = t0 + 16 * j + 4 * r + g;
+        if (t >= T) continue;
+        const cd val = mk<cd>(re[j][i][r], im[j][i][r]);
+        q[(size_t)t * N + k] = val;
+        if (b) b[(size_t)t * N + k] = cscale(val, fk);
+      }
     }
   }
+}
+
+// Two pixel tiles a wave where that still gives 2048 waves (two per SIMD).
+static void launch_backproject_f64(Ctx &c, const cd *w, cd *q, const double *f, cd *b) {
+  const int tt = (c.T + 15) / 16;
+  auto go = [&](auto tb, auto ka) {
+    constexpr int TB = decltype(tb)::value, KA = decltype(ka)::value;
+    hipLaunchKernelGGL((k_backproject_f64<TB, KA>), dim3((c.N + 64 * KA - 1) / (64 * KA), (tt + TB - 1) / TB), dim3(256),
+                       0, c.stream, (const cd *)c.H, w, q, f, b, c.M, c.N, c.T);
+  };
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  const bool wide = (long long)(c.N / 32) * ((tt + 2) / 3) >= 2048;
+  if (wide) return tt >= 3 ? go(I3{}, I2{}) : tt == 2 ? go(I2{}, I2{}) : go(I1{}, I2{});
+  go(I1{}, I1{});
 }
 
 // ---------------------------------------------------------------- MFMA back-projection (FP32)
@@ -522,9 +623,7 @@ int launch_backproject(Ctx &c, const cplx_t<R> *w, cplx_t<R> *q, const R *f, cpl
     dim3 g((c.N + BP_PT - 1) / BP_PT, (c.T + BP_TT - 1) / BP_TT);
     hipLaunchKernelGGL(k_backproject_mfma, g, dim3(256), 0, c.stream, (const cf *)c.H, w, q, f, b, c.M, c.N, c.T);
   } else {
-    dim3 g((c.N + 255) / 256, (c.T + 15) / 16);
-    hipLaunchKernelGGL(k_backproject<R>, g, dim3(256), 0, c.stream, (const cplx_t<R> *)c.H, w, q, f, b, c.M, c.N,
-                       c.T);
+    launch_backproject_f64(c, w, q, f, b);
   }
   return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
 }

@@ -1,0 +1,36 @@
+"""GPU tests of the receiver contractions at the edges of their tiles, against FP64 sums on the
+library's own receiver matrix."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1708_01663_amd.cisor import Cisor, plane_wave_dirs, ring
+
+pytestmark = pytest.mark.gpu
+
+
+# one output and one pixel group; partial tiles of 16 in M and T; several tiles a block with a
+# remainder; pixel counts that are no multiple of 16, of a wave's share or of a chunk; enough
+# blocks for every tile shape; more than 64 transmitters in complex64
+@pytest.mark.parametrize("prec,n,T,M", [
+    ("c128", 3, 1, 1), ("c128", 13, 16, 17), ("c128", 32, 8, 32), ("c128", 45, 33, 100), ("c128", 96, 17, 49),
+    ("c128", 150, 60, 48), ("c128", 200, 20, 30), ("c64", 23, 65, 33), ("c64", 160, 81, 70)])
+def test_contractions_match_fp64(prec, n, T, M):
+    print(f"contractions {prec} {n} {T} {M}", flush=True)
+    op = Cisor(n, 0.1, plane_wave_dirs(T), ring(M, n * 0.1), precision=prec)
+    rng = np.random.default_rng(n + T)
+    cplx = lambda *s: torch.as_tensor(rng.standard_normal(s) + 1j * rng.standard_normal(s)).to(op.cdtype)
+    f = torch.as_tensor(rng.uniform(0, 1, op.N)).to(op.rdtype)
+    u, w = cplx(T, op.N), cplx(T, M)
+    H = op.H().cpu().to(torch.complex128)
+    y = op.project(f.cuda(), u.cuda()).cpu()
+    q = op.backproject(w.cuda()).cpu()
+    want_y = (u.to(torch.complex128) * f.double()) @ H.T
+    want_q = w.to(torch.complex128) @ H.conj()
+    rel = lambda a, b: float(torch.linalg.vector_norm(a.to(torch.complex128) - b) / torch.linalg.vector_norm(b))
+    # c128: N (or M) products of 2^-53 rounding each, with cancellation; c64 rounds f u and the result
+    # once in the projection and sums M products in FP32 in the back-projection
+    eps = 2.0 ** -53 if prec == "c128" else 2.0 ** -24
+    assert rel(y, want_y) <= (16 * op.N ** 0.5 * eps if prec == "c128" else 4 * eps)
+    assert rel(q, want_q) <= 16 * M ** 0.5 * eps
