@@ -10,280 +10,399 @@
 // starting from p_0 = r_1 = 0, t_1 = 1; the output is clip(z + lam div p_K).
 //
 // The inner iterations run in launches of up to eight (temporal blocking): a
-// block stages a 16 x 16 tile plus an 8-pixel halo of z and both duals in
-// LDS, iterates there, and writes the exact tile back, which cuts the launches
-// per prox from 100 to 13.  The state (z and four dual arrays, 20 bytes per
-// pixel in FP32) stays resident in L2 between launches at n <= 512.
+// block iterates on a 16 x 16 tile plus an 8-pixel halo, one thread per pixel
+// with z and both duals in registers, and writes the exact tile back.  The state
+// (z and four dual arrays, 20 bytes per pixel in FP32) stays resident in L2
+// between launches at n <= 512.  An image of at most 32 x 32 pixels is one block
+// and one launch.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "internal.hpp"
 
 namespace cisor {
 
-constexpr int TVB = 16;
-
-// div r at (i, j) from LDS-resident r1 (x-component) and r2 (y-component),
-// with the last-index components treated as zero.
-template <typename R>
-__device__ __forceinline__ R tv_div(const R (*r1)[TVB + 2], const R (*r2)[TVB + 2], int li, int lj, int gi, int gj,
-                                    int n) {
-  const R a = (gi < n - 1) ? r1[li][lj] : R(0);
-  const R b = (gi > 0) ? r1[li - 1][lj] : R(0);
-  const R c = (gj < n - 1) ? r2[li][lj] : R(0);
-  const R d = (gj > 0) ? r2[li][lj - 1] : R(0);
-  return a - b + c - d;
-}
-
-// KB consecutive FGP iterations per launch (temporal blocking).  A block owns
-// a TVB x TVB output tile and stages the tile plus a KB-pixel halo of z, the
-// momentum dual r and the previous dual p in LDS.  One FGP iteration reads
-// its neighbours at distance one, so after m iterations the values in the
-// staged region are exact at least m pixels away from its edge; after kb <= KB
-// iterations the tile itself is exact and is written back.
-constexpr int TVK = 8;
-constexpr int TVS = TVB + 2 * TVK;
-struct TvWeights {
-  double w[TVK];
+constexpr int TVB = 16;              // tile side
+constexpr int TVK = 8;               // halo, and iterations per launch
+constexpr int TVS = TVB + 2 * TVK;   // staged side: TVS x TVS = 1024 threads
+constexpr int TV_THREADS = TVS * TVS;
+constexpr int TV_MAXW = 120;         // iterations of one launch on a whole image
+template <typename R, int NW> struct TvWeights {
+  R w[NW];
 };
 
-// One thread per staged pixel (TVS x TVS = 1024): the block's iterations are
-// latency-bound, so more waves per CU matter more than fewer threads.
-constexpr int TV_THREADS = TVS * TVS;
+// The value of the previous (next) lane of the wave; lane 0 (63) receives 0.
+template <int CTRL> __device__ __forceinline__ int dpp_shift(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL, typename R> __device__ __forceinline__ R lane_shift(R v) {
+  if constexpr (sizeof(R) == 4) {
+    return __builtin_bit_cast(R, dpp_shift<CTRL>(__builtin_bit_cast(int, v)));
+  } else {
+    typedef int int2v __attribute__((ext_vector_type(2)));
+    int2v p = __builtin_bit_cast(int2v, v);
+    p[0] = dpp_shift<CTRL>(p[0]);
+    p[1] = dpp_shift<CTRL>(p[1]);
+    return __builtin_bit_cast(R, p);
+  }
+}
+constexpr int DPP_WAVE_SHL = 0x130, DPP_WAVE_SHR = 0x138;
 
-template <typename R>
-__global__ void __launch_bounds__(TV_THREADS) k_fgp_block(const R *z, const R *rin, const R *pin, R *pout, R *rout, int n,
-                                                   R lam, R lo, R hi, R inv_step, TvWeights mw, int kb) {
-  __shared__ R sz[TVS][TVS], s1[TVS][TVS], s2[TVS][TVS], q1[TVS][TVS], q2[TVS][TVS], sx[TVS][TVS];
-  const int N = n * n;
-  const int gi0 = blockIdx.y * TVB - TVK, gj0 = blockIdx.x * TVB - TVK;
-  for (int idx = threadIdx.x; idx < TVS * TVS; idx += blockDim.x) {
-    const int li = idx / TVS, lj = idx % TVS;
-    const int gi = gi0 + li, gj = gj0 + lj;
-    R a = 0, b = 0, c = 0, d = 0, e = 0;
-    if (gi >= 0 && gi < n && gj >= 0 && gj < n) {
-      const size_t g = (size_t)gi * n + gj;
-      a = z[g];
-      b = rin[g];
-      c = rin[N + g];
-      d = pin[g];
-      e = pin[N + g];
-    }
-    sz[li][lj] = a;
-    s1[li][lj] = b;
-    s2[li][lj] = c;
-    q1[li][lj] = d;
-    q2[li][lj] = e;
+// (a, b) projected onto the unit disk.  FP32: the reciprocal root with one
+// Newton step in place of a square root and two divisions (a third of the
+// iteration's instructions); either rounds each component by about an ulp.
+__device__ __forceinline__ void tv_disk(double &a, double &b) {
+  const double nrm = sqrt(a * a + b * b);
+  if (nrm > 1.0) {
+    a /= nrm;
+    b /= nrm;
   }
-  __syncthreads();
-  for (int m = 0; m < kb; ++m) {
-    // primal x(r) = clip(z + lam div r) on the region still exact
-    for (int idx = threadIdx.x; idx < TVS * TVS; idx += blockDim.x) {
-      const int li = idx / TVS, lj = idx % TVS;
-      const int gi = gi0 + li, gj = gj0 + lj;
-      R xv = 0;
-      if (gi >= 0 && gi < n && gj >= 0 && gj < n && li > 0 && lj > 0) {
-        const R a = (gi < n - 1) ? s1[li][lj] : R(0);
-        const R b = (gi > 0) ? s1[li - 1][lj] : R(0);
-        const R c = (gj < n - 1) ? s2[li][lj] : R(0);
-        const R d = (gj > 0) ? s2[li][lj - 1] : R(0);
-        xv = fmin(fmax(sz[li][lj] + lam * (a - b + c - d), lo), hi);
-      }
-      sx[li][lj] = xv;
+}
+__device__ __forceinline__ void tv_disk(float &a, float &b) {
+  const float nn = a * a + b * b;
+  if (nn > 1.0f) {
+    if (nn < 1e37f) {
+      const float y = __builtin_amdgcn_rsqf(nn);
+      const float s = fmaf(0.5f * y, fmaf(-nn * y, y, 1.0f), y);
+      a *= s;
+      b *= s;
+    } else {   // the squares overflow, or nearly
+      const float nrm = sqrtf(nn);
+      a /= nrm;
+      b /= nrm;
     }
-    __syncthreads();
-    // dual step, projection and momentum (each pixel reads and writes only
-    // its own r and p, and its neighbours' x)
-    const R w = (R)mw.w[m];
-    for (int idx = threadIdx.x; idx < TVS * TVS; idx += blockDim.x) {
-      const int li = idx / TVS, lj = idx % TVS;
-      const int gi = gi0 + li, gj = gj0 + lj;
-      if (!(gi >= 0 && gi < n && gj >= 0 && gj < n) || li + 1 >= TVS || lj + 1 >= TVS) continue;
-      const R x0 = sx[li][lj];
-      const R g1 = (gi < n - 1) ? sx[li + 1][lj] - x0 : R(0);
-      const R g2 = (gj < n - 1) ? sx[li][lj + 1] - x0 : R(0);
-      R a = s1[li][lj] + g1 * inv_step;
-      R b = s2[li][lj] + g2 * inv_step;
-      const R nrm = sqrt(a * a + b * b);
-      if (nrm > R(1)) {
-        a /= nrm;
-        b /= nrm;
-      }
-      const R o1 = q1[li][lj], o2 = q2[li][lj];
-      q1[li][lj] = a;
-      q2[li][lj] = b;
-      s1[li][lj] = a + w * (a - o1);
-      s2[li][lj] = b + w * (b - o2);
-    }
-    __syncthreads();
-  }
-  for (int idx = threadIdx.x; idx < TVB * TVB; idx += blockDim.x) {
-    const int li = idx / TVB + TVK, lj = idx % TVB + TVK;
-    const int gi = gi0 + li, gj = gj0 + lj;
-    if (gi >= n || gj >= n) continue;
-    const size_t g = (size_t)gi * n + gj;
-    pout[g] = q1[li][lj];
-    pout[N + g] = q2[li][lj];
-    rout[g] = s1[li][lj];
-    rout[N + g] = s2[li][lj];
   }
 }
 
-template <typename R>
-__global__ void __launch_bounds__(TVB *TVB) k_fgp_final(const R *z, const R *p, R *x, int n, R lam, R lo, R hi) {
-  __shared__ R s1[TVB + 2][TVB + 2];
-  __shared__ R s2[TVB + 2][TVB + 2];
+// kb consecutive FGP iterations.  One FGP iteration reads its neighbours at
+// distance one, so after m iterations the values in the staged region are exact
+// at least m pixels away from its edge (or everywhere, when the region is the
+// whole image, WHOLE); after kb <= TVK iterations the tile itself is exact and
+// is written back.  FIRST starts from zero duals.  With x set (the last launch,
+// kb < TVK) it writes the prox clip(z + lam div p) of the tile instead.
+// A thread keeps its pixel's z, r and p in registers; a row of the region is
+// half a wave, so horizontal neighbours come from the adjacent lane (DPP) and
+// only the vertical ones (one value of r, one of x) go through LDS: four LDS
+// operations and two barriers an iteration.  With every value in LDS (17
+// operations an iteration) a launch of eight iterations at 256^2 took
+// 10.4 us, now 6.0 us; bound by the dependent chain of an iteration
+// (square root and two divisions) over 16 waves a CU.
+// Values outside the image are zero and stay zero, and r1 (r2) is zero in the
+// last row (column) from the start on, so div r needs no boundary test.
+template <typename R, bool WHOLE, bool FIRST, int NW>
+__global__ void __launch_bounds__(TV_THREADS) k_fgp_block(const R *z, const R *rin, const R *pin, R *pout, R *rout,
+                                                          R *x, int n, R lam, R lo, R hi, R inv_step,
+                                                          TvWeights<R, NW> mw, int kb) {
+  __shared__ R s1[TVS][TVS], sx[TVS][TVS];
   const int N = n * n;
-  const int i0 = blockIdx.y * TVB - 1, j0 = blockIdx.x * TVB - 1;
-  for (int idx = threadIdx.x; idx < (TVB + 2) * (TVB + 2); idx += TVB * TVB) {
-    const int li = idx / (TVB + 2), lj = idx % (TVB + 2);
-    const int gi = i0 + li, gj = j0 + lj;
-    R a = 0, b = 0;
-    if (gi >= 0 && gi < n && gj >= 0 && gj < n) {
-      a = p[(size_t)gi * n + gj];
-      b = p[N + (size_t)gi * n + gj];
+  const int li = threadIdx.x / TVS, lj = threadIdx.x % TVS;
+  const int gi = (WHOLE ? 0 : (int)blockIdx.y * TVB - TVK) + li, gj = (WHOLE ? 0 : (int)blockIdx.x * TVB - TVK) + lj;
+  const bool in = gi >= 0 && gi < n && gj >= 0 && gj < n;
+  const size_t g = (size_t)gi * n + gj;
+  R zv = 0, r1 = 0, r2 = 0, p1 = 0, p2 = 0;
+  if (in) {
+    zv = z[g];
+    if constexpr (!FIRST) {
+      r1 = rin[g];
+      r2 = rin[N + g];
+      p1 = pin[g];
+      p2 = pin[N + g];
     }
-    s1[li][lj] = a;
-    s2[li][lj] = b;
   }
-  __syncthreads();
-  const int li = threadIdx.x / TVB + 1, lj = threadIdx.x % TVB + 1;
-  const int gi = i0 + li, gj = j0 + lj;
-  if (gi >= n || gj >= n) return;
-  const size_t e = (size_t)gi * n + gj;
-  x[e] = fmin(fmax(z[e] + lam * tv_div<R>(s1, s2, li, lj, gi, gj, n), lo), hi);
+  // forward differences that exist (the region's own edge counts as the
+  // image's: what that spoils stays within the halo)
+  const bool d1 = in && gi < n - 1 && li + 1 < TVS, d2 = in && gj < n - 1 && lj + 1 < TVS;
+  const int up = li > 0 ? li - 1 : 0, dn = li + 1 < TVS ? li + 1 : li;
+  // x = clip(z + lam div v) on every thread (zero outside the image); s1 holds
+  // v1 for the row below
+  auto primal = [&](R v1, R v2) -> R {
+    const R left = lane_shift<DPP_WAVE_SHR>(v2);
+    const R b = li > 0 ? s1[up][lj] : R(0);
+    const R d = lj > 0 ? left : R(0);
+    const R v = fmin(fmax(zv + lam * (v1 - b + v2 - d), lo), hi);
+    return in ? v : R(0);
+  };
+  for (int m = 0; m < kb; ++m) {
+    // rows that the tile still depends on after this iteration (the output x
+    // reads p one row up) and the row on either side that they read: the
+    // other waves only keep the barriers
+    const int margin = kb - m + (x ? 1 : 0);
+    const bool act = WHOLE || (li >= TVK - margin && li < TVK + TVB + margin);
+    R x0 = 0, xr = 0;
+    if (act) s1[li][lj] = r1;
+    __syncthreads();
+    if (act) {
+      x0 = primal(r1, r2);
+      sx[li][lj] = x0;
+      xr = lane_shift<DPP_WAVE_SHL>(x0);
+    }
+    __syncthreads();
+    if (act && in) {
+      const R xd = sx[dn][lj];
+      const R g1 = d1 ? xd - x0 : R(0);
+      const R g2 = d2 ? xr - x0 : R(0);
+      R a = r1 + g1 * inv_step;
+      R b = r2 + g2 * inv_step;
+      tv_disk(a, b);
+      const R w = mw.w[m];
+      r1 = a + w * (a - p1);
+      r2 = b + w * (b - p2);
+      p1 = a;
+      p2 = b;
+    }
+  }
+  const bool tile = WHOLE || (li >= TVK && li < TVK + TVB && lj >= TVK && lj < TVK + TVB);
+  if (x) {
+    s1[li][lj] = p1;
+    __syncthreads();
+    const R v = primal(p1, p2);
+    if (in && tile) x[g] = v;
+  } else if (in && tile) {
+    pout[g] = p1;
+    pout[N + g] = p2;
+    rout[g] = r1;
+    rout[N + g] = r2;
+  }
 }
 
 template <typename R> __global__ void k_clip(const R *z, R *x, int N, R lo, R hi) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < N) x[i] = fmin(fmax(z[i], lo), hi);
 }
-template <typename R> __global__ void k_zero_real(R *x, size_t n) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) x[i] = 0;
-}
 
 // ---------------------------------------------------------------- 3D volumes
 // The same FGP on an n^3 volume (voxel q = (i n + j) n + l, axes of strides
 // n^2, n, 1): dual step 1 / (12 lam) (||grad||^2 <= 4 d with d = 3), the dual
-// projected voxel by voxel onto the unit ball of R^3.  One FGP iteration is
-// two launches over the volume: the primal point x(r), then the dual ascent
-// with its momentum, updated in place (each thread reads and writes only its
-// own voxel's duals).
+// projected voxel by voxel onto the unit ball of R^3, every expression in FP64.
+// One FGP iteration is one launch: a block forms x(r) on its tile and on the
+// layer past each forward face in LDS, then takes the dual ascent with its
+// momentum, p in place and r into the other of two buffers.  The tile is 64
+// voxels long on the fastest axis, so that every access is a whole 256-byte
+// row (32 on volumes of at most 32^3): 16 long it takes 6.6 us an iteration at
+// 64^3, 32 long 4.8, 64 long 4.35 (8.6 for the former two launches), of which an
+// empty launch is 1.5 and one that only stores p and r 2.5; the volume and its
+// duals stay in L2.
+template <int L> struct T3 {
+  static constexpr int TL = L, TJ = 4, TI = 128 / L, THREADS = TI * TJ * TL;
+  static constexpr int FACES = TJ * TL + TI * TL + TI * TJ;   // voxels past the forward faces
+  static_assert(FACES <= THREADS, "a thread forms at most one of them");
+};
 
-// div r at voxel (i, j, l), last-index components treated as zero; r is [3][N].
-template <typename R>
-__device__ __forceinline__ double tv3_div(const R *r, int q, int i, int j, int l, int n, int N) {
-  const int st[3] = {n * n, n, 1}, ix[3] = {i, j, l};
+// Element at a byte offset below 4 GiB from a uniform base (n <= 512).
+template <typename R> __device__ __forceinline__ R ld32(const R *base, unsigned off) {
+  return *reinterpret_cast<const R *>(reinterpret_cast<const char *>(base) + off);
+}
+
+// clip(z + lam div r) at voxel (i, j, l); ZERO: r is zero.  r_a is zero in the
+// last layer of its axis (it starts there and has no gradient to follow).
+// Rounding is monotone, so clipping the rounded value is rounding the clipped.
+template <typename R, bool ZERO>
+__device__ __forceinline__ R tv3_x(const R *z, const R *r, int i, int j, int l, int n, double lam, R lo, R hi) {
+  const int N = n * n * n;
+  const unsigned q = (unsigned)((i * n + j) * n + l) * (unsigned)sizeof(R);
   double d = 0.0;
+  if constexpr (!ZERO) {
+    const unsigned st[3] = {(unsigned)(n * n) * (unsigned)sizeof(R), (unsigned)n * (unsigned)sizeof(R),
+                            (unsigned)sizeof(R)};
+    const int ix[3] = {i, j, l};
+    R v[3], u[3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const R *ra = r + (size_t)a * N;
-    if (ix[a] < n - 1) d += (double)ra[q];
-    if (ix[a] > 0) d -= (double)ra[q - st[a]];
+    for (int a = 0; a < 3; ++a) {   // loaded without a branch, used where they exist
+      const R *ra = r + (size_t)a * N;
+      v[a] = ld32(ra, q);
+      u[a] = ld32(ra, q - (ix[a] > 0 ? st[a] : 0u));
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      d += (double)v[a];
+      d -= (double)(ix[a] > 0 ? u[a] : R(0));
+    }
   }
-  return d;
+  return fmin(fmax((R)((double)ld32(z, q) + lam * d), lo), hi);
 }
 
-template <typename R>
-__global__ void __launch_bounds__(256) k_fgp3_x(const R *z, const R *r, R *x, int n, double lam, double lo,
-                                                double hi) {
-  const int N = n * n * n;
-  const int q = blockIdx.x * 256 + threadIdx.x;
-  if (q >= N) return;
-  const int i = q / (n * n), j = (q / n) % n, l = q % n;
-  const double v = (double)z[q] + lam * tv3_div<R>(r, q, i, j, l, n, N);
-  x[q] = (R)fmin(fmax(v, lo), hi);
+// 1 / max(1, sqrt(nn)).  Rounded to FP32 afterwards (R = float): the
+// reciprocal root with two Newton steps (about 1e-15) for a square root and a
+// division.
+template <typename R> __device__ __forceinline__ double tv3_scale(double nn) {
+  if constexpr (sizeof(R) == 8) {
+    return 1.0 / fmax(1.0, sqrt(nn));
+  } else {
+    if (!(nn > 1.0)) return 1.0;
+    if (!(nn < 1e300)) return 1.0 / sqrt(nn);
+    double y = __builtin_amdgcn_rsq(nn);
+    y = fma(0.5 * y, fma(-nn * y, y, 1.0), y);
+    return fma(0.5 * y, fma(-nn * y, y, 1.0), y);
+  }
 }
 
-template <typename R>
-__global__ void __launch_bounds__(256) k_fgp3_dual(const R *x, R *p, R *r, int n, double inv_step, double w) {
-  const int N = n * n * n;
-  const int q = blockIdx.x * 256 + threadIdx.x;
-  if (q >= N) return;
-  const int st[3] = {n * n, n, 1};
-  const int ix[3] = {q / (n * n), (q / n) % n, q % n};
-  const double xc = (double)x[q];
+template <typename R, bool FIRST, int L>
+__global__ void __launch_bounds__(T3<L>::THREADS) k_fgp3_step(const R *z, const R *rin, R *p, R *rout, int n, double lam,
+                                                          R lo, R hi, double inv_step, double w) {
+  constexpr int T3I = T3<L>::TI, T3J = T3<L>::TJ, T3L = T3<L>::TL;
+  __shared__ R sx[T3I + 1][T3J + 1][T3L + 1];
+  const int N = n * n * n, tid = threadIdx.x;
+  const int i0 = blockIdx.z * T3I, j0 = blockIdx.y * T3J, l0 = blockIdx.x * T3L;
+  const int li = tid / (T3J * T3L), lj = tid / T3L % T3J, ll = tid % T3L;
+  const int i = i0 + li, j = j0 + lj, l = l0 + ll;
+  const bool in = i < n && j < n && l < n;
+  const unsigned q = (unsigned)((i * n + j) * n + l) * (unsigned)sizeof(R);
+  R rv[3] = {}, pv[3] = {};
+  if (in) {
+    if constexpr (!FIRST) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        rv[a] = ld32(rin + (size_t)a * N, q);
+        pv[a] = ld32((const R *)p + (size_t)a * N, q);
+      }
+    }
+    sx[li][lj][ll] = tv3_x<R, FIRST>(z, rin, i, j, l, n, lam, lo, hi);
+  }
+  if (tid < T3<L>::FACES) {
+    int fi, fj, fl;
+    if (tid < T3J * T3L) {
+      fi = T3I, fj = tid / T3L, fl = tid % T3L;
+    } else if (tid < T3J * T3L + T3I * T3L) {
+      fi = (tid - T3J * T3L) / T3L, fj = T3J, fl = tid % T3L;
+    } else {
+      fi = (tid - (T3J + T3I) * T3L) / T3J, fj = tid % T3J, fl = T3L;
+    }
+    if (i0 + fi < n && j0 + fj < n && l0 + fl < n)
+      sx[fi][fj][fl] = tv3_x<R, FIRST>(z, rin, i0 + fi, j0 + fj, l0 + fl, n, lam, lo, hi);
+  }
+  __syncthreads();
+  if (!in) return;
+  const double xc = (double)sx[li][lj][ll];
+  const double g[3] = {i < n - 1 ? (double)sx[li + 1][lj][ll] - xc : 0.0,
+                       j < n - 1 ? (double)sx[li][lj + 1][ll] - xc : 0.0,
+                       l < n - 1 ? (double)sx[li][lj][ll + 1] - xc : 0.0};
   double v[3], nrm = 0.0;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const double g = ix[a] < n - 1 ? (double)x[q + st[a]] - xc : 0.0;
-    v[a] = (double)r[(size_t)a * N + q] + g * inv_step;
+    v[a] = (double)rv[a] + g[a] * inv_step;
     nrm += v[a] * v[a];
   }
-  const double sc = 1.0 / fmax(1.0, sqrt(nrm));
+  const double sc = tv3_scale<R>(nrm);
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     const double pn = v[a] * sc;
-    const size_t e = (size_t)a * N + q;
-    r[e] = (R)(pn + w * (pn - (double)p[e]));
-    p[e] = (R)pn;
+    char *const ro = reinterpret_cast<char *>(rout + (size_t)a * N), *const po = reinterpret_cast<char *>(p + (size_t)a * N);
+    *reinterpret_cast<R *>(ro + q) = (R)(pn + w * (pn - (double)pv[a]));
+    *reinterpret_cast<R *>(po + q) = (R)pn;
   }
 }
 
+// x = clip(z + lam div p); x may be z.
+template <typename R>
+__global__ void __launch_bounds__(256) k_fgp3_final(const R *z, const R *p, R *x, int n, double lam, R lo,
+                                                    R hi) {
+  const int q = blockIdx.x * 256 + threadIdx.x;
+  if (q >= n * n * n) return;
+  x[q] = tv3_x<R, false>(z, p, q / (n * n), q / n % n, q % n, n, lam, lo, hi);
+}
+
 // The prox on a dim-dimensional grid of side n from the work area `work` of
-// 9 N reals (2D: a copy of z and two ping-pong pairs of [2][N] duals; 3D: a
-// copy of z, the primal point and [3][N] p and r), enqueued on stream s.  Every
+// 9 N reals (2D: a copy of z, made only where x overlaps it, and two ping-pong
+// pairs of [2][N] duals; 3D: [3][N] p and two of r), enqueued on stream s.  Every
 // launch is a kernel (no memset or copy call), so the prox can be captured in
-// a graph, and the work area needs no initial contents: the duals are zeroed
-// here on every call.
+// a graph, and the work area needs no initial contents: the first iteration's
+// duals are zero without being read.
+template <typename R> static bool overlap(const R *z, const R *x, int N) { return x < z + N && z < x + N; }
+
 template <typename R>
 static void tv_prox3_run(hipStream_t s, int n, R *work, const R *z, R *x, double lam, double lo, double hi,
                          int iters) {
   const int N = n * n * n;
-  // buffers: zc (copy of z, so x may alias z), xw (primal of the dual point), p, r ([3][N] each)
-  R *zc = work, *xw = work + N, *p = work + 2 * (size_t)N, *r = p + 3 * (size_t)N;
-  launch_copy<R>(s, zc, z, (size_t)N);
-  hipLaunchKernelGGL(k_zero_real<R>, dim3(256), dim3(256), 0, s, p, (size_t)6 * N);
-  const dim3 grid((N + 255) / 256), blk(256);
+  R *p = work, *rin = work + 3 * (size_t)N, *rout = rin + 3 * (size_t)N;
   const double inv_step = 1.0 / (12.0 * lam);
   double t = 1.0;
-  for (int k = 0; k < iters; ++k) {
+  auto step = [&](auto first, auto len) {
+    constexpr int L = decltype(len)::value;
+    using TT = T3<L>;
     const double tn = (1.0 + std::sqrt(1.0 + 4.0 * t * t)) / 2.0;
-    hipLaunchKernelGGL(k_fgp3_x<R>, grid, blk, 0, s, zc, r, xw, n, lam, lo, hi);
-    hipLaunchKernelGGL(k_fgp3_dual<R>, grid, blk, 0, s, xw, p, r, n, inv_step, (t - 1.0) / tn);
+    hipLaunchKernelGGL((k_fgp3_step<R, decltype(first)::value, L>),
+                       dim3((n + TT::TL - 1) / TT::TL, (n + TT::TJ - 1) / TT::TJ, (n + TT::TI - 1) / TT::TI),
+                       dim3(TT::THREADS), 0, s, z, rin, p, rout, n, lam, (R)lo, (R)hi, inv_step, (t - 1.0) / tn);
+    std::swap(rin, rout);
     t = tn;
+  };
+  const std::integral_constant<int, 32> l32{};
+  const std::integral_constant<int, 64> l64{};
+  for (int k = 0; k < iters; ++k) {
+    if (k == 0) n <= 32 ? step(std::true_type{}, l32) : step(std::true_type{}, l64);
+    else n <= 32 ? step(std::false_type{}, l32) : step(std::false_type{}, l64);
   }
-  hipLaunchKernelGGL(k_fgp3_x<R>, grid, blk, 0, s, zc, p, x, n, lam, lo, hi);
+  // the last kernel reads z at the voxel it writes only, so x may be z; where
+  // they overlap otherwise the result goes through the work area
+  const bool shifted = x != z && overlap<R>(z, x, N);
+  hipLaunchKernelGGL(k_fgp3_final<R>, dim3((N + 255) / 256), dim3(256), 0, s, z, p, shifted ? rin : x, n, lam,
+                     (R)lo, (R)hi);
+  if (shifted) launch_copy<R>(s, x, rin, (size_t)N);
+}
+
+template <typename R>
+static void tv_prox2_run(hipStream_t s, int n, R *work, const R *z, R *x, double lam, double lo, double hi,
+                         int iters) {
+  const int N = n * n;
+  R *zc = work;
+  R *pin = work + N, *pout = pin + 2 * (size_t)N, *rin = pout + 2 * (size_t)N, *rout = rin + 2 * (size_t)N;
+  const R inv_step = (R)(1.0 / (8.0 * lam));
+  const bool whole = n <= TVS;
+  // several blocks read z around the tiles that others write in the last launch
+  if (!whole && overlap<R>(z, x, N)) {
+    launch_copy<R>(s, zc, z, (size_t)N);
+    z = zc;
+  }
+  const dim3 grid(whole ? 1 : (n + TVB - 1) / TVB, whole ? 1 : (n + TVB - 1) / TVB);
+  double t = 1.0;
+  auto launch = [&](auto wh, auto first, auto nw, int kb, R *xo) {
+    constexpr int NW = decltype(nw)::value;
+    TvWeights<R, NW> mw{};
+    for (int m = 0; m < kb; ++m) {
+      const double tn = (1.0 + std::sqrt(1.0 + 4.0 * t * t)) / 2.0;
+      mw.w[m] = (R)((t - 1.0) / tn);
+      t = tn;
+    }
+    hipLaunchKernelGGL((k_fgp_block<R, decltype(wh)::value, decltype(first)::value, NW>), grid, dim3(TV_THREADS), 0, s,
+                       z, rin, pin, pout, rout, xo, n, (R)lam, (R)lo, (R)hi, inv_step, mw, kb);
+    std::swap(pin, pout);
+    std::swap(rin, rout);
+  };
+  const std::true_type yes{};
+  const std::false_type no{};
+  for (int done = 0, left = iters; left > 0;) {
+    // the last launch also forms the prox, which reads p one pixel further
+    // out: it runs fewer than TVK iterations
+    int kb;
+    if (whole) {
+      kb = std::min(left, TV_MAXW);
+      const std::integral_constant<int, TV_MAXW> nw{};
+      R *xo = kb == left ? x : nullptr;
+      done ? launch(yes, no, nw, kb, xo) : launch(yes, yes, nw, kb, xo);
+    } else {
+      kb = left == TVK ? TVK - 1 : std::min(left, TVK);
+      const std::integral_constant<int, TVK> nw{};
+      R *xo = kb == left ? x : nullptr;
+      done ? launch(no, no, nw, kb, xo) : launch(no, yes, nw, kb, xo);
+    }
+    left -= kb;
+    done += kb;
+  }
 }
 
 template <typename R>
 static int tv_prox_run(hipStream_t s, int dim, int n, R *work, const R *z, R *x, double lam, double lo, double hi,
                        int iters) {
   const int N = dim == 3 ? n * n * n : n * n;
-  if (lam <= 0.0 || iters == 0) {
-    // no regulariser, or a zero dual: x = clip(z)
+  if (lam <= 0.0 || iters == 0)   // no regulariser, or a zero dual: x = clip(z)
     hipLaunchKernelGGL(k_clip<R>, dim3((N + 255) / 256), dim3(256), 0, s, z, x, N, (R)lo, (R)hi);
-    return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
-  }
-  if (dim == 3) {
+  else if (dim == 3)
     tv_prox3_run<R>(s, n, work, z, x, lam, lo, hi, iters);
-    return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
-  }
-  // buffers: zc (copy of z, so x may alias z), pA, pB, rA, rB; each dual is [2][N]
-  R *zc = work;
-  R *pA = work + N, *pB = pA + 2 * (size_t)N, *rA = pB + 2 * (size_t)N, *rB = rA + 2 * (size_t)N;
-  launch_copy<R>(s, zc, z, (size_t)N);
-  hipLaunchKernelGGL(k_zero_real<R>, dim3(256), dim3(256), 0, s, pA, (size_t)8 * N);
-  const dim3 grid((n + TVB - 1) / TVB, (n + TVB - 1) / TVB);
-  const R inv_step = (R)(1.0 / (8.0 * lam));
-  double t = 1.0;
-  R *pin = pA, *pout = pB, *rin = rA, *rout = rB;
-  for (int k0 = 0; k0 < iters; k0 += TVK) {
-    const int kb = std::min(TVK, iters - k0);
-    TvWeights mw{};
-    for (int m = 0; m < kb; ++m) {
-      const double tn = (1.0 + std::sqrt(1.0 + 4.0 * t * t)) / 2.0;
-      mw.w[m] = (t - 1.0) / tn;
-      t = tn;
-    }
-    hipLaunchKernelGGL(k_fgp_block<R>, grid, dim3(TV_THREADS), 0, s, zc, rin, pin, pout, rout, n, (R)lam, (R)lo,
-                       (R)hi, inv_step, mw, kb);
-    std::swap(pin, pout);
-    std::swap(rin, rout);
-  }
-  hipLaunchKernelGGL(k_fgp_final<R>, grid, dim3(TVB * TVB), 0, s, zc, pin, x, n, (R)lam, (R)lo, (R)hi);
+  else
+    tv_prox2_run<R>(s, n, work, z, x, lam, lo, hi, iters);
   return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
 }
 
