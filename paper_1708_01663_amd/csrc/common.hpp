@@ -81,8 +81,9 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double *scratch /* >=
       const bool up = (lane & off) != 0;
 #pragma unroll
       for (int j = 0; j < half; ++j) {
-        const double send = up ? v[j] : v[j + half];
-        const double keep = up ? v[j + half] : v[j];
+        const double lo = v[j], hi = v[j + half];   // (values: a selected address would keep v in memory)
+        const double send = up ? lo : hi;
+        const double keep = up ? hi : lo;
         v[j] = keep + __shfl_xor(send, off, 64);
       }
       k += up ? half : 0;

@@ -6,7 +6,7 @@
 #include <type_traits>
 
 #include "conv_cfg.hpp"
-#include "internal.hpp"
+#include "solver_state.hpp"
 
 namespace cisor {
 
@@ -603,15 +603,23 @@ template <typename Rc, int P> struct PlaneCfg {
   static constexpr int NROW = P / 2;                // rows of B: n <= P/2
   static constexpr int SPAN = lds_span(P);
   static constexpr int BATCHES = P / LINES;        // batches of x-lines
+  static constexpr bool LEAN = false;
   static constexpr size_t LDS_BYTES = ((size_t)NROW * SPAN + (size_t)P * LINES + P) * 2 * sizeof(Rc);
   static constexpr bool OK = POW2 && P >= 64 && P <= 128 && NT <= 64 && 64 % NT == 0 && LINES >= NROW &&
                              P % LINES == 0 && BATCHES <= 2 && LDS_BYTES <= 160 * 1024;
 };
 
-template <typename Rs, typename Rc, int P, bool CONJ, bool MASK>
-__global__ void __launch_bounds__((PlaneCfg<Rc, P>::THREADS)) k_plane(ConvArgs<Rs, Rc> a) {
+// The convolution of one plane by the threads of a block (steps 1 to 3).
+// G is the plane's kernel spectrum [kx][ky].  A thread owns the samples
+// (x, y(i)), i < P / (2 NT), of the input and of the output alike:
+// ld(i, x, y) returns the input, st(i, x, y, v) takes the output; neither is
+// called outside the n x n samples.  stw is the LDS copy of the twiddles.
+// Ends without a barrier: the next use of B is by the same waves' rows, and
+// that of E comes after a barrier.
+template <typename CF, typename Rc, int P, bool CONJ, typename Ld, typename St>
+__device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const cplx_t<Rc> *stw, const cplx_t<Rc> *G,
+                                           const int n, Ld &&ld, St &&st) {
   using Cc = cplx_t<Rc>;
-  using CF = PlaneCfg<Rc, P>;
   using PL = Plan<P>;
   using FL = typename PL::fwd;
   using IL = typename PL::inv;
@@ -622,56 +630,44 @@ __global__ void __launch_bounds__((PlaneCfg<Rc, P>::THREADS)) k_plane(ConvArgs<R
   constexpr int RLI = Stockham<Cc, P, NT, +1, 1, IL>::LAST;
   static_assert(CF::OK, "plane kernel configuration");
   static_assert(R0I == RL, "inverse must start with the forward's last radix");
-  static_assert(R0 % 2 == 0 && RLI % 2 == 0, "the first and last radix are pruned");
-  const int kz = blockIdx.x, t = blockIdx.y;
-  if constexpr (MASK) {
-    if (!(a.st[t].flags & a.flag)) return;
-  }
-  if (a.fmask && !a.fmask[t]) return;
-  __shared__ Cc B[CF::NROW * SPAN];
-  __shared__ Cc E[P * L];
-  __shared__ Cc stw[P];
-  for (int i = threadIdx.x; i < P; i += CF::THREADS) stw[i] = a.tw[i];
-  __syncthreads();
-  const int n = a.n;
-  const size_t plane = ((size_t)t * P + kz) * (size_t)n * n;
-  const Cc *in = a.cin + plane;
-  Cc *out = a.cout + plane;
+  static_assert(R0 % 2 == 0 && R0 == RLI, "the first and last radix are pruned, and their samples the same");
   // the spectrum values of every batch of step 2, requested first so that
   // they arrive during step 1: thread (lc, tk) of batch q needs (kx, ky) with
   // ky = q L + lc and kx in the forward transform's output layout
+  // (LEAN: each batch's when it begins, for fewer registers)
   constexpr int NB = CF::BATCHES;
-  Cc g[NB][V];
-  {
+  Cc g[CF::LEAN ? 1 : NB][V];
+  auto load_g = [&](Cc (&gq)[V], int q) __attribute__((always_inline)) {
     const int lc = threadIdx.x % L, tk = threadIdx.x / L;
-    const Cc *G = a.Gpm + (size_t)kz * P * P;   // [kx][ky]
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
+    for (int b = 0; b < V / RL; ++b) {
 #pragma unroll
-      for (int b = 0; b < V / RL; ++b) {
-#pragma unroll
-        for (int r = 0; r < RL; ++r) {
-          Cc gg = G[(size_t)(tk + b * NT + r * (P / RL)) * P + q * L + lc];
-          if constexpr (CONJ) gg.y = -gg.y;
-          g[q][b * RL + r] = gg;
-        }
+      for (int r = 0; r < RL; ++r) {
+        Cc gg = G[(size_t)(tk + b * NT + r * (P / RL)) * P + q * L + lc];
+        if constexpr (CONJ) gg.y = -gg.y;
+        gq[b * RL + r] = gg;
       }
     }
+  };
+  if constexpr (!CF::LEAN) {
+#pragma unroll
+    for (int q = 0; q < NB; ++q) load_g(g[q], q);
   }
   // 1. y-forward; line x = threadIdx.x / NT (rows x >= n transform zeros)
   {
     const int x = threadIdx.x / NT, tid = threadIdx.x % NT;
     const TwTable<Cc, P, NT, -1, FL> twf{stw, tid};
-    Cc v[V];
-#pragma unroll
-    for (int b = 0; b < V / R0; ++b) {
-#pragma unroll
-      for (int r = 0; r < R0; ++r) {
-        const int y = tid + b * NT + r * (P / R0);
-        v[b * R0 + r] = (x < n && r < R0 / 2 && y < n) ? in[(size_t)x * n + y] : czero<Cc>();
-      }
-    }
     if (x < CF::NROW) {
+      Cc v[V];
+#pragma unroll
+      for (int b = 0; b < V / R0; ++b) {
+#pragma unroll
+        for (int r = 0; r < R0; ++r) {
+          const int y = tid + b * NT + r * (P / R0);
+          v[b * R0 + r] = czero<Cc>();
+          if (r < R0 / 2 && x < n && y < n) v[b * R0 + r] = ld(b * (R0 / 2) + r, x, y);
+        }
+      }
       fft_regs<Cc, P, NT, -1, FL, decltype(twf), WaveSync, true, true, false>(v, tid, B + x * SPAN, 1, twf);
 #pragma unroll
       for (int b = 0; b < V / RL; ++b) {
@@ -689,6 +685,8 @@ __global__ void __launch_bounds__((PlaneCfg<Rc, P>::THREADS)) k_plane(ConvArgs<R
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       const int ky = q * L + lc;
+      if constexpr (CF::LEAN) load_g(g[0], q);
+      const Cc (&gq)[V] = g[CF::LEAN ? 0 : q];
       Cc v[V];
 #pragma unroll
       for (int b = 0; b < V / R0; ++b) {
@@ -700,7 +698,7 @@ __global__ void __launch_bounds__((PlaneCfg<Rc, P>::THREADS)) k_plane(ConvArgs<R
       }
       fft_regs<Cc, P, NT, -1, FL, decltype(twf), BlockSync, false, true, false>(v, tk, E + lc, L, twf);
 #pragma unroll
-      for (int i = 0; i < V; ++i) v[i] = cmul(v[i], g[q][i]);
+      for (int i = 0; i < V; ++i) v[i] = cmul(v[i], gq[i]);
       fft_regs<Cc, P, NT, +1, IL, decltype(twi), BlockSync, false, false, true>(v, tk, E + lc, L, twi);
 #pragma unroll
       for (int b = 0; b < V / RLI; ++b) {
@@ -725,18 +723,303 @@ __global__ void __launch_bounds__((PlaneCfg<Rc, P>::THREADS)) k_plane(ConvArgs<R
         for (int r = 0; r < R0I; ++r) v[b * R0I + r] = B[x * SPAN + lds_index<true>(tid + b * NT + r * (P / R0I))];
       }
       fft_regs<Cc, P, NT, +1, IL, decltype(twi), WaveSync, true, false, true>(v, tid, B + x * SPAN, 1, twi);
-      if (x < n) {
 #pragma unroll
-        for (int b = 0; b < V / RLI; ++b) {
+      for (int b = 0; b < V / RLI; ++b) {
 #pragma unroll
-          for (int r = 0; r < RLI / 2; ++r) {
-            const int y = tid + b * NT + r * (P / RLI);
-            if (y < n) out[(size_t)x * n + y] = v[b * RLI + r];
-          }
+        for (int r = 0; r < RLI / 2; ++r) {
+          const int y = tid + b * NT + r * (P / RLI);
+          if (x < n && y < n) st(b * (RLI / 2) + r, x, y, v[b * RLI + r]);
         }
       }
     }
   }
+}
+
+template <typename Rs, typename Rc, int P, bool CONJ, bool MASK>
+__global__ void __launch_bounds__((PlaneCfg<Rc, P>::THREADS)) k_plane(ConvArgs<Rs, Rc> a) {
+  using Cc = cplx_t<Rc>;
+  using CF = PlaneCfg<Rc, P>;
+  const int kz = blockIdx.x, t = blockIdx.y;
+  if constexpr (MASK) {
+    if (!(a.st[t].flags & a.flag)) return;
+  }
+  if (a.fmask && !a.fmask[t]) return;
+  __shared__ Cc B[CF::NROW * CF::SPAN];
+  __shared__ Cc E[P * CF::LINES];
+  __shared__ Cc stw[P];
+  for (int i = threadIdx.x; i < P; i += CF::THREADS) stw[i] = a.tw[i];
+  __syncthreads();
+  const int n = a.n;
+  const size_t plane = ((size_t)t * P + kz) * (size_t)n * n;
+  const Cc *in = a.cin + plane;
+  Cc *out = a.cout + plane;
+  plane_conv<CF, Rc, P, CONJ>(
+      B, E, stw, a.Gpm + (size_t)kz * P * P, n, [&](int, int x, int y) { return in[(size_t)x * n + y]; },
+      [&](int, int x, int y, Cc v) { out[(size_t)x * n + y] = v; });
+}
+
+// ---------------------------------------------------------------- small 2D grids
+// Where the whole plane of a 2D transform fits in LDS (P = 64, and P = 128 in
+// FP32), one block convolves a field by itself: the three stages of an
+// application become one launch without intermediates in memory, and a
+// BiCGSTAB iteration, whose inner products then end in one block, needs no
+// launch at all.
+template <typename Rc, int P, bool LEAN_ = false> struct SmallCfg {
+  static constexpr bool LEAN = LEAN_;               // spectrum values fetched batch by batch
+  static constexpr bool POW2 = (P & (P - 1)) == 0;
+  static constexpr int V = 8, NT = P / V;
+  static constexpr int THREADS = 64 * NT;           // 64 column lines at a time
+  static constexpr int LINES = 64;
+  static constexpr int NROW = P / 2, SPAN = lds_span(P), BATCHES = P / LINES;
+  static constexpr int OWN = P / (2 * NT);          // samples per thread
+  static constexpr size_t LDS_BYTES = ((size_t)NROW * SPAN + (size_t)P * LINES + P) * 2 * sizeof(Rc);
+  static constexpr bool OK = POW2 && (P == 64 || (P == 128 && sizeof(Rc) == 4));
+};
+
+// y = A x, A^H x or G-type products of one field per block (EPI_AX, EPI_G,
+// EPI_GF, EPI_GRAD), as k_row_fwd, the column stage and k_row_inv form them.
+template <typename R, int P, int EPI, bool ADJ>
+__global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_conv_small(ConvArgs<R, R> a) {
+  using C = cplx_t<R>;
+  using CF = SmallCfg<R, P>;
+  constexpr bool PURE = EPI != EPI_AX;
+  constexpr bool FIN = (!ADJ && !PURE) || EPI == EPI_GF, FOUT = ADJ && !PURE;
+  const int t = blockIdx.x, n = a.n;
+  __shared__ C B[CF::NROW * CF::SPAN];
+  __shared__ C E[P * CF::LINES];
+  __shared__ C stw[P];
+  for (int i = threadIdx.x; i < P; i += CF::THREADS) stw[i] = a.tw[i];
+  __syncthreads();
+  const R *f = a.frow ? a.frow[t] : a.f;
+  const size_t base = (size_t)t * a.N;
+  const R scale = static_cast<R>(a.scale);
+  plane_conv<CF, R, P, ADJ>(
+      B, E, stw, a.Ghat, n,
+      [&](int, int x, int y) {
+        const int q = x * n + y;
+        const C v = a.x[base + q];
+        return FIN ? cscale(v, f[q]) : v;
+      },
+      [&](int, int x, int y, C v) {
+        const int q = x * n + y;
+        const size_t e = base + q;
+        C cv = cscale(v, scale);
+        if constexpr (FOUT) cv = cscale(cv, f[q]);
+        if constexpr (EPI == EPI_AX) {
+          a.y[e] = csub(a.x[e], cv);
+        } else if constexpr (EPI == EPI_GRAD) {
+          const C uu = a.u[e], s = cadd(a.q[e], cv);
+          a.gpart[e] = uu.x * s.x + uu.y * s.y;
+        } else {
+          a.y[e] = cv;
+        }
+      });
+}
+
+// BiCGSTAB iterations of one system per block (the recurrence of solver.hip,
+// stage by stage: see there), `count` of them or until the system pauses, and
+// what a chunk does around them: the start, the pending update of x and the
+// FP64 true residual.  A thread keeps its samples of p, v, s, t and f (and x
+// and rhat where they fit) in registers between stages; they live in the
+// context's work arrays between launches.
+// Bound by the transforms' dependent passes (one block, so one CU, per system).
+// Per iteration at 32^2 x 8 in FP64: SMALL_NEW us against 33 us for eight launches
+// of the staged path, which are 3 to 6 us each whatever the size.
+template <typename R, int P, bool ADJ>
+__global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(SmallArgs<R> a) {
+  using C = cplx_t<R>;
+  // where the registers do not hold everything (1024 threads, or FP64), x and
+  // rhat stay in memory and the spectrum is fetched batch by batch
+  constexpr bool LEAN = P == 128 || sizeof(R) == 8;
+  using CF = SmallCfg<R, P, LEAN>;
+  constexpr int OWN = CF::OWN, NT = CF::NT;
+  constexpr bool TR64 = SmallCfg<double, P>::OK;    // the FP64 plane fits too
+  using CT = std::conditional_t<TR64, cd, C>;
+  __shared__ __attribute__((aligned(16))) CT pool[CF::NROW * CF::SPAN + P * CF::LINES];
+  __shared__ C stw[P];
+  __shared__ cd stwd[TR64 ? P : 1];
+  __shared__ double scratch[16 * NPART];
+  __shared__ TxState st;
+  const int t = blockIdx.x, n = a.n, tid = threadIdx.x;
+  if (a.start < 0) {
+    const int status = a.st[t].status;
+    if (status == ST_DONE || status == ST_FAILED) return;
+  }
+  for (int i = tid; i < P; i += CF::THREADS) {
+    stw[i] = a.tw[i];
+    if constexpr (TR64) stwd[i] = a.twd[i];
+  }
+  if (tid == 0) {
+    if (a.start >= 0) st = initial_state();
+    else st = a.st[t];
+  }
+  __syncthreads();
+  const int row = tid / NT, tk = tid % NT;
+  // sample i of the thread and its element; P / NT samples apart as plane_conv hands them out
+  constexpr int R0 = FirstRadix<typename Plan<P>::fwd>::value;
+  auto col = [&](int i) __attribute__((always_inline)) { return tk + (i / (R0 / 2)) * NT + (i % (R0 / 2)) * (P / R0); };
+  const size_t base = (size_t)t * a.N;
+  const R *fr = a.frow ? a.frow[t] : a.f;
+  C xr[LEAN ? 1 : OWN], hr[LEAN ? 1 : OWN], p[OWN], v[OWN], s[OWN], tt[OWN];
+  R f[OWN];
+  unsigned e[OWN];   // element within the field
+  bool own[OWN];
+  auto x_get = [&](int i) __attribute__((always_inline)) -> C { return LEAN ? a.x[base + e[i]] : xr[LEAN ? 0 : i]; };
+  auto x_set = [&](int i, C val) __attribute__((always_inline)) {
+    if constexpr (LEAN) a.x[base + e[i]] = val;
+    else xr[i] = val;
+  };
+  auto h_get = [&](int i) __attribute__((always_inline)) -> C { return LEAN ? a.rhat[base + e[i]] : hr[LEAN ? 0 : i]; };
+#pragma unroll
+  for (int i = 0; i < OWN; ++i) {
+    own[i] = row < n && col(i) < n;
+    e[i] = own[i] ? (unsigned)(row * n + col(i)) : 0u;
+    p[i] = v[i] = s[i] = tt[i] = czero<C>();
+    if constexpr (!LEAN) xr[i] = hr[i] = czero<C>();
+    f[i] = R(0);
+    if (!own[i]) continue;
+    f[i] = fr[e[i]];
+    if (a.start == 0 || a.start == 1) x_set(i, a.start == 1 ? a.b[base + e[i]] : czero<C>());
+    else if constexpr (!LEAN) xr[i] = a.x[base + e[i]];
+    if (a.start >= 0) continue;
+    if constexpr (!LEAN) hr[i] = a.rhat[base + e[i]];
+    p[i] = a.p[base + e[i]];
+    v[i] = a.v[base + e[i]];
+    s[i] = a.s[base + e[i]];
+    tt[i] = a.t[base + e[i]];
+  }
+  C *const B = reinterpret_cast<C *>(pool), *const E = B + CF::NROW * CF::SPAN;
+  const R scale = static_cast<R>(a.scale);
+  // one scalar step from the block's sums of acc
+  auto step = [&](auto &acc, int stage) __attribute__((always_inline)) {
+    block_sum(acc, scratch);
+    if (tid == 0) advance_state(st, acc, stage, a.tol, a.replace_every, a.maxit);
+    __syncthreads();
+  };
+  // r = b - A x in precision Rc, its products, and the scalar step
+  auto residual = [&](auto one, const auto *G, const auto *tw, auto *Bc, auto *Ec,
+                      int stage) __attribute__((always_inline)) {
+    using Rc = decltype(one);
+    using Cc = cplx_t<Rc>;
+    const bool restart = st.restart != 0;
+    double acc[4] = {};
+    plane_conv<SmallCfg<Rc, P, LEAN>, Rc, P, ADJ>(
+        Bc, Ec, tw, G, n,
+        [&](int i, int, int) __attribute__((always_inline)) {
+          const Cc xv = ccast<Cc>(x_get(i));
+          return ADJ ? xv : cscale(xv, static_cast<Rc>(f[i]));
+        },
+        [&](int i, int, int, Cc cv) __attribute__((always_inline)) {
+          cv = cscale(cv, static_cast<Rc>(a.scale));
+          if constexpr (ADJ) cv = cscale(cv, static_cast<Rc>(f[i]));
+          const Cc bb = ccast<Cc>(a.b[base + e[i]]);
+          const Cc rr = cadd(csub(bb, ccast<Cc>(x_get(i))), cv);
+          const C rs = ccast<C>(rr);
+          a.r[base + e[i]] = rs;
+          const cd rd = ccast<cd>(rr), r2 = ccast<cd>(rs), bd = ccast<cd>(bb);
+          acc[0] += rd.x * rd.x + rd.y * rd.y;
+          if (restart) a.rhat[base + e[i]] = rs;
+          const cd hd = restart ? r2 : ccast<cd>(a.rhat[base + e[i]]);
+          acc[1] += hd.x * r2.x + hd.y * r2.y;
+          acc[2] += hd.x * r2.y - hd.y * r2.x;
+          acc[3] += bd.x * bd.x + bd.y * bd.y;
+        });
+    step(acc, stage);
+  };
+  if (a.start >= 0) residual(R(0), a.G, (const C *)stw, B, E, (int)STG_TR0);
+  for (int it = 0; it < a.count; ++it) {
+    if (!(st.flags & FLAG_ITER)) break;
+    const C om = ccast<C>(st.omega), be = ccast<C>(st.beta);
+    const bool fresh = st.r_fresh != 0, pend = st.x_pending != 0;
+    const bool bz = st.beta.x == 0.0 && st.beta.y == 0.0;
+    {
+      const C al = ccast<C>(st.alpha);
+#pragma unroll
+      for (int i = 0; i < OWN; ++i) {
+        if (!own[i]) continue;
+        C rr;
+        if (fresh) {
+          rr = a.r[base + e[i]];
+        } else {
+          rr = csub(s[i], cmul(om, tt[i]));
+          if (pend) x_set(i, cadd(x_get(i), cadd(cmul(al, p[i]), cmul(om, s[i]))));
+        }
+        p[i] = bz ? rr : cadd(rr, cmul(be, csub(p[i], cmul(om, v[i]))));
+      }
+    }
+    {
+      double acc[2] = {};
+      plane_conv<CF, R, P, ADJ>(
+          B, E, stw, a.G, n, [&](int i, int, int) __attribute__((always_inline)) { return ADJ ? p[i] : cscale(p[i], f[i]); },
+          [&](int i, int, int, C cv) __attribute__((always_inline)) {
+            cv = cscale(cv, scale);
+            if constexpr (ADJ) cv = cscale(cv, f[i]);
+            v[i] = csub(p[i], cv);
+            const cd hd = ccast<cd>(h_get(i)), w = ccast<cd>(v[i]);
+            acc[0] += hd.x * w.x + hd.y * w.y;
+            acc[1] += hd.x * w.y - hd.y * w.x;
+          });
+      step(acc, STG_ALPHA);
+    }
+    if (!(st.flags & FLAG_ITER)) break;
+    {
+      const C al = ccast<C>(st.alpha);
+#pragma unroll
+      for (int i = 0; i < OWN; ++i) {
+        if (!own[i]) continue;
+        const C rr = fresh ? a.r[base + e[i]] : csub(s[i], cmul(om, tt[i]));
+        s[i] = csub(rr, cmul(al, v[i]));
+      }
+    }
+    {
+      double acc[8] = {};
+      plane_conv<CF, R, P, ADJ>(
+          B, E, stw, a.G, n, [&](int i, int, int) __attribute__((always_inline)) { return ADJ ? s[i] : cscale(s[i], f[i]); },
+          [&](int i, int, int, C cv) __attribute__((always_inline)) {
+            cv = cscale(cv, scale);
+            if constexpr (ADJ) cv = cscale(cv, f[i]);
+            tt[i] = csub(s[i], cv);
+            const cd tv = ccast<cd>(tt[i]), sv = ccast<cd>(s[i]), hd = ccast<cd>(h_get(i));
+            acc[0] += tv.x * sv.x + tv.y * sv.y;
+            acc[1] += tv.x * sv.y - tv.y * sv.x;
+            acc[2] += tv.x * tv.x + tv.y * tv.y;
+            acc[3] += sv.x * sv.x + sv.y * sv.y;
+            acc[4] += hd.x * sv.x + hd.y * sv.y;
+            acc[5] += hd.x * sv.y - hd.y * sv.x;
+            acc[6] += hd.x * tv.x + hd.y * tv.y;
+            acc[7] += hd.x * tv.y - hd.y * tv.x;
+          });
+      step(acc, STG_OMEGA);
+    }
+  }
+  if (a.last) {
+    if (tid == 0 && (st.status == ST_ITER || st.status == ST_PAUSED)) st.flags = FLAG_TR;
+    __syncthreads();
+  }
+  if ((st.flags & FLAG_TR) && st.x_pending) {
+    const C al = ccast<C>(st.alpha), om = ccast<C>(st.omega);
+#pragma unroll
+    for (int i = 0; i < OWN; ++i)
+      if (own[i]) x_set(i, cadd(x_get(i), cadd(cmul(al, p[i]), cmul(om, s[i]))));
+  }
+#pragma unroll
+  for (int i = 0; i < OWN; ++i) {
+    if (!own[i]) continue;
+    if constexpr (!LEAN) a.x[base + e[i]] = xr[i];
+    if (a.start >= 0) continue;
+    a.p[base + e[i]] = p[i];
+    a.v[base + e[i]] = v[i];
+    a.s[base + e[i]] = s[i];
+    a.t[base + e[i]] = tt[i];
+  }
+  if constexpr (TR64) {
+    if (a.tr && (st.flags & FLAG_TR)) {
+      cd *const Bd = reinterpret_cast<cd *>(pool);
+      __syncthreads();   // the FP64 plane lies differently over the pool
+      residual(double(0), a.Gd, (const cd *)stwd, Bd, Bd + CF::NROW * CF::SPAN, (int)STG_TR);
+    }
+  }
+  if (tid == 0) a.st[t] = st;
 }
 
 // ---------------------------------------------------------------- launch
@@ -851,6 +1134,15 @@ int launch_conv_p(Ctx &c, ConvArgs<Rs, Rc> &a, bool adjoint) {
   a.rows = c.rows;
   a.scale = 1.0 / std::pow((double)P, c.dim);
   a.frow = (const Rs *const *)c.frow;
+  if constexpr (std::is_same<Rs, Rc>::value && SmallCfg<Rc, P>::OK && PRO == PRO_X && EPI != EPI_TR) {
+    // one launch per application on small 2D grids (the rule is small_path's)
+    if (c.dim == 2 && c.T <= SMALL_MAX_T) {
+      const dim3 b(SmallCfg<Rc, P>::THREADS);
+      if (adjoint) hipLaunchKernelGGL((k_conv_small<Rs, P, EPI, true>), dim3(c.T), b, 0, c.stream, a);
+      else hipLaunchKernelGGL((k_conv_small<Rs, P, EPI, false>), dim3(c.T), b, 0, c.stream, a);
+      return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
+    }
+  }
   using CF = ColCfg<Rc, P, 0>;
   constexpr int CT = CF::THREADS, CC = CF::COLS;
   dim3 grow((a.rows + RowCfg<P>::ROWS - 1) / RowCfg<P>::ROWS, c.T);
@@ -920,6 +1212,13 @@ int launch_conv_p(Ctx &c, ConvArgs<Rs, Rc> &a, bool adjoint) {
                        a);
   }
   rows(std::false_type{}, true);
+  return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
+}
+
+template <typename R, int P> int launch_small_p(Ctx &c, const SmallArgs<R> &a, bool adjoint) {
+  const dim3 b(SmallCfg<R, P>::THREADS);
+  if (adjoint) hipLaunchKernelGGL((k_solve_small<R, P, true>), dim3(c.T), b, 0, c.stream, a);
+  else hipLaunchKernelGGL((k_solve_small<R, P, false>), dim3(c.T), b, 0, c.stream, a);
   return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
 }
 

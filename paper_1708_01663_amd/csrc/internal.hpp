@@ -86,6 +86,27 @@ template <typename Rs, typename Rc> struct ConvArgs {
   const Cc *Gpm;          // 3D plane path: the kernel spectrum kz-major, [kz][kx][ky]
 };
 
+// Arguments of the kernel that runs whole BiCGSTAB iterations of a small 2D
+// system (one block per system; see k_solve_small).
+template <typename R> struct SmallArgs {
+  using C = cplx_t<R>;
+  int n, N;
+  const R *f;
+  const R *const *frow;     // per-field contrast pointers (replace f when set)
+  const C *b;
+  C *x, *r, *rhat, *p, *v, *s, *t;
+  TxState *st;
+  const C *G, *tw;          // kernel spectrum and twiddles in the field precision
+  const cd *Gd, *twd;       // and in FP64
+  double scale;             // 1 / P^2
+  int start;                // 0 zero, 1 x = b, 2 x as it is: fresh state and starting residual; -1: none
+  int count;                // iterations
+  int last;                 // flag every unfinished system for its true residual afterwards
+  int tr;                   // evaluate the FP64 true residual of the flagged system afterwards
+  double tol;
+  int replace_every, maxit;
+};
+
 // Identity of a captured launch sequence: the kernels' pointer and scalar
 // arguments are baked into the graph, so every one of them is part of the key.
 struct GraphKey {
@@ -194,6 +215,13 @@ template <typename Rs, typename Rc, int P, int PRO, int EPI>
 int launch_conv_p(Ctx &c, ConvArgs<Rs, Rc> &a, bool adjoint);
 template <typename Rs, typename Rc, int P>
 int launch_stage_p(Ctx &c, ConvArgs<Rs, Rc> &a, int stage, bool adjoint);
+
+// Whether the context's solves run in k_solve_small, and whether that kernel
+// also evaluates the FP64 true residual (else the three operator stages do).
+template <typename R> bool small_path(const Ctx &c);
+template <typename R> bool small_residual(const Ctx &c);
+template <typename R> int launch_small(Ctx &c, const SmallArgs<R> &a, bool adjoint);
+template <typename R, int P> int launch_small_p(Ctx &c, const SmallArgs<R> &a, bool adjoint);
 
 template <typename R>
 int solve_batch(Ctx &c, const R *f, const cplx_t<R> *b, cplx_t<R> *x, bool adjoint,

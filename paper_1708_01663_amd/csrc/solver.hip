@@ -38,40 +38,14 @@
 #include <cmath>
 #include <vector>
 
-#include "internal.hpp"
+#include "solver_state.hpp"
 
 namespace cisor {
-
-// STG_TR: FP64 true residual (the stop test); STG_TR0: provisional starting
-// residual in the field precision, which never finishes a system with x != 0.
-enum : int { STG_ALPHA = 0, STG_OMEGA = 1, STG_TR = 3, STG_TR0 = 4 };
-
-// Residual replacement when the recurrence residual^2 has fallen below this
-// fraction of its largest value since the last replacement (a drop by ~31.6x
-// in norm).  Measured on the 256^2 x 60 true-phantom solves: the slowest of 60
-// systems needed 443-467 iterations instead of 508-933 (the FP32 tail varies
-// with rounding; the FP64 solver needs 375), at about 1 % more time per solve
-// where the solves are short.
-constexpr double REPLACE_DROP2 = 1e-3;
-
-__device__ __forceinline__ cd cd_div(cd a, cd b) {
-  const double den = b.x * b.x + b.y * b.y;
-  return mk<cd>((a.x * b.x + a.y * b.y) / den, (a.y * b.x - a.x * b.y) / den);
-}
-__device__ __forceinline__ cd cd_mul(cd a, cd b) { return mk<cd>(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
-__device__ __forceinline__ bool cd_ok(cd a) { return isfinite(a.x) && isfinite(a.y); }
-__device__ __forceinline__ bool cd_zero(cd a) { return a.x == 0.0 && a.y == 0.0; }
 
 __global__ void k_init_state(TxState *st, int T) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= T) return;
-  TxState s{};
-  s.status = ST_PAUSED;
-  s.flags = FLAG_TR;
-  s.restart = 1;
-  s.rho = s.rho_prev = s.alpha = s.omega = mk<cd>(1.0, 0.0);
-  s.beta = mk<cd>(0.0, 0.0);
-  st[t] = s;
+  st[t] = initial_state();
 }
 
 // One block of 64 threads per transmitter: sum the partial slots in a fixed
@@ -93,103 +67,7 @@ __global__ void __launch_bounds__(64) k_scalar(TxState *st, const double *part, 
 #pragma unroll
   for (int k = 0; k < NPART; ++k) acc[k] = wave_sum(acc[k]);
   if (threadIdx.x != 0) return;
-  const double tol2 = tol * tol;
-  if (stage == STG_ALPHA) {
-    const cd rhv = mk<cd>(acc[0], acc[1]);
-    s.x_pending = 0;   // stage A has applied the last iteration's x update
-    if (cd_zero(rhv) || !cd_ok(rhv)) {
-      s.status = ST_PAUSED;
-      s.flags = FLAG_TR;
-      s.restart = 1;
-    } else {
-      s.alpha = cd_div(s.rho, rhv);
-    }
-  } else if (stage == STG_OMEGA) {
-    const cd ts = mk<cd>(acc[0], acc[1]);
-    const double tt = acc[2], ss = acc[3];
-    const cd rs = mk<cd>(acc[4], acc[5]), rt = mk<cd>(acc[6], acc[7]);
-    double rr;
-    if (tt == 0.0 || !std::isfinite(tt) || !cd_ok(ts)) {
-      s.omega = mk<cd>(0.0, 0.0);
-      rr = ss;
-    } else {
-      s.omega = mk<cd>(ts.x / tt, ts.y / tt);
-      rr = fmax(ss - (ts.x * ts.x + ts.y * ts.y) / tt, 0.0);   // ||s - omega t||^2
-    }
-    const cd wrt = cd_mul(s.omega, rt);
-    const cd rho_new = mk<cd>(rs.x - wrt.x, rs.y - wrt.y);       // <rhat, s - omega t>
-    s.r_fresh = 0;
-    s.x_pending = 1;
-    s.iters += 1;
-    s.rnorm2 = rr;
-    s.rmax2 = fmax(s.rmax2, rr);
-    const bool conv = rr <= tol2 * s.bnorm2;
-    const bool brk = cd_zero(s.omega) || cd_zero(rho_new) || !cd_ok(rho_new) || !std::isfinite(rr);
-    if (!brk) {
-      s.beta = cd_mul(cd_div(rho_new, s.rho), cd_div(s.alpha, s.omega));
-      s.rho_prev = s.rho;
-      s.rho = rho_new;
-    }
-    if (conv) {
-      s.status = ST_PAUSED;
-      s.flags = FLAG_TR;
-      s.restart = brk ? 1 : 0;
-    } else if (brk) {
-      s.status = ST_PAUSED;
-      s.flags = FLAG_TR;
-      s.restart = 1;
-    } else if (s.iters - s.last_tr >= replace_every || s.iters >= maxit || rr < REPLACE_DROP2 * s.rmax2) {
-      s.flags = FLAG_ITER | FLAG_TR;
-    }
-  } else {  // STG_TR: r = b - A x has just been computed in FP64 (x up to date)
-    const double rr = acc[0];
-    const cd rhr = mk<cd>(acc[1], acc[2]);
-    if (s.restart) s.bnorm2 = acc[3];
-    s.last_tr = s.iters;
-    s.rmax2 = rr;
-    s.rnorm2 = rr;
-    s.x_pending = 0;
-    s.r_fresh = 1;
-    if (s.bnorm2 == 0.0) {
-      s.true_rel = 0.0;
-      s.status = ST_DONE;
-      s.flags = 0;
-      s.zero_x = 1;
-    } else if (!std::isfinite(rr)) {
-      s.true_rel = rr;
-      s.status = ST_FAILED;
-      s.flags = 0;
-    } else {
-      s.true_rel = sqrt(rr / s.bnorm2);
-      if (rr <= tol2 * s.bnorm2 && stage == STG_TR0) {
-        s.status = ST_PAUSED;   // looks converged: confirm with the FP64 residual
-        s.flags = FLAG_TR;
-      } else if (rr <= tol2 * s.bnorm2) {
-        s.status = ST_DONE;
-        s.flags = 0;
-      } else if (s.restart) {
-        s.rho = rhr;
-        s.rho_prev = mk<cd>(1.0, 0.0);
-        s.alpha = s.omega = mk<cd>(1.0, 0.0);
-        s.beta = mk<cd>(0.0, 0.0);
-        s.restart = 0;
-        s.status = ST_ITER;
-        s.flags = FLAG_ITER;
-      } else {
-        // residual replacement: keep the search directions, rebase rho
-        if (cd_zero(rhr) || !cd_ok(rhr)) {
-          s.restart = 1;
-          s.status = ST_PAUSED;
-          s.flags = FLAG_TR;
-        } else {
-          s.beta = cd_mul(cd_div(rhr, s.rho_prev), cd_div(s.alpha, s.omega));
-          s.rho = rhr;
-          s.status = ST_ITER;
-          s.flags = FLAG_ITER;
-        }
-      }
-    }
-  }
+  advance_state(s, acc, stage, tol, replace_every, maxit);
   st[t] = s;
 }
 
@@ -364,6 +242,31 @@ static int true_residual(Ctx &c, const R *f, const cplx_t<R> *b, const cplx_t<R>
   return launch_conv<R, Rc, PRO_X, EPI_TR>(c, a, adjoint);
 }
 
+// A job's arguments of the kernel for small grids (no iterations, no start).
+template <typename R> static SmallArgs<R> small_args(const SolveJob &j, const cisor_ls_opts &o, int replace_every) {
+  using C = cplx_t<R>;
+  Ctx &c = *j.c;
+  SmallArgs<R> a{};
+  a.n = c.n;
+  a.N = c.N;
+  a.f = (const R *)j.f;
+  a.frow = (const R *const *)c.frow;
+  a.b = (const C *)j.b;
+  a.x = (C *)j.x;
+  a.r = (C *)c.ws[0], a.rhat = (C *)c.ws[1], a.p = (C *)c.ws[2], a.v = (C *)c.ws[3], a.s = (C *)c.ws[4];
+  a.t = (C *)c.ws[5];
+  a.st = c.st;
+  a.G = (const C *)c.Ghat, a.tw = (const C *)c.tw;
+  a.Gd = std::is_same<R, double>::value ? (const cd *)c.Ghat : c.Ghat_d;
+  a.twd = std::is_same<R, double>::value ? (const cd *)c.tw : c.tw_d;
+  a.scale = 1.0 / ((double)c.P * c.P);
+  a.start = -1;
+  a.tol = o.tol;
+  a.replace_every = replace_every;
+  a.maxit = o.maxit;
+  return a;
+}
+
 // Start of one job: starting guess, fresh states, first true residual.
 template <typename R>
 static int job_start(SolveJob &j, bool adjoint, const cisor_ls_opts &o, int replace_every) {
@@ -375,6 +278,11 @@ static int job_start(SolveJob &j, bool adjoint, const cisor_ls_opts &o, int repl
   const size_t TN = (size_t)c.T * c.N;
   C *r = (C *)c.ws[0], *rhat = (C *)c.ws[1], *p = (C *)c.ws[2], *v = (C *)c.ws[3], *s = (C *)c.ws[4];
   int e;
+  if (small_path<R>(c) && o.start <= 2) {
+    SmallArgs<R> a = small_args<R>(j, o, replace_every);
+    a.start = o.start;
+    return launch_small<R>(c, a, adjoint);
+  }
   if (o.start == 0) {
     launch_fill<C>(c.stream, x, TN, mk<C>(0, 0));
   } else if (o.start == 1) {
@@ -426,6 +334,19 @@ static int job_chunk(SolveJob &j, bool adjoint, const cisor_ls_opts &o, int repl
   C *x = (C *)j.x;
   C *r = (C *)c.ws[0], *rhat = (C *)c.ws[1], *p = (C *)c.ws[2], *v = (C *)c.ws[3], *s = (C *)c.ws[4],
     *tv = (C *)c.ws[5];
+  int e;
+  const bool small = small_path<R>(c);
+  if (small) {
+    SmallArgs<R> a = small_args<R>(j, o, replace_every);
+    a.count = count;
+    a.last = last;
+    a.tr = small_residual<R>(c);
+    if ((e = launch_small<R>(c, a, adjoint))) return e;
+    if (a.tr) {
+      hipLaunchKernelGGL(k_count_open, dim3(1), dim3(64), 0, c.stream, c.st, c.T, d_count);
+      return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
+    }
+  }
   ConvArgs<R, R> aA{}, aB{};
   fill_tables<R>(c, aA.Ghat, aA.tw, aA.X1, aA.X2);
   aA.f = f;
@@ -444,8 +365,7 @@ static int job_chunk(SolveJob &j, bool adjoint, const cisor_ls_opts &o, int repl
   aB.xw = nullptr;
   aB.y = tv;
   const dim3 gupd(c.nub, c.T);
-  int e;
-  for (int i = 0; i < count; ++i) {
+  for (int i = 0; !small && i < count; ++i) {
     if ((e = launch_conv<R, R, PRO_PUPD, EPI_V>(c, aA, adjoint))) return e;
     hipLaunchKernelGGL(k_scalar, dim3(c.T), dim3(64), 0, c.stream, c.st, c.part, c.nrb, (int)STG_ALPHA, o.tol,
                        replace_every, o.maxit);
@@ -453,9 +373,10 @@ static int job_chunk(SolveJob &j, bool adjoint, const cisor_ls_opts &o, int repl
     hipLaunchKernelGGL(k_scalar, dim3(c.T), dim3(64), 0, c.stream, c.st, c.part, c.nrb, (int)STG_OMEGA, o.tol,
                        replace_every, o.maxit);
   }
-  if (last) hipLaunchKernelGGL(k_mark_unfinished, dim3((c.T + 63) / 64), dim3(64), 0, c.stream, c.st, c.T);
-  hipLaunchKernelGGL(k_apply_pending<R>, gupd, dim3(UPD_THREADS), 0, c.stream, c.st, x, (const cplx_t<R> *)p,
-                     (const cplx_t<R> *)s, c.N);
+  if (!small && last) hipLaunchKernelGGL(k_mark_unfinished, dim3((c.T + 63) / 64), dim3(64), 0, c.stream, c.st, c.T);
+  if (!small)
+    hipLaunchKernelGGL(k_apply_pending<R>, gupd, dim3(UPD_THREADS), 0, c.stream, c.st, x, (const cplx_t<R> *)p,
+                       (const cplx_t<R> *)s, c.N);
   if ((e = true_residual<R>(c, f, b, x, r, rhat, adjoint))) return e;
   hipLaunchKernelGGL(k_scalar, dim3(c.T), dim3(64), 0, c.stream, c.st, c.part, c.nrb, (int)STG_TR, o.tol,
                      replace_every, o.maxit);
@@ -532,7 +453,8 @@ int solve_multi(SolveJob *jobs, int nj, SolveShared &sh, hipStream_t main, bool 
       });
     };
     int g = 1;
-    if (!last) {
+    // (two launches of one small context are cheaper than their graph)
+    if (!last && !(nj == 1 && !forked && small_path<R>(*jobs[0].c))) {
       GraphKey key;
       for (int k : act) {
         key.ptrs.push_back(jobs[k].c);
