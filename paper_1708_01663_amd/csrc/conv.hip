@@ -76,25 +76,10 @@ int launch_conv(Ctx &c, ConvArgs<Rs, Rc> &a, bool adjoint) {
   }
 }
 
-// Grids whose transform plane fits one block's LDS (PlaneCfg of the length in
-// the precision concerned).  A system then has one block for all its work, so
-// it is no longer the faster way once there are so many systems that every
-// CU has several rounds of them while the three stages fill the chip anyway.
-template <typename R> bool small_path(const Ctx &c) {
-  return c.dim == 2 && c.P <= (sizeof(R) == 4 ? 128 : 64) && c.T <= SMALL_MAX_T;
-}
-template <typename R> bool small_residual(const Ctx &c) { return c.P <= 64; }
+bool small_path(const Ctx &c) { return c.dim == 2 && c.P == 64; }
 template <typename R> int launch_small(Ctx &c, const SmallArgs<R> &a, bool adjoint) {
-  if (c.P == 64) return launch_small_p<R, 64>(c, a, adjoint);
-  if constexpr (sizeof(R) == 4) {
-    if (c.P == 128) return launch_small_p<R, 128>(c, a, adjoint);
-  }
-  return CISOR_E_UNSUPPORTED;
+  return launch_small_p<R, 64>(c, a, adjoint);
 }
-template bool small_path<float>(const Ctx &);
-template bool small_path<double>(const Ctx &);
-template bool small_residual<float>(const Ctx &);
-template bool small_residual<double>(const Ctx &);
 template int launch_small<float>(Ctx &, const SmallArgs<float> &, bool);
 template int launch_small<double>(Ctx &, const SmallArgs<double> &, bool);
 

@@ -27,9 +27,6 @@ namespace cisor {
 //         (k_colbw); radix plan Plan<P>
 constexpr int COL_VARIANTS = 10;
 
-// Most systems of a context whose solves run one block per system.
-constexpr int SMALL_MAX_T = 512;
-
 constexpr int pow2_floor(int x) { return x >= 2 ? 2 * pow2_floor(x / 2) : 1; }
 
 // Column-stage tiling: V points per thread, COLS columns per block, block of

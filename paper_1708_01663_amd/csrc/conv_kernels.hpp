@@ -759,21 +759,28 @@ __global__ void __launch_bounds__((PlaneCfg<Rc, P>::THREADS)) k_plane(ConvArgs<R
 }
 
 // ---------------------------------------------------------------- small 2D grids
-// Where the whole plane of a 2D transform fits in LDS (P = 64, and P = 128 in
-// FP32), one block convolves a field by itself: the three stages of an
-// application become one launch without intermediates in memory, and a
+// Where the whole plane of a 2D transform fits in LDS in FP64 too (P = 64,
+// grids up to 32^2), one block convolves a field by itself: the three stages of
+// an application become one launch without intermediates in memory, and a
 // BiCGSTAB iteration, whose inner products then end in one block, needs no
-// launch at all.
-template <typename Rc, int P, bool LEAN_ = false> struct SmallCfg {
-  static constexpr bool LEAN = LEAN_;               // spectrum values fetched batch by batch
-  static constexpr bool POW2 = (P & (P - 1)) == 0;
+// launch at all.  Against the staged path (us; 7 to 9 iterations a solve):
+//   32^2, T =          8        64       256      512      1024
+//   operator  c64   13.9/9.3  14.3/9.4  14.0/9.0 19.7/9.3 25.6/14.7
+//             c128  13.9/8.8  13.7/8.9  15.0/9.2 24.7/17  36.9/31
+//   solve     c64   359/145   381/148   598/207  705/328  920/550
+//             c128  385/192   406/195   602/229  776/409  1163/736
+// so the rule asks for the length only.  At P = 128 the complex64 plane alone
+// would fit, but one CU takes 16 us for it where three launches over up to 64
+// transmitters take 15.
+template <typename Rc, int P> struct SmallCfg {
   static constexpr int V = 8, NT = P / V;
-  static constexpr int THREADS = 64 * NT;           // 64 column lines at a time
-  static constexpr int LINES = 64;
+  static constexpr int LINES = 64;                  // column lines at a time
+  static constexpr int THREADS = LINES * NT;
   static constexpr int NROW = P / 2, SPAN = lds_span(P), BATCHES = P / LINES;
   static constexpr int OWN = P / (2 * NT);          // samples per thread
-  static constexpr size_t LDS_BYTES = ((size_t)NROW * SPAN + (size_t)P * LINES + P) * 2 * sizeof(Rc);
-  static constexpr bool OK = POW2 && (P == 64 || (P == 128 && sizeof(Rc) == 4));
+  static constexpr bool OK = P == 64;
+  // spectrum values fetched batch by batch (the FP64 solver's registers do not hold them as well)
+  static constexpr bool LEAN = sizeof(Rc) == 8;
 };
 
 // y = A x, A^H x or G-type products of one field per block (EPI_AX, EPI_G,
@@ -823,21 +830,17 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_conv_small(ConvAr
 // and rhat where they fit) in registers between stages; they live in the
 // context's work arrays between launches.
 // Bound by the transforms' dependent passes (one block, so one CU, per system).
-// Per iteration at 32^2 x 8 in FP64: SMALL_NEW us against 33 us for eight launches
-// of the staged path, which are 3 to 6 us each whatever the size.
+// Per iteration at 32^2 x 8 in FP64: 16 us against 33 us for eight launches of
+// the staged path, which are 3 to 6 us each whatever the size.
 template <typename R, int P, bool ADJ>
 __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(SmallArgs<R> a) {
   using C = cplx_t<R>;
-  // where the registers do not hold everything (1024 threads, or FP64), x and
-  // rhat stay in memory and the spectrum is fetched batch by batch
-  constexpr bool LEAN = P == 128 || sizeof(R) == 8;
-  using CF = SmallCfg<R, P, LEAN>;
+  using CF = SmallCfg<R, P>;
+  constexpr bool LEAN = CF::LEAN;   // FP64: x and rhat stay in memory
   constexpr int OWN = CF::OWN, NT = CF::NT;
-  constexpr bool TR64 = SmallCfg<double, P>::OK;    // the FP64 plane fits too
-  using CT = std::conditional_t<TR64, cd, C>;
-  __shared__ __attribute__((aligned(16))) CT pool[CF::NROW * CF::SPAN + P * CF::LINES];
+  __shared__ cd pool[CF::NROW * CF::SPAN + P * CF::LINES];
   __shared__ C stw[P];
-  __shared__ cd stwd[TR64 ? P : 1];
+  __shared__ cd stwd[P];
   __shared__ double scratch[16 * NPART];
   __shared__ TxState st;
   const int t = blockIdx.x, n = a.n, tid = threadIdx.x;
@@ -847,7 +850,7 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
   }
   for (int i = tid; i < P; i += CF::THREADS) {
     stw[i] = a.tw[i];
-    if constexpr (TR64) stwd[i] = a.twd[i];
+    stwd[i] = a.twd[i];
   }
   if (tid == 0) {
     if (a.start >= 0) st = initial_state();
@@ -903,7 +906,7 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
     using Cc = cplx_t<Rc>;
     const bool restart = st.restart != 0;
     double acc[4] = {};
-    plane_conv<SmallCfg<Rc, P, LEAN>, Rc, P, ADJ>(
+    plane_conv<SmallCfg<Rc, P>, Rc, P, ADJ>(
         Bc, Ec, tw, G, n,
         [&](int i, int, int) __attribute__((always_inline)) {
           const Cc xv = ccast<Cc>(x_get(i));
@@ -1012,12 +1015,9 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
     a.s[base + e[i]] = s[i];
     a.t[base + e[i]] = tt[i];
   }
-  if constexpr (TR64) {
-    if (a.tr && (st.flags & FLAG_TR)) {
-      cd *const Bd = reinterpret_cast<cd *>(pool);
-      __syncthreads();   // the FP64 plane lies differently over the pool
-      residual(double(0), a.Gd, (const cd *)stwd, Bd, Bd + CF::NROW * CF::SPAN, (int)STG_TR);
-    }
+  if (a.tr && (st.flags & FLAG_TR)) {
+    __syncthreads();   // the FP64 plane lies differently over the pool
+    residual(double(0), a.Gd, (const cd *)stwd, pool, pool + CF::NROW * CF::SPAN, (int)STG_TR);
   }
   if (tid == 0) a.st[t] = st;
 }
@@ -1135,8 +1135,8 @@ int launch_conv_p(Ctx &c, ConvArgs<Rs, Rc> &a, bool adjoint) {
   a.scale = 1.0 / std::pow((double)P, c.dim);
   a.frow = (const Rs *const *)c.frow;
   if constexpr (std::is_same<Rs, Rc>::value && SmallCfg<Rc, P>::OK && PRO == PRO_X && EPI != EPI_TR) {
-    // one launch per application on small 2D grids (the rule is small_path's)
-    if (c.dim == 2 && c.T <= SMALL_MAX_T) {
+    // one launch per application on small 2D grids
+    if (c.dim == 2) {
       const dim3 b(SmallCfg<Rc, P>::THREADS);
       if (adjoint) hipLaunchKernelGGL((k_conv_small<Rs, P, EPI, true>), dim3(c.T), b, 0, c.stream, a);
       else hipLaunchKernelGGL((k_conv_small<Rs, P, EPI, false>), dim3(c.T), b, 0, c.stream, a);

@@ -21,10 +21,8 @@ namespace cisor {
 CISOR_INST_P(float, float)
 CISOR_INST_P(double, double)
 template int launch_conv_p<float, double, CISOR_P, PRO_X, EPI_TR>(Ctx &, ConvArgs<float, double> &, bool);
-#if CISOR_P <= 128
+#if CISOR_P == 64
 template int launch_small_p<float, CISOR_P>(Ctx &, const SmallArgs<float> &, bool);
-#endif
-#if CISOR_P <= 64
 template int launch_small_p<double, CISOR_P>(Ctx &, const SmallArgs<double> &, bool);
 #endif
 

@@ -397,7 +397,6 @@ __global__ void __launch_bounds__(256, 2) k_backproject_f64(const cd *H, const c
   for (int j = 0; j < TB; ++j)
 #pragma unroll
     for (int i = 0; i < KA; ++i) re[j][i] = im[j][i] = doublex4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 2
   for (int mb = 0; mb < M; mb += 4) {
     const bool ok = mb + g < M;
     const int m = min(mb + g, M - 1);   // loaded without a branch, zeroed past the end

@@ -216,10 +216,9 @@ int launch_conv_p(Ctx &c, ConvArgs<Rs, Rc> &a, bool adjoint);
 template <typename Rs, typename Rc, int P>
 int launch_stage_p(Ctx &c, ConvArgs<Rs, Rc> &a, int stage, bool adjoint);
 
-// Whether the context's solves run in k_solve_small, and whether that kernel
-// also evaluates the FP64 true residual (else the three operator stages do).
-template <typename R> bool small_path(const Ctx &c);
-template <typename R> bool small_residual(const Ctx &c);
+// Whether the context's solves run in k_solve_small (2D grids whose transform
+// length is 64; see SmallCfg).
+bool small_path(const Ctx &c);
 template <typename R> int launch_small(Ctx &c, const SmallArgs<R> &a, bool adjoint);
 template <typename R, int P> int launch_small_p(Ctx &c, const SmallArgs<R> &a, bool adjoint);
 

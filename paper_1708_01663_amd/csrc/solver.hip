@@ -278,7 +278,7 @@ static int job_start(SolveJob &j, bool adjoint, const cisor_ls_opts &o, int repl
   const size_t TN = (size_t)c.T * c.N;
   C *r = (C *)c.ws[0], *rhat = (C *)c.ws[1], *p = (C *)c.ws[2], *v = (C *)c.ws[3], *s = (C *)c.ws[4];
   int e;
-  if (small_path<R>(c) && o.start <= 2) {
+  if (small_path(c) && o.start <= 2) {
     SmallArgs<R> a = small_args<R>(j, o, replace_every);
     a.start = o.start;
     return launch_small<R>(c, a, adjoint);
@@ -335,17 +335,14 @@ static int job_chunk(SolveJob &j, bool adjoint, const cisor_ls_opts &o, int repl
   C *r = (C *)c.ws[0], *rhat = (C *)c.ws[1], *p = (C *)c.ws[2], *v = (C *)c.ws[3], *s = (C *)c.ws[4],
     *tv = (C *)c.ws[5];
   int e;
-  const bool small = small_path<R>(c);
-  if (small) {
+  if (small_path(c)) {
     SmallArgs<R> a = small_args<R>(j, o, replace_every);
     a.count = count;
     a.last = last;
-    a.tr = small_residual<R>(c);
+    a.tr = 1;
     if ((e = launch_small<R>(c, a, adjoint))) return e;
-    if (a.tr) {
-      hipLaunchKernelGGL(k_count_open, dim3(1), dim3(64), 0, c.stream, c.st, c.T, d_count);
-      return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
-    }
+    hipLaunchKernelGGL(k_count_open, dim3(1), dim3(64), 0, c.stream, c.st, c.T, d_count);
+    return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
   }
   ConvArgs<R, R> aA{}, aB{};
   fill_tables<R>(c, aA.Ghat, aA.tw, aA.X1, aA.X2);
@@ -365,7 +362,7 @@ static int job_chunk(SolveJob &j, bool adjoint, const cisor_ls_opts &o, int repl
   aB.xw = nullptr;
   aB.y = tv;
   const dim3 gupd(c.nub, c.T);
-  for (int i = 0; !small && i < count; ++i) {
+  for (int i = 0; i < count; ++i) {
     if ((e = launch_conv<R, R, PRO_PUPD, EPI_V>(c, aA, adjoint))) return e;
     hipLaunchKernelGGL(k_scalar, dim3(c.T), dim3(64), 0, c.stream, c.st, c.part, c.nrb, (int)STG_ALPHA, o.tol,
                        replace_every, o.maxit);
@@ -373,10 +370,9 @@ static int job_chunk(SolveJob &j, bool adjoint, const cisor_ls_opts &o, int repl
     hipLaunchKernelGGL(k_scalar, dim3(c.T), dim3(64), 0, c.stream, c.st, c.part, c.nrb, (int)STG_OMEGA, o.tol,
                        replace_every, o.maxit);
   }
-  if (!small && last) hipLaunchKernelGGL(k_mark_unfinished, dim3((c.T + 63) / 64), dim3(64), 0, c.stream, c.st, c.T);
-  if (!small)
-    hipLaunchKernelGGL(k_apply_pending<R>, gupd, dim3(UPD_THREADS), 0, c.stream, c.st, x, (const cplx_t<R> *)p,
-                       (const cplx_t<R> *)s, c.N);
+  if (last) hipLaunchKernelGGL(k_mark_unfinished, dim3((c.T + 63) / 64), dim3(64), 0, c.stream, c.st, c.T);
+  hipLaunchKernelGGL(k_apply_pending<R>, gupd, dim3(UPD_THREADS), 0, c.stream, c.st, x, (const cplx_t<R> *)p,
+                     (const cplx_t<R> *)s, c.N);
   if ((e = true_residual<R>(c, f, b, x, r, rhat, adjoint))) return e;
   hipLaunchKernelGGL(k_scalar, dim3(c.T), dim3(64), 0, c.stream, c.st, c.part, c.nrb, (int)STG_TR, o.tol,
                      replace_every, o.maxit);
@@ -454,7 +450,7 @@ int solve_multi(SolveJob *jobs, int nj, SolveShared &sh, hipStream_t main, bool 
     };
     int g = 1;
     // (two launches of one small context are cheaper than their graph)
-    if (!last && !(nj == 1 && !forked && small_path<R>(*jobs[0].c))) {
+    if (!last && !(nj == 1 && !forked && small_path(*jobs[0].c))) {
       GraphKey key;
       for (int k : act) {
         key.ptrs.push_back(jobs[k].c);

@@ -67,17 +67,16 @@ def test_iteration_cap_and_zero_systems(prec, n):
     assert code == 0 and rel(to_np(often), to_np(long)) < 1e-4
 
 
-def test_many_systems_take_the_staged_path():
-    """One context either side of the most systems that run one block each: the same fields."""
+def test_many_systems():
+    """More systems than CUs, several blocks a CU: each gets the field it gets alone."""
     from paper_1708_01663_amd.cisor import Cisor, SolveOpts, ring
-    n, M = 6, 4
+    n, M, T = 6, 4, 700
     f = torch.as_tensor(contrast(n).ravel()).float().cuda()
-    out = []
-    for T in (512, 513):
-        say(f"small grid T={T}")
-        a = 0.01 * np.arange(T)
-        op = Cisor(n, H, np.stack([np.cos(a), np.sin(a)], 1), ring(M, n * H))
-        u, _, _, code = op.forward(f, SolveOpts(tol=1e-6, start=1))
-        assert code == 0
-        out.append(to_np(u)[:512])
-    assert rel(out[0], out[1]) < 1e-4
+    a = 0.01 * np.arange(T)
+    dirs = np.stack([np.cos(a), np.sin(a)], 1)
+    say(f"small grid T={T}")
+    u, _, its, code = Cisor(n, H, dirs, ring(M, n * H)).forward(f, SolveOpts(tol=1e-6, start=1))
+    assert code == 0
+    for t in (0, 255, 699):
+        one, _, it1, _ = Cisor(n, H, dirs[t:t + 1], ring(M, n * H)).forward(f, SolveOpts(tol=1e-6, start=1))
+        assert rel(to_np(u)[t], to_np(one)[0]) < 1e-6 and it1[0] == its[t]
