@@ -157,26 +157,34 @@ __global__ void __launch_bounds__(256) k_project_mfma(const cf *H, const float *
   // three real products per complex one (Gauss): P1 = Hr Xr, P2 = Hi Xi,
   // P3 = (Hr + Hi)(Xr + Xi); Re = P1 - P2, Im = P3 - P1 - P2
   floatx16 acc1 = {0}, acc2 = {0}, acc3 = {0};
-  // the next step's H and f u elements are loaded into registers while the
-  // current step runs on the matrix cores
+  // the next step's H, u and f elements are loaded into registers while the
+  // current step runs on the matrix cores, without branches or arithmetic
+  // (forming f u here would wait for the loads before the MFMAs: 137 instead
+  // of 105 us at 360 x 65536 x 60); rows past M or T repeat the last one and
+  // are not stored, pixels past the chunk become zeros on the way to LDS.  A
+  // thread's elements all have the same pixel of the step.
+  static_assert(256 % KS == 0, "one pixel per thread and step");
+  const int kk = threadIdx.x % KS, row = threadIdx.x / KS;
+  constexpr int RS = 256 / KS;   // rows between a thread's elements
   cf rh[PER], ru[PER];
+  float rf = 0.0f;
   auto load = [&](int kb) {
+    const int k = min(kb + kk, N - 1);
+    rf = f[k];
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-      const int i = threadIdx.x + 256 * e;
-      const int mm = i / KS, kk = i % KS;
-      const int m = m0 + mm, k = kb + kk;
-      rh[e] = (m < M && k < kend) ? H[(size_t)m * N + k] : mk<cf>(0, 0);
-      ru[e] = (mm < T && k < kend) ? cscale(u[(size_t)mm * N + k], f[k]) : mk<cf>(0, 0);
+      rh[e] = H[(size_t)min(m0 + row + RS * e, M - 1) * N + k];
+      ru[e] = u[(size_t)min(row + RS * e, T - 1) * N + k];
     }
   };
   load(k0);
   for (int kb = k0; kb < kend; kb += KS) {
+    const bool ok = kb + kk < kend;
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-      const int i = threadIdx.x + 256 * e;
-      sh[i / KS][i % KS] = rh[e];
-      su[i / KS][i % KS] = ru[e];
+      const cf x = cscale(ru[e], rf);
+      sh[row + RS * e][kk] = ok ? rh[e] : mk<cf>(0, 0);
+      su[row + RS * e][kk] = ok ? x : mk<cf>(0, 0);
     }
     __syncthreads();
     if (kb + KS < kend) load(kb + KS);
@@ -184,9 +192,9 @@ __global__ void __launch_bounds__(256) k_project_mfma(const cf *H, const float *
     const int bt = wt * 32 + (lane & 31);
     const int kl = lane >> 5;
 #pragma unroll
-    for (int kk = 0; kk < KS; kk += 2) {
-      const cf a = sh[am][kk + kl];
-      const cf b = su[bt][kk + kl];
+    for (int q = 0; q < KS; q += 2) {
+      const cf a = sh[am][q + kl];
+      const cf b = su[bt][q + kl];
       acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc1, 0, 0, 0);
       acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc2, 0, 0, 0);
       acc3 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x + a.y, b.x + b.y, acc3, 0, 0, 0);
@@ -223,34 +231,29 @@ __global__ void __launch_bounds__(256) k_project_mfma16(const cf *H, const float
   const int kend = min(k0 + PJ_KCHUNK, N);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   floatx4 acc1 = {0}, acc2 = {0}, acc3 = {0};   // Gauss's three products, as in k_project_mfma
+  // raw loads ahead of the MFMAs, as in k_project_mfma
+  static_assert(256 % KS == 0, "one pixel per thread and step");
+  const int kk = threadIdx.x % KS, row = threadIdx.x / KS;
+  constexpr int RS = 256 / KS;
   cf rh[PH], ru[PU];
+  float rf = 0.0f;
   auto load = [&](int kb) {
+    const int k = min(kb + kk, N - 1);
+    rf = f[k];
 #pragma unroll
-    for (int e = 0; e < PH; ++e) {
-      const int i = threadIdx.x + 256 * e;
-      const int mm = i / KS, kk = i % KS;
-      const int m = m0 + mm, k = kb + kk;
-      rh[e] = (m < M && k < kend) ? H[(size_t)m * N + k] : mk<cf>(0, 0);
-    }
+    for (int e = 0; e < PH; ++e) rh[e] = H[(size_t)min(m0 + row + RS * e, M - 1) * N + k];
 #pragma unroll
-    for (int e = 0; e < PU; ++e) {
-      const int i = threadIdx.x + 256 * e;
-      const int tt = i / KS, kk = i % KS;
-      const int k = kb + kk;
-      ru[e] = (tt < T && k < kend) ? cscale(u[(size_t)tt * N + k], f[k]) : mk<cf>(0, 0);
-    }
+    for (int e = 0; e < PU; ++e) ru[e] = u[(size_t)min(row + RS * e, T - 1) * N + k];
   };
   load(k0);
   for (int kb = k0; kb < kend; kb += KS) {
+    const bool ok = kb + kk < kend;
 #pragma unroll
-    for (int e = 0; e < PH; ++e) {
-      const int i = threadIdx.x + 256 * e;
-      sh[i / KS][i % KS] = rh[e];
-    }
+    for (int e = 0; e < PH; ++e) sh[row + RS * e][kk] = ok ? rh[e] : mk<cf>(0, 0);
 #pragma unroll
     for (int e = 0; e < PU; ++e) {
-      const int i = threadIdx.x + 256 * e;
-      su[i / KS][i % KS] = ru[e];
+      const cf x = cscale(ru[e], rf);
+      su[row + RS * e][kk] = ok ? x : mk<cf>(0, 0);
     }
     __syncthreads();
     if (kb + KS < kend) load(kb + KS);
@@ -258,9 +261,9 @@ __global__ void __launch_bounds__(256) k_project_mfma16(const cf *H, const float
     const int bt = lane & 15;
     const int kl = lane >> 4;
 #pragma unroll
-    for (int kk = 0; kk < KS; kk += 4) {
-      const cf a = sh[am][kk + kl];
-      const cf b = su[bt][kk + kl];
+    for (int q = 0; q < KS; q += 4) {
+      const cf a = sh[am][q + kl];
+      const cf b = su[bt][q + kl];
       acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, acc1, 0, 0, 0);
       acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, acc2, 0, 0, 0);
       acc3 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x + a.y, b.x + b.y, acc3, 0, 0, 0);
