@@ -594,6 +594,11 @@ __global__ void __launch_bounds__(256) k_row_inv(ConvArgs<Rs, Rc> a) {
 // The intermediates never leave the CU: the three passes' n P^2 x 2 x 3 HBM
 // streams per field become one read and one write of n^2 P.  The spectrum is
 // read from its kz-major copy, so a batch's reads are contiguous in ky.
+// Padding of the plane's lines in LDS (see lds_index).
+template <typename Rc, int P> struct PlanePad {
+  static constexpr int PAD = sizeof(Rc) == 8 && P == 64 ? 3 : 1;
+  static constexpr int SPAN = PAD == 3 ? P + P / 8 : lds_span(P);
+};
 template <typename Rc, int P> struct PlaneCfg {
   static constexpr bool POW2 = (P & (P - 1)) == 0;
   static constexpr int V = 8;                       // points per thread and line
@@ -601,7 +606,7 @@ template <typename Rc, int P> struct PlaneCfg {
   static constexpr int THREADS = (sizeof(Rc) == 4 && P == 128) ? 1024 : 256;
   static constexpr int LINES = THREADS / NT;        // lines per round (y) and per batch (x)
   static constexpr int NROW = P / 2;                // rows of B: n <= P/2
-  static constexpr int SPAN = lds_span(P);
+  static constexpr int SPAN = PlanePad<Rc, P>::SPAN;
   static constexpr int BATCHES = P / LINES;        // batches of x-lines
   static constexpr bool LEAN = false;
   static constexpr size_t LDS_BYTES = ((size_t)NROW * SPAN + (size_t)P * LINES + P) * 2 * sizeof(Rc);
@@ -623,7 +628,7 @@ __device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const c
   using PL = Plan<P>;
   using FL = typename PL::fwd;
   using IL = typename PL::inv;
-  constexpr int NT = CF::NT, V = CF::V, SPAN = CF::SPAN, L = CF::LINES;
+  constexpr int NT = CF::NT, V = CF::V, SPAN = CF::SPAN, L = CF::LINES, PAD = PlanePad<Rc, P>::PAD;
   constexpr int R0 = FirstRadix<FL>::value;
   constexpr int RL = Stockham<Cc, P, NT, -1, 1, FL>::LAST;
   constexpr int R0I = FirstRadix<IL>::value;
@@ -668,11 +673,11 @@ __device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const c
           if (r < R0 / 2 && x < n && y < n) v[b * R0 + r] = ld(b * (R0 / 2) + r, x, y);
         }
       }
-      fft_regs<Cc, P, NT, -1, FL, decltype(twf), WaveSync, true, true, false>(v, tid, B + x * SPAN, 1, twf);
+      fft_regs<Cc, P, NT, -1, FL, decltype(twf), WaveSync, PAD, true, false>(v, tid, B + x * SPAN, 1, twf);
 #pragma unroll
       for (int b = 0; b < V / RL; ++b) {
 #pragma unroll
-        for (int r = 0; r < RL; ++r) B[x * SPAN + lds_index<true>(tid + b * NT + r * (P / RL))] = v[b * RL + r];
+        for (int r = 0; r < RL; ++r) B[x * SPAN + lds_index<PAD>(tid + b * NT + r * (P / RL))] = v[b * RL + r];
       }
     }
   }
@@ -693,7 +698,7 @@ __device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const c
 #pragma unroll
         for (int r = 0; r < R0; ++r) {
           const int x = tk + b * NT + r * (P / R0);
-          v[b * R0 + r] = (r < R0 / 2 && x < n) ? B[x * SPAN + lds_index<true>(ky)] : czero<Cc>();
+          v[b * R0 + r] = (r < R0 / 2 && x < n) ? B[x * SPAN + lds_index<PAD>(ky)] : czero<Cc>();
         }
       }
       fft_regs<Cc, P, NT, -1, FL, decltype(twf), BlockSync, false, true, false>(v, tk, E + lc, L, twf);
@@ -705,7 +710,7 @@ __device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const c
 #pragma unroll
         for (int r = 0; r < RLI / 2; ++r) {
           const int x = tk + b * NT + r * (P / RLI);
-          if (x < n) B[x * SPAN + lds_index<true>(ky)] = v[b * RLI + r];
+          if (x < n) B[x * SPAN + lds_index<PAD>(ky)] = v[b * RLI + r];
         }
       }
     }
@@ -720,9 +725,9 @@ __device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const c
 #pragma unroll
       for (int b = 0; b < V / R0I; ++b) {
 #pragma unroll
-        for (int r = 0; r < R0I; ++r) v[b * R0I + r] = B[x * SPAN + lds_index<true>(tid + b * NT + r * (P / R0I))];
+        for (int r = 0; r < R0I; ++r) v[b * R0I + r] = B[x * SPAN + lds_index<PAD>(tid + b * NT + r * (P / R0I))];
       }
-      fft_regs<Cc, P, NT, +1, IL, decltype(twi), WaveSync, true, false, true>(v, tid, B + x * SPAN, 1, twi);
+      fft_regs<Cc, P, NT, +1, IL, decltype(twi), WaveSync, PAD, false, true>(v, tid, B + x * SPAN, 1, twi);
 #pragma unroll
       for (int b = 0; b < V / RLI; ++b) {
 #pragma unroll
@@ -776,7 +781,7 @@ template <typename Rc, int P> struct SmallCfg {
   static constexpr int V = 8, NT = P / V;
   static constexpr int LINES = 64;                  // column lines at a time
   static constexpr int THREADS = LINES * NT;
-  static constexpr int NROW = P / 2, SPAN = lds_span(P), BATCHES = P / LINES;
+  static constexpr int NROW = P / 2, SPAN = PlanePad<Rc, P>::SPAN, BATCHES = P / LINES;
   static constexpr int OWN = P / (2 * NT);          // samples per thread
   static constexpr bool OK = P == 64;
   // spectrum values fetched batch by batch (the FP64 solver's registers do not hold them as well)
@@ -838,7 +843,7 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
   using CF = SmallCfg<R, P>;
   constexpr bool LEAN = CF::LEAN;   // FP64: x and rhat stay in memory
   constexpr int OWN = CF::OWN, NT = CF::NT;
-  __shared__ cd pool[CF::NROW * CF::SPAN + P * CF::LINES];
+  __shared__ cd pool[SmallCfg<double, P>::NROW * SmallCfg<double, P>::SPAN + P * CF::LINES];
   __shared__ C stw[P];
   __shared__ cd stwd[P];
   __shared__ double scratch[16 * NPART];
@@ -1017,7 +1022,8 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
   }
   if (a.tr && (st.flags & FLAG_TR)) {
     __syncthreads();   // the FP64 plane lies differently over the pool
-    residual(double(0), a.Gd, (const cd *)stwd, pool, pool + CF::NROW * CF::SPAN, (int)STG_TR);
+    residual(double(0), a.Gd, (const cd *)stwd, pool, pool + SmallCfg<double, P>::NROW * SmallCfg<double, P>::SPAN,
+             (int)STG_TR);
   }
   if (tid == 0) a.st[t] = st;
 }

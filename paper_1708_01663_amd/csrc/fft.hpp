@@ -366,9 +366,11 @@ struct WaveSync {
 // P then occupies lds_span(P) elements.  PAD 2: one element of padding after
 // every 16 (P + P/16 elements; power-of-two P): with ls = 8 interleaved
 // columns, the first pass's writes of rows 8 tid + r by the eight row offsets
-// of a wave would otherwise share 16 banks.
+// of a wave would otherwise share 16 banks.  PAD 3: one element after every 8
+// (P + P/8; P = 64 as 8 x 8 only): transforms of 16-byte elements held
+// contiguously by eight threads, whose first writes are 8 elements apart.
 template <int PAD> __device__ __forceinline__ int lds_index(int i) {
-  return PAD == 1 ? i + (i >> 5) : (PAD == 2 ? i + (i >> 4) : i);
+  return PAD == 1 ? i + (i >> 5) : (PAD == 2 ? i + (i >> 4) : (PAD == 3 ? i + (i >> 3) : i));
 }
 __host__ __device__ constexpr int lds_span(int P) { return P + P / 32; }
 // With PAD 2, lds_index(i + d) = lds_index(i) + pad_step<2>(d) whenever
@@ -379,7 +381,7 @@ __host__ __device__ constexpr int lds_span(int P) { return P + P / 32; }
 // power-of-two lengths a thread forms one padded index per butterfly and the
 // rest are compile-time offsets.
 template <int PAD> __host__ __device__ constexpr int pad_step(int d) {
-  return PAD == 1 ? d + d / 32 : (PAD == 2 ? d + d / 16 : d);
+  return PAD == 1 ? d + d / 32 : (PAD == 2 ? d + d / 16 : (PAD == 3 ? d + d / 8 : d));
 }
 
 // PI: the input is zero from P/2 on (prune the first pass); PO: only outputs
@@ -416,6 +418,7 @@ struct Stockham<C, P, NT, DIR, Ns, RadixList<R, R2, Rest...>, SY, PAD, PI, PO> {
       const int k = j % Ns;
       const int base = (j / Ns) * Ns * R + k;
       static_assert(PAD != 2 || (P & (P - 1)) == 0, "PAD 2 needs a power-of-two length");
+      static_assert(PAD != 3 || (P == 64 && R == 8 && R2 == 8), "PAD 3 is for 8 x 8");
       if constexpr (PAD != 0 && (P & (P - 1)) == 0) {
         C *const pb = lds + lds_index<PAD>(base) * ls;
 #pragma unroll
