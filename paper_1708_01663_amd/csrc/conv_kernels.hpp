@@ -614,16 +614,47 @@ template <typename Rc, int P> struct PlaneCfg {
                              P % LINES == 0 && BATCHES <= 2 && LDS_BYTES <= 160 * 1024;
 };
 
-// The convolution of one plane by the threads of a block (steps 1 to 3).
-// G is the plane's kernel spectrum [kx][ky].  A thread owns the samples
+// The values of a plane's kernel spectrum G[kx][ky] that a thread needs in
+// step 2: thread (lc, tk) of batch q takes (kx, ky) with ky = q L + lc and kx
+// in the forward transform's output layout.  Held for every batch, and kept
+// from one plane to the next where a block convolves several with one G; with
+// CF::LEAN one batch at a time, for fewer registers.
+template <typename CF, typename Rc, int P, bool CONJ> struct PlaneSpectrum {
+  using Cc = cplx_t<Rc>;
+  static constexpr int NB = CF::BATCHES, V = CF::V, NT = CF::NT;
+  static constexpr int RL = Stockham<Cc, P, NT, -1, 1, typename Plan<P>::fwd>::LAST;
+  const Cc *G;
+  Cc v[CF::LEAN ? 1 : NB][V];
+  __device__ __forceinline__ void load(int slot, int q) {
+    const int lc = threadIdx.x % CF::LINES, tk = threadIdx.x / CF::LINES;
+#pragma unroll
+    for (int b = 0; b < V / RL; ++b) {
+#pragma unroll
+      for (int r = 0; r < RL; ++r) {
+        Cc gg = G[(size_t)(tk + b * NT + r * (P / RL)) * P + q * CF::LINES + lc];
+        if constexpr (CONJ) gg.y = -gg.y;
+        v[slot][b * RL + r] = gg;
+      }
+    }
+  }
+  __device__ __forceinline__ explicit PlaneSpectrum(const Cc *g) : G(g) {
+    if constexpr (!CF::LEAN) {
+#pragma unroll
+      for (int q = 0; q < NB; ++q) load(q, q);
+    }
+  }
+};
+
+// The convolution of one plane by the threads of a block (steps 1 to 3) with
+// the kernel spectrum g.  A thread owns the samples
 // (x, y(i)), i < P / (2 NT), of the input and of the output alike:
 // ld(i, x, y) returns the input, st(i, x, y, v) takes the output; neither is
 // called outside the n x n samples.  stw is the LDS copy of the twiddles.
 // Ends without a barrier: the next use of B is by the same waves' rows, and
 // that of E comes after a barrier.
 template <typename CF, typename Rc, int P, bool CONJ, typename Ld, typename St>
-__device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const cplx_t<Rc> *stw, const cplx_t<Rc> *G,
-                                           const int n, Ld &&ld, St &&st) {
+__device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const cplx_t<Rc> *stw,
+                                           PlaneSpectrum<CF, Rc, P, CONJ> &g, const int n, Ld &&ld, St &&st) {
   using Cc = cplx_t<Rc>;
   using PL = Plan<P>;
   using FL = typename PL::fwd;
@@ -636,28 +667,6 @@ __device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const c
   static_assert(CF::OK, "plane kernel configuration");
   static_assert(R0I == RL, "inverse must start with the forward's last radix");
   static_assert(R0 % 2 == 0 && R0 == RLI, "the first and last radix are pruned, and their samples the same");
-  // the spectrum values of every batch of step 2, requested first so that
-  // they arrive during step 1: thread (lc, tk) of batch q needs (kx, ky) with
-  // ky = q L + lc and kx in the forward transform's output layout
-  // (LEAN: each batch's when it begins, for fewer registers)
-  constexpr int NB = CF::BATCHES;
-  Cc g[CF::LEAN ? 1 : NB][V];
-  auto load_g = [&](Cc (&gq)[V], int q) __attribute__((always_inline)) {
-    const int lc = threadIdx.x % L, tk = threadIdx.x / L;
-#pragma unroll
-    for (int b = 0; b < V / RL; ++b) {
-#pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        Cc gg = G[(size_t)(tk + b * NT + r * (P / RL)) * P + q * L + lc];
-        if constexpr (CONJ) gg.y = -gg.y;
-        gq[b * RL + r] = gg;
-      }
-    }
-  };
-  if constexpr (!CF::LEAN) {
-#pragma unroll
-    for (int q = 0; q < NB; ++q) load_g(g[q], q);
-  }
   // 1. y-forward; line x = threadIdx.x / NT (rows x >= n transform zeros)
   {
     const int x = threadIdx.x / NT, tid = threadIdx.x % NT;
@@ -688,10 +697,10 @@ __device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const c
     const TwTable<Cc, P, NT, -1, FL> twf{stw, tk};
     const TwTable<Cc, P, NT, +1, IL> twi{stw, tk};
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
+    for (int q = 0; q < CF::BATCHES; ++q) {
       const int ky = q * L + lc;
-      if constexpr (CF::LEAN) load_g(g[0], q);
-      const Cc (&gq)[V] = g[CF::LEAN ? 0 : q];
+      if constexpr (CF::LEAN) g.load(0, q);
+      const Cc (&gq)[V] = g.v[CF::LEAN ? 0 : q];
       Cc v[V];
 #pragma unroll
       for (int b = 0; b < V / R0; ++b) {
@@ -740,27 +749,61 @@ __device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const c
   }
 }
 
+// A block convolves the plane kz of a.pf fields one after the other: the
+// spectrum (four times a field's samples in bytes at n = P/2) is read once for
+// them, and a field's samples are requested while the one before is
+// transformed.  Operator at 64^3 x 16 in FP32, one block a CU: 178 us with one
+// field a block, 166 with 2, 154 with 4, 147 with 8 (256 blocks); the FP64
+// planes of 243 fields at 32^3: 199 us a launch with one, 183 with 4.
 template <typename Rs, typename Rc, int P, bool CONJ, bool MASK>
 __global__ void __launch_bounds__((PlaneCfg<Rc, P>::THREADS)) k_plane(ConvArgs<Rs, Rc> a) {
   using Cc = cplx_t<Rc>;
   using CF = PlaneCfg<Rc, P>;
-  const int kz = blockIdx.x, t = blockIdx.y;
-  if constexpr (MASK) {
-    if (!(a.st[t].flags & a.flag)) return;
-  }
-  if (a.fmask && !a.fmask[t]) return;
+  constexpr int NT = CF::NT, OWN = P / (2 * NT);
+  constexpr int R0 = FirstRadix<typename Plan<P>::fwd>::value;
+  const int kz = blockIdx.x, n = a.n;
+  // a field takes part unless its system is masked out
+  auto runs = [&](int t) {
+    if constexpr (MASK) {
+      if (!(a.st[t].flags & a.flag)) return false;
+    }
+    return !(a.fmask && !a.fmask[t]);
+  };
+  const int t1 = min(((int)blockIdx.y + 1) * a.pf, a.T);
+  int t = blockIdx.y * a.pf;
+  while (t < t1 && !runs(t)) ++t;
+  if (t == t1) return;
   __shared__ Cc B[CF::NROW * CF::SPAN];
   __shared__ Cc E[P * CF::LINES];
   __shared__ Cc stw[P];
   for (int i = threadIdx.x; i < P; i += CF::THREADS) stw[i] = a.tw[i];
+  const size_t nn = (size_t)n * n;
+  const int x = threadIdx.x / NT, tk = threadIdx.x % NT;
+  Cc next[OWN];
+  auto request = [&](int f) {
+    const Cc *in = a.cin + ((size_t)f * P + kz) * nn;
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+      const int y = tk + (i / (R0 / 2)) * NT + (i % (R0 / 2)) * (P / R0);
+      if (x < n && y < n) next[i] = in[x * n + y];
+    }
+  };
+  request(t);
+  PlaneSpectrum<CF, Rc, P, CONJ> g(a.Gpm + (size_t)kz * P * P);
   __syncthreads();
-  const int n = a.n;
-  const size_t plane = ((size_t)t * P + kz) * (size_t)n * n;
-  const Cc *in = a.cin + plane;
-  Cc *out = a.cout + plane;
-  plane_conv<CF, Rc, P, CONJ>(
-      B, E, stw, a.Gpm + (size_t)kz * P * P, n, [&](int, int x, int y) { return in[(size_t)x * n + y]; },
-      [&](int, int x, int y, Cc v) { out[(size_t)x * n + y] = v; });
+  while (t < t1) {
+    Cc cur[OWN];
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) cur[i] = next[i];
+    int u = t + 1;
+    while (u < t1 && !runs(u)) ++u;
+    if (u < t1) request(u);
+    Cc *out = a.cout + ((size_t)t * P + kz) * nn;
+    plane_conv<CF, Rc, P, CONJ>(
+        B, E, stw, g, n, [&](int i, int, int) { return cur[i]; },
+        [&](int, int xx, int y, Cc v) { out[xx * n + y] = v; });
+    t = u;
+  }
 }
 
 // ---------------------------------------------------------------- small 2D grids
@@ -805,8 +848,9 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_conv_small(ConvAr
   const R *f = a.frow ? a.frow[t] : a.f;
   const size_t base = (size_t)t * a.N;
   const R scale = static_cast<R>(a.scale);
+  PlaneSpectrum<CF, R, P, ADJ> g(a.Ghat);
   plane_conv<CF, R, P, ADJ>(
-      B, E, stw, a.Ghat, n,
+      B, E, stw, g, n,
       [&](int, int x, int y) {
         const int q = x * n + y;
         const C v = a.x[base + q];
@@ -905,14 +949,13 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
     __syncthreads();
   };
   // r = b - A x in precision Rc, its products, and the scalar step
-  auto residual = [&](auto one, const auto *G, const auto *tw, auto *Bc, auto *Ec,
-                      int stage) __attribute__((always_inline)) {
+  auto residual = [&](auto one, auto &g, const auto *tw, auto *Bc, auto *Ec, int stage) __attribute__((always_inline)) {
     using Rc = decltype(one);
     using Cc = cplx_t<Rc>;
     const bool restart = st.restart != 0;
     double acc[4] = {};
     plane_conv<SmallCfg<Rc, P>, Rc, P, ADJ>(
-        Bc, Ec, tw, G, n,
+        Bc, Ec, tw, g, n,
         [&](int i, int, int) __attribute__((always_inline)) {
           const Cc xv = ccast<Cc>(x_get(i));
           return ADJ ? xv : cscale(xv, static_cast<Rc>(f[i]));
@@ -934,7 +977,8 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
         });
     step(acc, stage);
   };
-  if (a.start >= 0) residual(R(0), a.G, (const C *)stw, B, E, (int)STG_TR0);
+  PlaneSpectrum<CF, R, P, ADJ> g(a.G);
+  if (a.start >= 0) residual(R(0), g, (const C *)stw, B, E, (int)STG_TR0);
   for (int it = 0; it < a.count; ++it) {
     if (!(st.flags & FLAG_ITER)) break;
     const C om = ccast<C>(st.omega), be = ccast<C>(st.beta);
@@ -958,7 +1002,7 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
     {
       double acc[2] = {};
       plane_conv<CF, R, P, ADJ>(
-          B, E, stw, a.G, n, [&](int i, int, int) __attribute__((always_inline)) { return ADJ ? p[i] : cscale(p[i], f[i]); },
+          B, E, stw, g, n, [&](int i, int, int) __attribute__((always_inline)) { return ADJ ? p[i] : cscale(p[i], f[i]); },
           [&](int i, int, int, C cv) __attribute__((always_inline)) {
             cv = cscale(cv, scale);
             if constexpr (ADJ) cv = cscale(cv, f[i]);
@@ -982,7 +1026,7 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
     {
       double acc[8] = {};
       plane_conv<CF, R, P, ADJ>(
-          B, E, stw, a.G, n, [&](int i, int, int) __attribute__((always_inline)) { return ADJ ? s[i] : cscale(s[i], f[i]); },
+          B, E, stw, g, n, [&](int i, int, int) __attribute__((always_inline)) { return ADJ ? s[i] : cscale(s[i], f[i]); },
           [&](int i, int, int, C cv) __attribute__((always_inline)) {
             cv = cscale(cv, scale);
             if constexpr (ADJ) cv = cscale(cv, f[i]);
@@ -1022,7 +1066,8 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
   }
   if (a.tr && (st.flags & FLAG_TR)) {
     __syncthreads();   // the FP64 plane lies differently over the pool
-    residual(double(0), a.Gd, (const cd *)stwd, pool, pool + SmallCfg<double, P>::NROW * SmallCfg<double, P>::SPAN,
+    PlaneSpectrum<SmallCfg<double, P>, double, P, ADJ> gd(a.Gd);
+    residual(double(0), gd, (const cd *)stwd, pool, pool + SmallCfg<double, P>::NROW * SmallCfg<double, P>::SPAN,
              (int)STG_TR);
   }
   if (tid == 0) a.st[t] = st;
@@ -1036,6 +1081,19 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
 template <int P> constexpr bool row_exact_ok() { return (P & (P - 1)) == 0; }
 template <int P> static bool row_exact(const Ctx &c, int rows) {
   return row_exact_ok<P>() && 2 * c.n == P && rows % RowCfg<P>::ROWS == 0;
+}
+// Fields per block of k_plane: the count whose blocks, in whole rounds of what
+// 256 CUs hold at once, take the least time; a block's own start counts as
+// half a field.
+template <typename Rc, int P> static int plane_fields(int T) {
+  constexpr int slots = 256 * (int)(160 * 1024 / PlaneCfg<Rc, P>::LDS_BYTES);
+  int best = 1;
+  long long least = 0;
+  for (int f = 1; f <= 16 && f <= T; ++f) {
+    const long long rounds = ((long long)P * ((T + f - 1) / f) + slots - 1) / slots, cost = rounds * (2 * f + 1);
+    if (f == 1 || cost < least) best = f, least = cost;
+  }
+  return best;
 }
 template <typename Rc> static const cplx_t<Rc> *plane_table(const Ctx &c) {
   if constexpr (sizeof(Rc) == 8) return c.precision == 1 ? (const cd *)c.Gpm : c.Gpm_d;
@@ -1186,7 +1244,8 @@ int launch_conv_p(Ctx &c, ConvArgs<Rs, Rc> &a, bool adjoint) {
     if (c.dim == 3 && a.Gpm) {
       rows(std::true_type{}, false);
       a.cin = a.X1, a.cout = a.X2;
-      const dim3 gp(P, c.T), bp(PlaneCfg<Rc, P>::THREADS);
+      a.pf = plane_fields<Rc, P>(c.T);
+      const dim3 gp(P, (c.T + a.pf - 1) / a.pf), bp(PlaneCfg<Rc, P>::THREADS);
       if (adjoint)
         hipLaunchKernelGGL((k_plane<Rs, Rc, P, true, MASKED>), gp, bp, 0, c.stream, a);
       else

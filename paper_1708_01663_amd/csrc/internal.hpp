@@ -84,6 +84,7 @@ template <typename Rs, typename Rc> struct ConvArgs {
   const Cc *Ghat;         // [P][P]
   const Cc *tw;           // [P]
   const Cc *Gpm;          // 3D plane path: the kernel spectrum kz-major, [kz][kx][ky]
+  int pf;                 // 3D plane path: fields per block
 };
 
 // Arguments of the kernel that runs whole BiCGSTAB iterations of a small 2D
