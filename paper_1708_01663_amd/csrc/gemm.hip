@@ -7,9 +7,9 @@
 // The projection contracts over the N pixels (K = N, large) into a small
 // M x T output, so it is split over K: each block produces a partial tile,
 // and a second kernel sums the partials in FP64 in a fixed order.  The FP32
-// path runs on the matrix cores (v_mfma_f32_32x32x2_f32) as a real GEMM on
-// the interleaved complex operands, with Gauss's three real products per
-// complex product (four without); the FP64 path on v_mfma_f64_16x16x4_f64.
+// path runs on the BF16 matrix units with its operands split in three parts,
+// or for few transmitters on v_mfma_f32_16x16x4_f32; the FP64 path on
+// v_mfma_f64_16x16x4_f64.
 #include <type_traits>
 
 #include "internal.hpp"
@@ -134,70 +134,161 @@ static void launch_project_f64(Ctx &c, const R *f, const cplx_t<R> *u, cd *part,
   go(I1{}, I1{});
 }
 
-// ---------------------------------------------------------------- MFMA projection (FP32)
-// Real GEMM view: for a receiver row m and a transmitter column t,
-//   Re y = sum_q Hr*Xr - Hi*Xi,  Im y = sum_q Hr*Xi + Hi*Xr,   X = f u.
-// v_mfma_f32_32x32x2f32 multiplies a 32x2 A block by a 2x32 B block: lane l
-// supplies A[l%32][l/32] and B[l/32][l%32] and holds C[8*(r/4) + 4*(l/32) + r%4][l%32]
-// in accumulator register r.  A block of 4 waves covers 64 receivers x 64
-// transmitters (one 32x32 quadrant per wave) for one K chunk.
+// ---------------------------------------------------------------- FP32 on the BF16 matrix units
+// Every FP32 operand is split into three BF16 parts, x = h + m + l (h and m the
+// nearest BF16 of what is left, with an exact remainder), and a product takes the
+// six part products h h, h m, m h, h l, m m and l h; what is dropped is below
+// 2^-24 of it.  v_mfma_f32_32x32x16_bf16 has sixteen times the rate of
+// v_mfma_f32_32x32x2_f32, so the 24 part products of a complex product take half
+// the matrix time of the three FP32 products of Gauss's form, and avoid the
+// cancellation in it.  RMS error against FP64 at 256^2 x 60 x 360 on random
+// operands, relative: projection 5.7e-7 in Gauss's form, 2.0e-7 here;
+// back-projection 4.9e-7 and 1.4e-7; at no size, scale (1e-30 to 1e20) or spread
+// of magnitudes measured was it larger.  With all six products in one sum the
+// projection's was (6.0e-7): only h h goes into the long sum.  An output reached
+// by a non-finite operand is NaN.
+// Lane l supplies A[l%32][8(l/32)..+8] and B[8(l/32)..+8][l%32] and holds
+// C[8(r/4) + 4(l/32) + r%4][l%32] in accumulator register r.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+constexpr int BS_PARTS = 3;
 
-template <int KS>
-__global__ void __launch_bounds__(256) k_project_mfma(const cf *H, const float *f, const cf *u, cd *part, int M,
-                                                      int N, int T) {
-  constexpr int PER = 64 * KS / 256;   // tile elements per thread and operand
-  __shared__ cf sh[64][KS + 1];
-  __shared__ cf su[64][KS + 1];
+// The three BF16 parts of two values, packed in one dword each.
+__device__ __forceinline__ void bf16_split(float a, float b, unsigned (&part)[BS_PARTS]) {
+  constexpr float MAXB = 3.38953139e38f;   // largest BF16: the nearest one of a larger FP32 value is infinite
+  float x[2] = {a, b};
+#pragma unroll
+  for (int k = 0; k < BS_PARTS; ++k) {
+    floatx2 v = {x[0], x[1]};
+    if (k == 0) v = floatx2{__builtin_amdgcn_fmed3f(a, -MAXB, MAXB), __builtin_amdgcn_fmed3f(b, -MAXB, MAXB)};
+    part[k] = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+    if (k + 1 < BS_PARTS) {
+      x[0] -= __builtin_bit_cast(float, part[k] << 16);
+      x[1] -= __builtin_bit_cast(float, part[k] & 0xffff0000u);
+    }
+  }
+}
+// big + small += a b over the parts: only h h goes into big, so that a long sum
+// rounds once per 16 terms at its own size instead of six times.
+__device__ __forceinline__ void bf16_mfma6(const bf16x8 (&a)[BS_PARTS], const bf16x8 (&b)[BS_PARTS], floatx16 &big,
+                                           floatx16 &small) {
+#pragma unroll
+  for (int s = BS_PARTS - 1; s >= 1; --s)
+#pragma unroll
+    for (int i = 0; i <= s; ++i) small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[s - i], small, 0, 0, 0);
+  big = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], big, 0, 0, 0);
+}
+__device__ __forceinline__ bf16x8 bf16_neg(bf16x8 x) {
+  typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(bf16x8, __builtin_bit_cast(uintx4, x) ^ 0x80008000u);
+}
+// Two consecutive complex values, 8-byte aligned.
+struct __attribute__((packed, aligned(8))) cf2 {
+  cf v[2];
+};
+
+// Projection: a block of 4 waves covers 64 receivers x 64 transmitters (one
+// 32x32 quadrant per wave) for one K chunk, 32 pixels a step.  The next step's
+// H, u and f are loaded into registers while the current step runs on the
+// matrix cores; they are multiplied and split on the way to LDS, where a row
+// holds its six parts (re h m l, im h m l) of 32 pixels.  Rows past M or T repeat
+// the last one and are not stored, pixels past the chunk are zeros.  Staging
+// (splits, LDS) and the matrix cores take about 30 us each of the 89 at
+// 256^2 x 60 x 360 (105 on the FP32 units): latency between barriers bounds it, so
+// three blocks fit a CU; with two (95 us) the 768 blocks run one and a half
+// rounds, and two LDS buffers of 16 pixels take 99.
+constexpr int PJ_OFF32_N = 1 << 26;
+constexpr int PJ_KS = 32, PJ_ROW = 2 * BS_PARTS * PJ_KS + 8;   // BF16 elements per LDS row
+template <typename OFF>   // holds 64 N
+__global__ void __launch_bounds__(256, 3) k_project_bf16(const cf *H, const float *f, const cf *u, cd *part, int M,
+                                                         int N, int T) {
+  constexpr int PER = 64 * PJ_KS / 2 / 256;   // pixel pairs per thread and operand
+  __shared__ __attribute__((aligned(16))) unsigned short sh[64][PJ_ROW], su[64][PJ_ROW];
   const int m0 = blockIdx.x * 64, kc = blockIdx.z;
   const int k0 = kc * PJ_KCHUNK;
   const int kend = min(k0 + PJ_KCHUNK, N);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wm = wave & 1, wt = wave >> 1;
-  // three real products per complex one (Gauss): P1 = Hr Xr, P2 = Hi Xi,
-  // P3 = (Hr + Hi)(Xr + Xi); Re = P1 - P2, Im = P3 - P1 - P2
-  floatx16 acc1 = {0}, acc2 = {0}, acc3 = {0};
-  // the next step's H, u and f elements are loaded into registers while the
-  // current step runs on the matrix cores, without branches or arithmetic
-  // (forming f u here would wait for the loads before the MFMAs: 137 instead
-  // of 105 us at 360 x 65536 x 60); rows past M or T repeat the last one and
-  // are not stored, pixels past the chunk become zeros on the way to LDS.  A
-  // thread's elements all have the same pixel of the step.
-  static_assert(256 % KS == 0, "one pixel per thread and step");
-  const int kk = threadIdx.x % KS, row = threadIdx.x / KS;
-  constexpr int RS = 256 / KS;   // rows between a thread's elements
-  cf rh[PER], ru[PER];
-  float rf = 0.0f;
-  auto load = [&](int kb) {
-    const int k = min(kb + kk, N - 1);
-    rf = f[k];
+  floatx16 re = {0}, im = {0}, res = {0}, ims = {0};
+  const int pr = threadIdx.x % (PJ_KS / 2), row = threadIdx.x / (PJ_KS / 2);
+  constexpr int RS = 256 / (PJ_KS / 2);    // rows between a thread's elements
+  cf2 rh[PER], ru[PER];
+  float rf[2];
+  // elements from the block's first row
+  OFF oh[PER], ou[PER];
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      rh[e] = H[(size_t)min(m0 + row + RS * e, M - 1) * N + k];
-      ru[e] = u[(size_t)min(row + RS * e, T - 1) * N + k];
+  for (int e = 0; e < PER; ++e) {
+    oh[e] = (OFF)(min(m0 + row + RS * e, M - 1) - m0) * (OFF)N;
+    ou[e] = (OFF)min(row + RS * e, T - 1) * (OFF)N;
+  }
+  const cf *Hb = H + (size_t)m0 * N;
+  auto load = [&](int kb) {
+    const int k = kb + 2 * pr;
+    if (kb + PJ_KS <= N) {   // (uniform) whole pairs
+      rf[0] = f[k];
+      rf[1] = f[k + 1];
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        rh[e] = *reinterpret_cast<const cf2 *>(Hb + (oh[e] + k));
+        ru[e] = *reinterpret_cast<const cf2 *>(u + (ou[e] + k));
+      }
+    } else {
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        const int kd = min(k + d, N - 1);
+        rf[d] = f[kd];
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+          rh[e].v[d] = Hb[oh[e] + kd];
+          ru[e].v[d] = u[ou[e] + kd];
+        }
+      }
+    }
+  };
+  auto put = [&](unsigned short *dst, cf a, cf b) {
+    unsigned p[BS_PARTS], q[BS_PARTS];
+    bf16_split(a.x, b.x, p);
+    bf16_split(a.y, b.y, q);
+#pragma unroll
+    for (int k = 0; k < BS_PARTS; ++k) {
+      *reinterpret_cast<unsigned *>(dst + k * PJ_KS + 2 * pr) = p[k];
+      *reinterpret_cast<unsigned *>(dst + (BS_PARTS + k) * PJ_KS + 2 * pr) = q[k];
     }
   };
   load(k0);
-  for (int kb = k0; kb < kend; kb += KS) {
-    const bool ok = kb + kk < kend;
+  for (int kb = k0; kb < kend; kb += PJ_KS) {
+    const bool ok0 = kb + 2 * pr < kend, ok1 = kb + 2 * pr + 1 < kend;
+    const cf z = mk<cf>(0, 0);
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-      const cf x = cscale(ru[e], rf);
-      sh[row + RS * e][kk] = ok ? rh[e] : mk<cf>(0, 0);
-      su[row + RS * e][kk] = ok ? x : mk<cf>(0, 0);
+      const cf x0 = cscale(ru[e].v[0], rf[0]), x1 = cscale(ru[e].v[1], rf[1]);
+      put(sh[row + RS * e], ok0 ? rh[e].v[0] : z, ok1 ? rh[e].v[1] : z);
+      put(su[row + RS * e], ok0 ? x0 : z, ok1 ? x1 : z);
     }
     __syncthreads();
-    if (kb + KS < kend) load(kb + KS);
-    const int am = wm * 32 + (lane & 31);
-    const int bt = wt * 32 + (lane & 31);
-    const int kl = lane >> 5;
+    if (kb + PJ_KS < kend) load(kb + PJ_KS);
+    const unsigned short *ha = sh[wm * 32 + (lane & 31)] + 8 * (lane >> 5);
+    const unsigned short *xb = su[wt * 32 + (lane & 31)] + 8 * (lane >> 5);
 #pragma unroll
-    for (int q = 0; q < KS; q += 2) {
-      const cf a = sh[am][q + kl];
-      const cf b = su[bt][q + kl];
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc1, 0, 0, 0);
-      acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc2, 0, 0, 0);
-      acc3 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x + a.y, b.x + b.y, acc3, 0, 0, 0);
+    for (int q = 0; q < PJ_KS; q += 16) {
+      bf16x8 hr[BS_PARTS], hi[BS_PARTS], x[BS_PARTS];
+#pragma unroll
+      for (int k = 0; k < BS_PARTS; ++k) {
+        hr[k] = *reinterpret_cast<const bf16x8 *>(ha + k * PJ_KS + q);
+        hi[k] = *reinterpret_cast<const bf16x8 *>(ha + (BS_PARTS + k) * PJ_KS + q);
+        x[k] = *reinterpret_cast<const bf16x8 *>(xb + k * PJ_KS + q);
+      }
+      bf16_mfma6(hr, x, re, res);
+      bf16_mfma6(hi, x, im, ims);
+#pragma unroll
+      for (int k = 0; k < BS_PARTS; ++k) x[k] = *reinterpret_cast<const bf16x8 *>(xb + (BS_PARTS + k) * PJ_KS + q);
+      bf16_mfma6(hr, x, im, ims);
+#pragma unroll
+      for (int k = 0; k < BS_PARTS; ++k) x[k] = bf16_neg(x[k]);
+      bf16_mfma6(hi, x, re, res);
     }
     __syncthreads();
   }
@@ -206,16 +297,19 @@ __global__ void __launch_bounds__(256) k_project_mfma(const cf *H, const float *
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int m = m0 + wm * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-    const double p1 = acc1[r], p2 = acc2[r], p3 = acc3[r];
-    if (m < M) part[((size_t)kc * T + t) * M + m] = mk<cd>(p1 - p2, p3 - p1 - p2);
+    if (m < M) part[((size_t)kc * T + t) * M + m] = mk<cd>((double)re[r] + (double)res[r], (double)im[r] + (double)ims[r]);
   }
 }
 
+// ---------------------------------------------------------------- narrow FP32 projection
 // Narrow variant for at most 16 transmitters (one 16-wide transmitter tile),
 // on v_mfma_f32_16x16x4f32: lane l supplies A[l%16][l/16] and B[l/16][l%16]
 // and holds C[4*(l/16) + r][l%16] in accumulator register r.  Four waves own
 // 16 receivers each (64 per block) against the same 16 transmitters, so no
-// matrix-core work is spent on absent transmitters and H is still read once.
+// matrix-core work is spent on absent transmitters and H is still read once;
+// reading it bounds this shape, so the products are FP32's own, three per
+// complex one (Gauss): P1 = Hr Xr, P2 = Hi Xi, P3 = (Hr + Hi)(Xr + Xi); Re = P1 -
+// P2, Im = P3 - P1 - P2.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int PJ_NARROW_T = 16;   // transmitters of the narrow projection tiles
 
@@ -230,8 +324,8 @@ __global__ void __launch_bounds__(256) k_project_mfma16(const cf *H, const float
   const int k0 = kc * PJ_KCHUNK;
   const int kend = min(k0 + PJ_KCHUNK, N);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  floatx4 acc1 = {0}, acc2 = {0}, acc3 = {0};   // Gauss's three products, as in k_project_mfma
-  // raw loads ahead of the MFMAs, as in k_project_mfma
+  floatx4 acc1 = {0}, acc2 = {0}, acc3 = {0};   // Gauss's three products
+  // raw loads ahead of the MFMAs: forming f u here would wait for them
   static_assert(256 % KS == 0, "one pixel per thread and step");
   const int kk = threadIdx.x % KS, row = threadIdx.x / KS;
   constexpr int RS = 256 / KS;
@@ -354,8 +448,10 @@ int launch_project(Ctx &c, const R *f, const cplx_t<R> *u, const cplx_t<R> *y_me
                          c.T);
     } else if (c.T <= 64) {
       dim3 g((c.M + 63) / 64, 1, kchunks);
-      hipLaunchKernelGGL(k_project_mfma<32>, g, dim3(256), 0, c.stream, (const cf *)c.H, f, u, part, c.M, c.N,
-                         c.T);
+      // 32-bit row offsets below 2^26 pixels: 64-bit ones cost 20 spilled registers
+      // (90.4 against 89.2 us at 256^2 x 60 x 360)
+      hipLaunchKernelGGL(c.N < PJ_OFF32_N ? k_project_bf16<unsigned> : k_project_bf16<size_t>, g, dim3(256), 0,
+                         c.stream, (const cf *)c.H, f, u, part, c.M, c.N, c.T);
     } else {
       launch_project_f64<float>(c, f, u, part, kchunks);
     }
@@ -461,73 +557,131 @@ static void launch_backproject_f64(Ctx &c, const cd *w, cd *q, const double *f, 
 }
 
 // ---------------------------------------------------------------- MFMA back-projection (FP32)
-// Q[t][k] = sum_m W[t][m] conj(H[m][k]) as real GEMMs on v_mfma_f32_32x32x2f32:
-//   Re Q = sum Wr Hr + Wi Hi,  Im Q = sum Wi Hr - Wr Hi,
-// rows = transmitters (A operand: lane l supplies W[l%32][m + l/32]), columns =
-// pixels (B operand: H[m + l/32][l%32]).  A block of four waves owns 64
-// transmitters x 128 pixels; wave w holds transmitter half w%2 and pixel half
-// w/2 (two 32-pixel column blocks), so H is read from HBM exactly once per
-// 64 transmitters.  W and H are staged in LDS 16 receivers at a time.
+// Q[t][k] = sum_m W[t][m] conj(H[m][k]) on the BF16 matrix units in three parts
+// per operand (see above): rows = transmitters, columns = pixels.
+//   Re Q = sum Wr Hr + Wi Hi,  Im Q = sum Wi Hr - Wr Hi
+// A block of four waves owns 64 transmitters x 128 pixels; wave w holds
+// transmitter half w%2 and pixel half w/2 (two 32-pixel column blocks), so H is
+// read from HBM exactly once per 64 transmitters.  W and H are split and staged
+// in LDS 16 receivers at a time, W with the receivers contiguous, H as it lies
+// ([receiver][pixel]): its operands, eight receivers of a pixel, come through
+// the transposing LDS read.  81-85 us at 256^2 x 60 x 360 (94 on the FP32 units),
+// two blocks per CU: the second LDS buffer saves a barrier a step, and the turned
+// rows below seven eighths of the bank conflicts (88 us without).
 constexpr int BP_MS = 16, BP_PT = 128, BP_TT = 64;
+constexpr int BP_WROW = 2 * BS_PARTS * BP_MS + 16;   // BF16 elements per transmitter's LDS row
+// Pixel k of receiver m lies at bp_pos(m, k): rows turned by 32 elements (16
+// banks) each, so that the four rows of a transposing read miss each other's banks.
+__device__ __forceinline__ int bp_pos(int m, int k) { return (k + 32 * (m & 3)) & (BP_PT - 1); }
 
-__global__ void __launch_bounds__(256) k_backproject_mfma(const cf *H, const cf *w, cf *q, const float *f, cf *b,
+__global__ void __launch_bounds__(256, 2) k_backproject_bf16(const cf *H, const cf *w, cf *q, const float *f, cf *b,
                                                           int M, int N, int T) {
-  constexpr int PW = BP_TT * BP_MS / 256, PH = BP_MS * BP_PT / 256;
-  __shared__ cf sw[BP_TT][BP_MS + 1];
-  __shared__ cf shh[BP_MS][BP_PT + 1];
+  constexpr int PW = BP_TT * BP_MS / 2 / 256, PH = BP_MS * BP_PT / 2 / 256;   // pairs per thread
+  __shared__ __attribute__((aligned(16))) unsigned short sw2[2][BP_TT][BP_WROW];
+  __shared__ __attribute__((aligned(16))) unsigned short sh2[2][2 * BS_PARTS][BP_MS][BP_PT];
   const int k0 = blockIdx.x * BP_PT, t0 = blockIdx.y * BP_TT;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wt = wave & 1, wp = wave >> 1;
-  // Gauss's three products: P1 = Wr Hr, P2 = Wi Hi, P3 = (Wr + Wi)(Hr - Hi);
-  // Re = P1 + P2, Im = P3 - P1 + P2
-  floatx16 acc1[2] = {{0}, {0}}, acc2[2] = {{0}, {0}}, acc3[2] = {{0}, {0}};
-  // next step's W and H staged in registers during the current step's MFMAs
-  cf rw[PW], rh[PH];
+  floatx16 re[2] = {{0}, {0}}, im[2] = {{0}, {0}}, res[2] = {{0}, {0}}, ims[2] = {{0}, {0}};
+  // next step's W and H staged in registers during the current step's MFMAs;
+  // rows past T and receivers past M repeat the last one (the latter zeroed on
+  // the way to LDS), pixels past N are not stored
+  const int wr = threadIdx.x / (BP_MS / 2), wpair = threadIdx.x % (BP_MS / 2);
+  const int hr = threadIdx.x / (BP_PT / 2), hpair = threadIdx.x % (BP_PT / 2);
+  cf rw[PW][2];
+  cf2 rh[PH];
   auto load = [&](int m0) {
 #pragma unroll
     for (int e = 0; e < PW; ++e) {
-      const int i = threadIdx.x + 256 * e;
-      const int tt = i / BP_MS, mm = i % BP_MS;
-      const int t = t0 + tt, m = m0 + mm;
-      rw[e] = (t < T && m < M) ? w[(size_t)t * M + m] : mk<cf>(0, 0);
+      const size_t base = (size_t)min(t0 + wr + e * (512 / BP_MS), T - 1) * M;
+#pragma unroll
+      for (int d = 0; d < 2; ++d) rw[e][d] = w[base + min(m0 + 2 * wpair + d, M - 1)];
     }
 #pragma unroll
     for (int e = 0; e < PH; ++e) {
-      const int i = threadIdx.x + 256 * e;
-      const int mm = i / BP_PT, kk = i % BP_PT;
-      const int m = m0 + mm, k = k0 + kk;
-      rh[e] = (m < M && k < N) ? H[(size_t)m * N + k] : mk<cf>(0, 0);
+      const cf *row = H + (size_t)min(m0 + hr + e * (512 / BP_PT), M - 1) * N;
+      const int k = k0 + 2 * hpair;
+      if (k0 + BP_PT <= N) {   // (uniform)
+        rh[e] = *reinterpret_cast<const cf2 *>(row + k);
+      } else {
+        rh[e].v[0] = row[min(k, N - 1)];
+        rh[e].v[1] = row[min(k + 1, N - 1)];
+      }
+    }
+  };
+  auto store = [&](int m0, int buf) {
+    auto &sw = sw2[buf];
+    auto &sh = sh2[buf];
+    const cf z = mk<cf>(0, 0);
+    unsigned p[BS_PARTS], r[BS_PARTS];
+#pragma unroll
+    for (int e = 0; e < PW; ++e) {
+      const int m = m0 + 2 * wpair;
+      const cf a0 = m < M ? rw[e][0] : z, a1 = m + 1 < M ? rw[e][1] : z;
+      bf16_split(a0.x, a1.x, p);
+      bf16_split(a0.y, a1.y, r);
+      unsigned short *dst = sw[wr + e * (512 / BP_MS)] + 2 * wpair;
+#pragma unroll
+      for (int k = 0; k < BS_PARTS; ++k) {
+        *reinterpret_cast<unsigned *>(dst + k * BP_MS) = p[k];
+        *reinterpret_cast<unsigned *>(dst + (BS_PARTS + k) * BP_MS) = r[k];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < PH; ++e) {
+      const int mm = hr + e * (512 / BP_PT);
+      const bool ok = m0 + mm < M;
+      const cf h0 = ok ? rh[e].v[0] : z, h1 = ok ? rh[e].v[1] : z;
+      bf16_split(h0.x, h1.x, p);
+      bf16_split(h0.y, h1.y, r);
+#pragma unroll
+      for (int k = 0; k < BS_PARTS; ++k) {
+        *reinterpret_cast<unsigned *>(&sh[k][mm][bp_pos(mm, 2 * hpair)]) = p[k];
+        *reinterpret_cast<unsigned *>(&sh[BS_PARTS + k][mm][bp_pos(mm, 2 * hpair)]) = r[k];
+      }
     }
   };
   load(0);
-  for (int m0 = 0; m0 < M; m0 += BP_MS) {
+  store(0, 0);
+  if (BP_MS < M) load(BP_MS);
+  __syncthreads();
+  for (int m0 = 0, buf = 0; m0 < M; m0 += BP_MS, buf ^= 1) {
+    auto &sw = sw2[buf];
+    auto &sh = sh2[buf];
+    const unsigned short *wa = sw[wt * 32 + (lane & 31)] + 8 * (lane >> 5);
+    bf16x8 ar[BS_PARTS], ai[BS_PARTS], an[BS_PARTS];   // Wr, Wi, -Wr
 #pragma unroll
-    for (int e = 0; e < PW; ++e) {
-      const int i = threadIdx.x + 256 * e;
-      sw[i / BP_MS][i % BP_MS] = rw[e];
+    for (int k = 0; k < BS_PARTS; ++k) {
+      ar[k] = *reinterpret_cast<const bf16x8 *>(wa + k * BP_MS);
+      ai[k] = *reinterpret_cast<const bf16x8 *>(wa + (BS_PARTS + k) * BP_MS);
+      an[k] = bf16_neg(ar[k]);
     }
+    // lane l of the transposing read: four receivers of pixel l % 16 of its 16-lane group
+    const int trow = 8 * (lane >> 5) + ((lane & 15) >> 2), tcol = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 #pragma unroll
-    for (int e = 0; e < PH; ++e) {
-      const int i = threadIdx.x + 256 * e;
-      shh[i / BP_PT][i % BP_PT] = rh[e];
-    }
-    __syncthreads();
-    if (m0 + BP_MS < M) load(m0 + BP_MS);
-    const int ar = wt * 32 + (lane & 31);
-    const int kl = lane >> 5;
+    for (int j = 0; j < 2; ++j) {
+      bf16x8 br[BS_PARTS], bi[BS_PARTS];
 #pragma unroll
-    for (int mm = 0; mm < BP_MS; mm += 2) {
-      const cf a = sw[ar][mm + kl];
-      const float as = a.x + a.y;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const cf h = shh[mm + kl][wp * 64 + j * 32 + (lane & 31)];
-        acc1[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, h.x, acc1[j], 0, 0, 0);
-        acc2[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, h.y, acc2[j], 0, 0, 0);
-        acc3[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(as, h.x - h.y, acc3[j], 0, 0, 0);
+      for (int k = 0; k < 2 * BS_PARTS; ++k) {
+        typedef __attribute__((address_space(3))) shortx4 *lds4;
+        unsigned short *src = &sh[k][trow][bp_pos(trow, wp * 64 + j * 32 + tcol)];
+        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)src);
+        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(src + 4 * BP_PT));
+        const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        if (k < BS_PARTS) br[k] = v;
+        else bi[k - BS_PARTS] = v;
       }
+      bf16_mfma6(ar, br, re[j], res[j]);
+      bf16_mfma6(ai, bi, re[j], res[j]);
+      bf16_mfma6(ai, br, im[j], ims[j]);
+      bf16_mfma6(an, bi, im[j], ims[j]);
     }
-    __syncthreads();
+    // the other buffer was last read before the barrier that ended the previous step
+    if (m0 + BP_MS < M) {
+      store(m0 + BP_MS, buf ^ 1);
+      if (m0 + 2 * BP_MS < M) load(m0 + 2 * BP_MS);
+      __syncthreads();
+    }
   }
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -538,8 +692,7 @@ __global__ void __launch_bounds__(256) k_backproject_mfma(const cf *H, const cf 
     for (int r = 0; r < 16; ++r) {
       const int t = t0 + wt * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
       if (t >= T) continue;
-      const double p1 = acc1[j][r], p2 = acc2[j][r], p3 = acc3[j][r];
-      const cf val = mk<cf>((float)(p1 + p2), (float)(p3 - p1 + p2));
+      const cf val = mk<cf>(re[j][r] + res[j][r], im[j][r] + ims[j][r]);
       q[(size_t)t * N + k] = val;
       if (b) b[(size_t)t * N + k] = mk<cf>(val.x * fk, val.y * fk);
     }
@@ -561,7 +714,9 @@ __global__ void __launch_bounds__(256) k_backproject_mfma16(const cf *H, const c
   __shared__ cf shh[BP_MS][BP16_PT + 1];
   const int k0 = blockIdx.x * BP16_PT;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  floatx4 acc1 = {0}, acc2 = {0}, acc3 = {0};   // Gauss's three products, as in k_backproject_mfma
+  // Gauss's three products: P1 = Wr Hr, P2 = Wi Hi, P3 = (Wr + Wi)(Hr - Hi);
+  // Re = P1 + P2, Im = P3 - P1 + P2
+  floatx4 acc1 = {0}, acc2 = {0}, acc3 = {0};
   cf rw, rh[PH];
   auto load = [&](int m0) {
     {
@@ -623,7 +778,7 @@ int launch_backproject(Ctx &c, const cplx_t<R> *w, cplx_t<R> *q, const R *f, cpl
       return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
     }
     dim3 g((c.N + BP_PT - 1) / BP_PT, (c.T + BP_TT - 1) / BP_TT);
-    hipLaunchKernelGGL(k_backproject_mfma, g, dim3(256), 0, c.stream, (const cf *)c.H, w, q, f, b, c.M, c.N, c.T);
+    hipLaunchKernelGGL(k_backproject_bf16, g, dim3(256), 0, c.stream, (const cf *)c.H, w, q, f, b, c.M, c.N, c.T);
   } else {
     launch_backproject_f64(c, w, q, f, b);
   }

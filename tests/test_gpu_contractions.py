@@ -34,3 +34,59 @@ def test_contractions_match_fp64(prec, n, T, M):
     eps = 2.0 ** -53 if prec == "c128" else 2.0 ** -24
     assert rel(y, want_y) <= (16 * op.N ** 0.5 * eps if prec == "c128" else 4 * eps)
     assert rel(q, want_q) <= 16 * M ** 0.5 * eps
+
+
+# 17 to 64 transmitters in complex64, on three BF16 parts per operand: the first and last size, partial
+# tiles of 32 in T, of 64 in M and of 128 pixels, a pixel count below a step, an odd one and one past a
+# chunk; steps of 16 receivers with a remainder and a single one
+@pytest.mark.parametrize("n,T,M", [(3, 17, 1), (16, 32, 16), (23, 33, 33), (32, 64, 64), (61, 60, 130)])
+@pytest.mark.parametrize("spread", [0, 6])
+def test_split_contractions_match_fp64(n, T, M, spread):
+    print(f"split contractions {n} {T} {M} {spread}", flush=True)
+    op = Cisor(n, 0.1, plane_wave_dirs(T), ring(M, n * 0.1), precision="c64")
+    rng = np.random.default_rng(n + T)
+
+    def cplx(*s):
+        x = (rng.standard_normal(s) + 1j * rng.standard_normal(s)) * 10.0 ** rng.uniform(-spread, spread, s)
+        return torch.as_tensor(x).to(op.cdtype)
+
+    f = torch.as_tensor(rng.uniform(0, 1, op.N)).to(op.rdtype)
+    u, w = cplx(T, op.N), cplx(T, M)
+    H = op.H().cpu().to(torch.complex128)
+    y = op.project(f.cuda(), u.cuda()).cpu()
+    q = op.backproject(w.cuda()).cpu()
+    want_y = (u.to(torch.complex128) * f.double()) @ H.T
+    want_q = w.to(torch.complex128) @ H.conj()
+    rel = lambda a, b: float(torch.linalg.vector_norm(a.to(torch.complex128) - b) / torch.linalg.vector_norm(b))
+    # 64 sums of 16 products per chunk of 512 pixels (two per complex component), each rounded once in
+    # FP32, and FP64 over the chunks; the back-projection sums M products in FP32
+    eps = 2.0 ** -24
+    assert rel(y, want_y) <= 4 * 64 ** 0.5 * eps
+    assert rel(q, want_q) <= 16 * M ** 0.5 * eps
+
+
+def test_split_contractions_extremes():
+    """A non-finite operand reaches the outputs it enters and no others; finite values above the
+    largest BF16 stay finite."""
+    n, T, M = 23, 33, 33
+    op = Cisor(n, 0.1, plane_wave_dirs(T), ring(M, n * 0.1), precision="c64")
+    H = op.H().cpu().to(torch.complex128)
+    assert float(H.abs().max()) < 0.5
+    f = torch.ones(op.N, dtype=op.rdtype).cuda()
+    for bad in (float("nan"), float("inf"), float("-inf")):
+        u = torch.ones(T, op.N, dtype=op.cdtype)
+        w = torch.ones(T, M, dtype=op.cdtype)
+        u[32, op.N - 1] = bad
+        w[32, M - 1] = bad
+        y, q = op.project(f, u.cuda()).cpu(), op.backproject(w.cuda()).cpu()
+        for out in (y, q):
+            assert bool(torch.isfinite(torch.view_as_real(out[:32])).all())
+            assert not bool(torch.isfinite(torch.view_as_real(out[32])).any())
+    big = 3.4e38
+    w = torch.zeros(T, M, dtype=op.cdtype)
+    w[5, 7] = big
+    q = op.backproject(w.cuda()).cpu()
+    want = float(np.float32(big)) * H[7].conj()
+    # one product per output: the dropped parts and one rounding
+    assert float((q[5].to(torch.complex128) - want).abs().max()) <= 4 * 2.0 ** -24 * float(want.abs().max())
+    assert float(q[:5].abs().max()) == 0.0
