@@ -21,6 +21,14 @@ template <int P, bool PM> constexpr int row_lds() {
                                                                              : RowCfg<P>::ROWS * RowCfg<P>::SPAN;
 }
 
+// First-radix groups of a thread's elements whose operands, `bytes` a group, the
+// row kernels hold at once: as many as ROW_HOLD bytes take, a divisor of the groups.
+constexpr int ROW_HOLD = 384;
+template <int GROUPS> constexpr int row_batch(int bytes) {
+  int n = GROUPS;
+  while (n > 1 && (n * bytes > ROW_HOLD || GROUPS % n)) --n;
+  return n;
+}
 // PM: X1 is written plane-major, X1[t][k][row] (3D: the n^2 rows of one kz
 // together) instead of X1[t][row][k].  EXACT (2D, power-of-two P = 2n, rows a
 // multiple of the block's): every row is valid and column j + r P/R0 < n
@@ -61,43 +69,81 @@ __global__ void __launch_bounds__(256) k_row_fwd(ConvArgs<Rs, Rc> a) {
     pend = a.st[t].x_pending;
     bz = a.st[t].beta.x == 0.0 && a.st[t].beta.y == 0.0;
   }
+  // In two phases, batch by batch: every load of a batch is issued before its
+  // first store.  Element by element, a load would wait for the store before it
+  // (nothing tells the compiler that the vectors are distinct), a memory latency
+  // each: the p update took 10.7 us so and takes 8.0 at 125^2 x 25, 36.5 and 33.0
+  // at 256^2 x 60, where memory traffic bounds it
+  constexpr int RV = (R0 + 1) / 2;   // the column of a later r is at least P/2 >= n
+  constexpr int NLD = PRO == PRO_PUPD ? 5 : PRO == PRO_SUPD ? 3 : 1;
+  constexpr int BB = row_batch<V / R0>(RV * NLD * (int)sizeof(Cs));
   Cc v[V];
 #pragma unroll
-  for (int b = 0; b < V / R0; ++b) {
-    const int j = tid + b * NT;
+  for (int b0 = 0; b0 < V / R0; b0 += BB) {
+    Cs la[BB][RV], lb[BB][RV], lc[BB][RV], ld[BB][RV], le[BB][RV];
+    Rs lf[BB][RV];
+    // columns past n are read from the system's first element and not used
+    auto col_of = [&](int b, int r) { return tid + (b0 + b) * NT + r * (P / R0); };
+    auto ok = [&](int b, int r) { return EXACT ? r < R0 / 2 : vr && col_of(b, r) < a.n; };
+    auto at = [&](int b, int r) { return ok(b, r) ? rowoff + col_of(b, r) : (size_t)t * a.N; };
+    auto load = [&](Cs(&dst)[BB][RV], const Cs *src) {
 #pragma unroll
-    for (int r = 0; r < R0; ++r) {
-      const int col = j + r * (P / R0);
-      Cc val = czero<Cc>();
-      if (EXACT ? (r < R0 / 2) : (vr && col < a.n)) {
-        const size_t e = rowoff + col;
-        if constexpr (PRO == PRO_X) {
-          val = ccast<Cc>(a.x[e]);
-        } else if constexpr (PRO == PRO_PUPD) {
-          // x += alpha p + omega s (last iteration); p = r + beta (p - omega v),
-          // which is p = r when beta = 0: p and v are then not read, so a
-          // solve's first iteration needs no initial p and v
-          Cc pp = czero<Cc>();
-          if (pend || !bz) pp = ccast<Cc>(a.p[e]);
-          Cc rr;
-          if (fresh) {
-            rr = ccast<Cc>(a.r[e]);
-          } else {
-            const Cc ss = ccast<Cc>(a.s[e]);
-            rr = csub(ss, cmul(om, ccast<Cc>(a.tt[e])));
-            if (pend) a.xw[e] = ccast<Cs>(cadd(ccast<Cc>(a.xw[e]), cadd(cmul(al, pp), cmul(om, ss))));
-          }
-          val = bz ? rr : cadd(rr, cmul(be, csub(pp, cmul(om, ccast<Cc>(a.v[e])))));
-          a.p[e] = ccast<Cs>(val);
-        } else {
-          // s = r - alpha v (alpha of this iteration, omega of the last)
-          const Cc rr = fresh ? ccast<Cc>(a.r[e]) : csub(ccast<Cc>(a.s[e]), cmul(om, ccast<Cc>(a.tt[e])));
-          val = csub(rr, cmul(al, ccast<Cc>(a.v[e])));
-          a.s[e] = ccast<Cs>(val);
-        }
-        if constexpr (MULF) val = cscale(val, static_cast<Rc>(fr[(size_t)row * a.n + col]));
+      for (int b = 0; b < BB; ++b)
+#pragma unroll
+        for (int r = 0; r < RV; ++r) dst[b][r] = src[at(b, r)];
+    };
+    if constexpr (PRO == PRO_X) {
+      load(la, a.x);
+    } else {
+      if (PRO == PRO_SUPD || !bz) load(ld, a.v);
+      if (PRO == PRO_PUPD && (pend || !bz)) load(lb, a.p);
+      if (fresh) {
+        load(la, a.r);
+      } else {
+        load(la, a.s);
+        load(lc, a.tt);
+        if (PRO == PRO_PUPD && pend) load(le, a.xw);
       }
-      v[b * R0 + r] = val;
+    }
+    if constexpr (MULF) {
+#pragma unroll
+      for (int b = 0; b < BB; ++b)
+#pragma unroll
+        for (int r = 0; r < RV; ++r) lf[b][r] = fr[at(b, r) - (size_t)t * a.N];
+    }
+#pragma unroll
+    for (int b = 0; b < BB; ++b) {
+#pragma unroll
+      for (int r = 0; r < R0; ++r) {
+        Cc val = czero<Cc>();
+        if (r < RV && ok(b, r)) {
+          const size_t e = rowoff + col_of(b, r);
+          if constexpr (PRO == PRO_X) {
+            val = ccast<Cc>(la[b][r]);
+          } else if constexpr (PRO == PRO_PUPD) {
+            // x += alpha p + omega s (last iteration); p = r + beta (p - omega v),
+            // which is p = r when beta = 0: p and v are then not read, so a
+            // solve's first iteration needs no initial p and v
+            const Cc pp = pend || !bz ? ccast<Cc>(lb[b][r]) : czero<Cc>();
+            Cc rr = ccast<Cc>(la[b][r]);
+            if (!fresh) {
+              const Cc ss = rr;
+              rr = csub(ss, cmul(om, ccast<Cc>(lc[b][r])));
+              if (pend) a.xw[e] = ccast<Cs>(cadd(ccast<Cc>(le[b][r]), cadd(cmul(al, pp), cmul(om, ss))));
+            }
+            val = bz ? rr : cadd(rr, cmul(be, csub(pp, cmul(om, ccast<Cc>(ld[b][r])))));
+            a.p[e] = ccast<Cs>(val);
+          } else {
+            // s = r - alpha v (alpha of this iteration, omega of the last)
+            Cc rr = ccast<Cc>(la[b][r]);
+            if (!fresh) rr = csub(rr, cmul(om, ccast<Cc>(lc[b][r])));
+            val = csub(rr, cmul(al, ccast<Cc>(ld[b][r])));
+            a.s[e] = ccast<Cs>(val);
+          }
+          if constexpr (MULF) val = cscale(val, static_cast<Rc>(lf[b][r]));
+        }
+        v[(b0 + b) * R0 + r] = val;
+      }
     }
   }
   // the row is zero from column n <= P/2 on: the first pass is pruned
@@ -499,6 +545,37 @@ __global__ void __launch_bounds__(256) k_row_inv(ConvArgs<Rs, Rc> a) {
       for (int r = 0; r < R0; ++r) v[b * R0 + r] = vr ? in[j + r * (P / R0)] : czero<Cc>();
     }
   }
+  // The epilogue's operands, in two phases as in k_row_fwd; where they take few
+  // registers (FP32 vectors) they are loaded ahead of the transform, which hides
+  // their latency: with the products of t, 8.9 us before and 7.0 at 125^2 x 25,
+  // 24.8 and 22.8 at 256^2 x 60 (memory traffic)
+  constexpr int RV = (RL + 1) / 2;   // the column of a later r is at least P/2 >= n
+  constexpr int NLD = EPI == EPI_AX ? 1 : (EPI == EPI_G || EPI == EPI_GF) ? 0 : 2;
+  constexpr bool EARLY = sizeof(Cs) == 8;
+  constexpr int BB = EARLY ? V / RL : row_batch<V / RL>(RV * NLD * (int)sizeof(Cs) + 1);
+  Cs l1[BB][RV], l2[BB][RV];
+  Rs lf[BB][RV];
+  auto col_of = [&](int b, int r) { return tid + b * NT + r * (P / RL); };
+  auto ok = [&](int b, int r) { return EXACT ? r < RL / 2 : vr && col_of(b, r) < a.n; };
+  auto load = [&](int b0) {
+    // columns past n are read from the system's first element and not used
+    auto at = [&](int b, int r) { return ok(b0 + b, r) ? rowoff + col_of(b0 + b, r) : (size_t)t * a.N; };
+    const Cs *p1 = nullptr, *p2 = nullptr;
+    if constexpr (EPI == EPI_AX) p1 = a.x;
+    else if constexpr (EPI == EPI_V) p1 = a.p, p2 = a.rhat;
+    else if constexpr (EPI == EPI_T) p1 = a.s, p2 = a.rhat;
+    else if constexpr (EPI == EPI_TR) p1 = a.b, p2 = a.x;
+    else if constexpr (NLD == 2) p1 = a.u, p2 = a.q;
+#pragma unroll
+    for (int b = 0; b < BB; ++b)
+#pragma unroll
+      for (int r = 0; r < RV; ++r) {
+        if constexpr (NLD >= 1) l1[b][r] = p1[at(b, r)];
+        if constexpr (NLD >= 2) l2[b][r] = p2[at(b, r)];
+        if constexpr (MULF) lf[b][r] = fr[at(b, r) - (size_t)t * a.N];
+      }
+  };
+  if constexpr (EARLY) load(0);
   // only columns below n <= P/2 are kept: the last pass is pruned
   fft_regs<Cc, P, NT, +1, typename PL::inv, decltype(twi), BlockSync, true, false, true>(v, tid, lds + lr * SPAN, 1,
                                                                                        twi);
@@ -507,34 +584,34 @@ __global__ void __launch_bounds__(256) k_row_inv(ConvArgs<Rs, Rc> a) {
   if constexpr (EPI == EPI_TR) restart = a.st ? a.st[t].restart : 1;
   double acc[NA] = {};
 #pragma unroll
-  for (int b = 0; b < V / RL; ++b) {
-    const int j = tid + b * NT;
+  for (int b0 = 0; b0 < V / RL; b0 += BB) {
+    if constexpr (!EARLY) load(b0);
 #pragma unroll
-    for (int r = 0; r < RL; ++r) {
-      const int col = j + r * (P / RL);
-      if (EXACT ? (r >= RL / 2) : !(vr && col < a.n)) continue;
-      const size_t e = rowoff + col;
+    for (int br = 0; br < BB * RV; ++br) {
+      const int bi = br / RV, r = br % RV, b = b0 + bi;
+      if (!ok(b, r)) continue;
+      const size_t e = rowoff + col_of(b, r);
       Cc cv = cscale(v[b * RL + r], scale);
-      if constexpr (MULF) cv = cscale(cv, static_cast<Rc>(fr[(size_t)row * a.n + col]));
+      if constexpr (MULF) cv = cscale(cv, static_cast<Rc>(lf[bi][r]));
       if constexpr (EPI == EPI_AX) {
-        a.y[e] = ccast<Cs>(csub(ccast<Cc>(a.x[e]), cv));
+        a.y[e] = ccast<Cs>(csub(ccast<Cc>(l1[bi][r]), cv));
       } else if constexpr (EPI == EPI_G || EPI == EPI_GF) {
         a.y[e] = ccast<Cs>(cv);
       } else if constexpr (EPI == EPI_V) {
-        const Cs vv = ccast<Cs>(csub(ccast<Cc>(a.p[e]), cv));
+        const Cs vv = ccast<Cs>(csub(ccast<Cc>(l1[bi][r]), cv));
         a.y[e] = vv;
-        const cd h = ccast<cd>(a.rhat[e]);
+        const cd h = ccast<cd>(l2[bi][r]);
         const cd w = ccast<cd>(vv);
         acc[0] += h.x * w.x + h.y * w.y;
         acc[1] += h.x * w.y - h.y * w.x;
       } else if constexpr (EPI == EPI_T) {
         // t = A s; <t,s>, <t,t>, <s,s>, <rhat,s>, <rhat,t> (the residual
         // r = s - omega t is never formed: its dot products follow from these)
-        const Cs tt = ccast<Cs>(csub(ccast<Cc>(a.s[e]), cv));
+        const Cs tt = ccast<Cs>(csub(ccast<Cc>(l1[bi][r]), cv));
         a.y[e] = tt;
         const cd tv = ccast<cd>(tt);
-        const cd sv = ccast<cd>(a.s[e]);
-        const cd h = ccast<cd>(a.rhat[e]);
+        const cd sv = ccast<cd>(l1[bi][r]);
+        const cd h = ccast<cd>(l2[bi][r]);
         acc[0] += tv.x * sv.x + tv.y * sv.y;
         acc[1] += tv.x * sv.y - tv.y * sv.x;
         acc[2] += tv.x * tv.x + tv.y * tv.y;
@@ -545,8 +622,8 @@ __global__ void __launch_bounds__(256) k_row_inv(ConvArgs<Rs, Rc> a) {
         acc[7] += h.x * tv.y - h.y * tv.x;
       } else if constexpr (EPI == EPI_TR) {
         // r = b - A x = b - x + conv, evaluated in the compute precision
-        const Cc bb = ccast<Cc>(a.b[e]);
-        const Cc rr = cadd(csub(bb, ccast<Cc>(a.x[e])), cv);
+        const Cc bb = ccast<Cc>(l1[bi][r]);
+        const Cc rr = cadd(csub(bb, ccast<Cc>(l2[bi][r])), cv);
         const Cs rs = ccast<Cs>(rr);
         a.y[e] = rs;
         const cd rd = ccast<cd>(rr);
@@ -564,8 +641,8 @@ __global__ void __launch_bounds__(256) k_row_inv(ConvArgs<Rs, Rc> a) {
         const cd bd = ccast<cd>(bb);
         acc[3] += bd.x * bd.x + bd.y * bd.y;
       } else {  // EPI_GRAD: Re{conj(u) (q + G^H v)}
-        const Cc uu = ccast<Cc>(a.u[e]);
-        const Cc s = cadd(ccast<Cc>(a.q[e]), cv);
+        const Cc uu = ccast<Cc>(l1[bi][r]);
+        const Cc s = cadd(ccast<Cc>(l2[bi][r]), cv);
         a.gpart[e] = static_cast<Rs>(uu.x * s.x + uu.y * s.y);
       }
     }
