@@ -199,9 +199,10 @@ int launch_apply_A(Ctx &c, const R *f, const cplx_t<R> *x, cplx_t<R> *y, bool ad
 // One stage (1, 2 or 3) of the unmasked operator A or A^H.
 template <typename R>
 int launch_conv_stage(Ctx &c, const R *f, const cplx_t<R> *x, cplx_t<R> *y, int stage, bool adjoint);
-// y = G x or G^H x (no identity, no contrast).
+// y = G x or G^H x (no identity), or G (f x) where f is given (conj = false).
 template <typename R>
-int launch_apply_G(Ctx &c, const cplx_t<R> *x, cplx_t<R> *y, bool conj, const int *fmask = nullptr);
+int launch_apply_G(Ctx &c, const cplx_t<R> *x, cplx_t<R> *y, bool conj, const int *fmask = nullptr,
+                   const R *f = nullptr);
 // y_t = G (f u_in,t) for all transmitters (first-Born scattered fields).
 template <typename R>
 int launch_born_field(Ctx &c, const R *f, cplx_t<R> *y);

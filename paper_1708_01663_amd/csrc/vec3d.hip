@@ -127,8 +127,8 @@ __device__ __forceinline__ void write_partials(const FieldArgs &a, int t, double
   }
 }
 
-// Convolution input of the operator: f x (forward) or x + D x / k^2 (adjoint).
-template <bool ADJ>
+// Convolution input of the adjoint operator: x + D x / k^2 (the forward one's,
+// f x, is formed by the row transforms).
 __global__ void __launch_bounds__(VB) k_vpre(FieldArgs a) {
   const int t = blockIdx.y;
   if (skip_system(a, t)) return;
@@ -136,14 +136,10 @@ __global__ void __launch_bounds__(VB) k_vpre(FieldArgs a) {
   const cd *X = a.x + (size_t)t * L;
   cd *W = a.pre + (size_t)t * L;
   for (int e = blockIdx.x * VB + threadIdx.x; e < L; e += a.nbv * VB) {
-    if constexpr (ADJ) {
-      int c, cell, q[3];
-      split(a, e, c, cell, q);
-      const cd d = graddiv(X, a.n, a.N, c, q, cell);
-      W[e] = mk<cd>(X[e].x + a.c2 * d.x, X[e].y + a.c2 * d.y);
-    } else {
-      W[e] = cscale(X[e], a.f[cell_of(a, e)]);
-    }
+    int c, cell, q[3];
+    split(a, e, c, cell, q);
+    const cd d = graddiv(X, a.n, a.N, c, q, cell);
+    W[e] = mk<cd>(X[e].x + a.c2 * d.x, X[e].y + a.c2 * d.y);
   }
 }
 
@@ -192,8 +188,7 @@ __global__ void __launch_bounds__(VB) k_vpost(FieldArgs a) {
   if constexpr (DOT != DOT_NONE) write_partials<3>(a, t, acc);
 }
 
-// p = r + beta (p - omega v); forward operator input f p.
-template <bool FWD>
+// p = r + beta (p - omega v).
 __global__ void __launch_bounds__(VB) k_vpupd(FieldArgs a) {
   const int t = blockIdx.y;
   if (a.st[t].status != V_ITER) return;
@@ -204,12 +199,10 @@ __global__ void __launch_bounds__(VB) k_vpupd(FieldArgs a) {
     const size_t g = base + e;
     const cd pv = cadd(a.r[g], cmul(be, csub(a.p[g], cmul(om, a.v[g]))));
     a.p[g] = pv;
-    if constexpr (FWD) a.pre[g] = cscale(pv, a.f[cell_of(a, e)]);
   }
 }
 
-// s = r - alpha v and ||s||^2; forward operator input f s.
-template <bool FWD>
+// s = r - alpha v and ||s||^2.
 __global__ void __launch_bounds__(VB) k_vsupd(FieldArgs a) {
   const int t = blockIdx.y;
   if (a.st[t].status != V_ITER) return;
@@ -221,7 +214,6 @@ __global__ void __launch_bounds__(VB) k_vsupd(FieldArgs a) {
     const size_t g = base + e;
     const cd sv = csub(a.r[g], cmul(al, a.v[g]));
     a.s[g] = sv;
-    if constexpr (FWD) a.pre[g] = cscale(sv, a.f[cell_of(a, e)]);
     acc[0] += sv.x * sv.x + sv.y * sv.y;
   }
   write_partials<1>(a, t, acc);
@@ -455,14 +447,26 @@ __global__ void __launch_bounds__(64) k_vfield_mask(const VState *st, int need, 
 // With need != NO_MASK only the systems whose status is `need` are
 // transformed (the field kernels around it skip the others too, so their Y
 // is never read).
-int convolve(VecCtx &v, const cd *in, cd *out, bool adjoint, int need) {
+// With f the input is f times in: the row transforms multiply it on the way.
+int convolve(VecCtx &v, const cd *in, cd *out, bool adjoint, int need, const double *f = nullptr) {
   v.sc->stream = v.stream;
   const int *mask = nullptr;
   if (need != NO_MASK) {
     hipLaunchKernelGGL(k_vfield_mask, dim3((3 * v.T + 63) / 64), dim3(64), 0, v.stream, v.st, need, v.fmask, v.T);
     mask = v.fmask;
   }
-  return launch_apply_G<double>(*v.sc, in, out, adjoint, mask);
+  return launch_apply_G<double>(*v.sc, in, out, adjoint, mask, f);
+}
+
+// Y = G (f x) or G^H (x + grad div x / k^2).  Writing f x out with the updates of
+// p and s cost a stream each, at the rate of memory: at 32^3 x 81 the update of p
+// took 118 us with it and takes 92 without, that of s 82 and 60; the row
+// transforms take 62 with the product and 52 without.
+int convolve_input(VecCtx &v, const FieldArgs &a, bool adjoint) {
+  if (!adjoint) return convolve(v, a.x, v.ws[7], false, a.need, a.f);
+  hipLaunchKernelGGL(k_vpre, dim3(v.nbv, v.T), dim3(VB), 0, v.stream, a);
+  if (int rc = last_error()) return rc;
+  return convolve(v, a.pre, v.ws[7], true, a.need);
 }
 
 // out = A x (DOT_NONE), the residual b - A x (DOT_TR), ... for systems with status `need`.
@@ -470,10 +474,7 @@ template <int DOT>
 int operator_pass(VecCtx &v, FieldArgs a, const cd *x, cd *out, bool adjoint) {
   const dim3 grid(v.nbv, v.T);
   a.x = x;
-  if (adjoint) hipLaunchKernelGGL(k_vpre<true>, grid, dim3(VB), 0, v.stream, a);
-  else hipLaunchKernelGGL(k_vpre<false>, grid, dim3(VB), 0, v.stream, a);
-  if (int rc = last_error()) return rc;
-  if (int rc = convolve(v, a.pre, v.ws[7], adjoint, a.need)) return rc;
+  if (int rc = convolve_input(v, a, adjoint)) return rc;
   a.out = out;
   if (adjoint) hipLaunchKernelGGL((k_vpost<true, DOT>), grid, dim3(VB), 0, v.stream, a);
   else hipLaunchKernelGGL((k_vpost<false, DOT>), grid, dim3(VB), 0, v.stream, a);
@@ -491,33 +492,21 @@ int iteration(VecCtx &v, const double *f, cd *x, bool adjoint, const cisor_ls_op
   a.f = f;
   const dim3 grid(v.nbv, v.T);
   scalar_step<PH_BETA>(v, o);
-  if (adjoint) hipLaunchKernelGGL(k_vpupd<false>, grid, dim3(VB), 0, v.stream, a);
-  else hipLaunchKernelGGL(k_vpupd<true>, grid, dim3(VB), 0, v.stream, a);
+  hipLaunchKernelGGL(k_vpupd, grid, dim3(VB), 0, v.stream, a);
   a.need = V_ITER;
   // v = A p
-  if (adjoint) {
-    a.x = a.p;
-    hipLaunchKernelGGL(k_vpre<true>, grid, dim3(VB), 0, v.stream, a);
-  }
-  if (int rc = last_error()) return rc;
-  if (int rc = convolve(v, a.pre, v.ws[7], adjoint, a.need)) return rc;
   a.x = a.p;
+  if (int rc = convolve_input(v, a, adjoint)) return rc;
   a.out = a.v;
   if (adjoint) hipLaunchKernelGGL((k_vpost<true, DOT_V>), grid, dim3(VB), 0, v.stream, a);
   else hipLaunchKernelGGL((k_vpost<false, DOT_V>), grid, dim3(VB), 0, v.stream, a);
   scalar_step<PH_ALPHA>(v, o);
   // s = r - alpha v
-  if (adjoint) hipLaunchKernelGGL(k_vsupd<false>, grid, dim3(VB), 0, v.stream, a);
-  else hipLaunchKernelGGL(k_vsupd<true>, grid, dim3(VB), 0, v.stream, a);
+  hipLaunchKernelGGL(k_vsupd, grid, dim3(VB), 0, v.stream, a);
   scalar_step<PH_S>(v, o);
   // t = A s
-  if (adjoint) {
-    a.x = a.s;
-    hipLaunchKernelGGL(k_vpre<true>, grid, dim3(VB), 0, v.stream, a);
-  }
-  if (int rc = last_error()) return rc;
-  if (int rc = convolve(v, a.pre, v.ws[7], adjoint, a.need)) return rc;
   a.x = a.s;
+  if (int rc = convolve_input(v, a, adjoint)) return rc;
   a.out = a.t;
   if (adjoint) hipLaunchKernelGGL((k_vpost<true, DOT_T>), grid, dim3(VB), 0, v.stream, a);
   else hipLaunchKernelGGL((k_vpost<false, DOT_T>), grid, dim3(VB), 0, v.stream, a);
@@ -633,7 +622,7 @@ int launch_backproject(VecCtx &v, const double *f, const cd *w, cd *q, cd *rhs) 
 int launch_gradient(VecCtx &v, const cd *E, const cd *q, const cd *V, double *grad) {
   FieldArgs a = field_args(v);
   a.x = V;
-  hipLaunchKernelGGL(k_vpre<true>, dim3(v.nbv, v.T), dim3(VB), 0, v.stream, a);
+  hipLaunchKernelGGL(k_vpre, dim3(v.nbv, v.T), dim3(VB), 0, v.stream, a);
   if (int rc = last_error()) return rc;
   if (int rc = convolve(v, a.pre, v.ws[7], true, NO_MASK)) return rc;
   hipLaunchKernelGGL(k_vgrad, dim3((v.N + VB - 1) / VB), dim3(VB), 0, v.stream, E, q, v.ws[7], grad, v.N, v.T);
