@@ -548,10 +548,12 @@ __global__ void __launch_bounds__(256) k_row_inv(ConvArgs<Rs, Rc> a) {
   // The epilogue's operands, in two phases as in k_row_fwd; where they take few
   // registers (FP32 vectors) they are loaded ahead of the transform, which hides
   // their latency: with the products of t, 8.9 us before and 7.0 at 125^2 x 25,
-  // 24.8 and 22.8 at 256^2 x 60 (memory traffic)
+  // 24.8 and 22.8 at 256^2 x 60 (memory traffic).  Not for y = A x, whose one
+  // operand arrives no later after the transform (the operator at 256^2 x 60:
+  // 72.3 us with the early loads, 72.1 without)
   constexpr int RV = (RL + 1) / 2;   // the column of a later r is at least P/2 >= n
   constexpr int NLD = EPI == EPI_AX ? 1 : (EPI == EPI_G || EPI == EPI_GF) ? 0 : 2;
-  constexpr bool EARLY = sizeof(Cs) == 8;
+  constexpr bool EARLY = sizeof(Cs) == 8 && EPI != EPI_AX;
   constexpr int BB = EARLY ? V / RL : row_batch<V / RL>(RV * NLD * (int)sizeof(Cs) + 1);
   Cs l1[BB][RV], l2[BB][RV];
   Rs lf[BB][RV];
