@@ -7,9 +7,9 @@
 // The projection contracts over the N pixels (K = N, large) into a small
 // M x T output, so it is split over K: each block produces a partial tile,
 // and a second kernel sums the partials in FP64 in a fixed order.  The FP32
-// path runs on the BF16 matrix units with its operands split in three parts,
-// or for few transmitters on v_mfma_f32_16x16x4_f32; the FP64 path on
-// v_mfma_f64_16x16x4_f64.
+// path runs on the BF16 matrix units with its operands split in three parts
+// where these hold them exactly, or for few transmitters on
+// v_mfma_f32_16x16x4_f32; the FP64 path on v_mfma_f64_16x16x4_f64.
 #include <type_traits>
 
 #include "internal.hpp"
@@ -143,10 +143,16 @@ static void launch_project_f64(Ctx &c, const R *f, const cplx_t<R> *u, cd *part,
 // the matrix time of the three FP32 products of Gauss's form, and avoid the
 // cancellation in it.  RMS error against FP64 at 256^2 x 60 x 360 on random
 // operands, relative: projection 5.7e-7 in Gauss's form, 2.0e-7 here;
-// back-projection 4.9e-7 and 1.4e-7; at no size, scale (1e-30 to 1e20) or spread
-// of magnitudes measured was it larger.  With all six products in one sum the
-// projection's was (6.0e-7): only h h goes into the long sum.  An output reached
-// by a non-finite operand is NaN.
+// back-projection 4.9e-7 and 1.4e-7; at no size, scale or spread of magnitudes
+// measured was it larger.  With all six products in one sum the projection's was
+// (6.0e-7): only h h goes into the long sum.
+// The parts hold an operand exactly down to 2^-110, where the last one leaves the
+// subnormals of BF16 (unscaled, 2.6e-6 at 1e-35 and 2.5e-4 at 1e-37, where FP32
+// products keep 6e-7).  The fields and residuals are therefore scaled by 2^23; the
+// receiver matrix is looked over once, when the context is made (h_split).  Where
+// it has smaller components, and in a block whose sums end non-finite (operands
+// from 2^105 on, infinities), the outputs are formed from FP32 products instead
+// (v_mfma_f32_32x32x2_f32, Gauss's form).
 // Lane l supplies A[l%32][8(l/32)..+8] and B[8(l/32)..+8][l%32] and holds
 // C[8(r/4) + 4(l/32) + r%4][l%32] in accumulator register r.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -155,6 +161,16 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 constexpr int BS_PARTS = 3;
+// The operand that comes with a call is scaled by this, and the sums back: its
+// smallest parts are then normal numbers whatever its own size.
+constexpr float BF16_UP = 0x1p23f, BF16_DOWN = 0x1p-23f;
+// Zero where every sum is finite, else NaN.
+__device__ __forceinline__ float split_finite(const floatx16 &a, const floatx16 &b) {
+  float z = 0.0f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) z = fmaf(a[r], 0.0f, fmaf(b[r], 0.0f, z));
+  return z;
+}
 
 // The three BF16 parts of two values, packed in one dword each.
 __device__ __forceinline__ void bf16_split(float a, float b, unsigned (&part)[BS_PARTS]) {
@@ -171,6 +187,8 @@ __device__ __forceinline__ void bf16_split(float a, float b, unsigned (&part)[BS
     }
   }
 }
+// Whether any thread of the block asks for it (as a uniform value).
+__device__ __forceinline__ bool block_any(bool v) { return __builtin_amdgcn_readfirstlane(__syncthreads_or(v)) != 0; }
 // big + small += a b over the parts: only h h goes into big, so that a long sum
 // rounds once per 16 terms at its own size instead of six times.
 __device__ __forceinline__ void bf16_mfma6(const bf16x8 (&a)[BS_PARTS], const bf16x8 (&b)[BS_PARTS], floatx16 &big,
@@ -202,11 +220,78 @@ struct __attribute__((packed, aligned(8))) cf2 {
 // rounds, and two LDS buffers of 16 pixels take 99.
 constexpr int PJ_OFF32_N = 1 << 26;
 constexpr int PJ_KS = 32, PJ_ROW = 2 * BS_PARTS * PJ_KS + 8;   // BF16 elements per LDS row
+
+// The tile of k_project_bf16 from FP32 products, P1 = Hr Xr, P2 = Hi Xi and
+// P3 = (Hr + Hi)(Xr + Xi): Re = P1 - P2, Im = P3 - P1 - P2 (Gauss).  Lane l supplies
+// A[l%32][l/32] and B[l/32][l%32] of v_mfma_f32_32x32x2_f32.
+typedef cf PjRow32[PJ_KS + 1];
+// AHEAD: the next step's operands are loaded during the current one (the kernel
+// that tries the BF16 units first has no registers for them).
+template <bool AHEAD>
+__device__ __forceinline__ void project_tile_f32(const cf *H, const float *f, const cf *u, cd *part, int M, int N,
+                                                 int T, PjRow32 *sh, PjRow32 *su) {
+  constexpr int PER = 64 * PJ_KS / 256;
+  const int m0 = blockIdx.x * 64, kc = blockIdx.z;
+  const int k0 = kc * PJ_KCHUNK, kend = min(k0 + PJ_KCHUNK, N);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int am = (wave & 1) * 32 + (lane & 31), bt = (wave >> 1) * 32 + (lane & 31), kl = lane >> 5;
+  floatx16 p1 = {0}, p2 = {0}, p3 = {0};
+  cf rh[PER], ru[PER];
+  auto load = [&](int kb, int e) {
+    const int i = threadIdx.x + 256 * e, row = i / PJ_KS, k = kb + i % PJ_KS;
+    rh[AHEAD ? e : 0] = (m0 + row < M && k < kend) ? H[(size_t)(m0 + row) * N + k] : mk<cf>(0, 0);
+    ru[AHEAD ? e : 0] = (row < T && k < kend) ? cscale(u[(size_t)row * N + k], f[k]) : mk<cf>(0, 0);
+  };
+  auto load_ahead = [&](int kb) {
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int e = 0; e < PER; ++e) load(kb, e);
+    }
+  };
+  load_ahead(k0);
+  for (int kb = k0; kb < kend; kb += PJ_KS) {
+#pragma unroll AHEAD ? PER : 1
+    for (int e = 0; e < PER; ++e) {
+      if constexpr (!AHEAD) load(kb, e);
+      const int i = threadIdx.x + 256 * e;
+      sh[i / PJ_KS][i % PJ_KS] = rh[AHEAD ? e : 0];
+      su[i / PJ_KS][i % PJ_KS] = ru[AHEAD ? e : 0];
+    }
+    __syncthreads();
+    if (kb + PJ_KS < kend) load_ahead(kb + PJ_KS);
+#pragma unroll AHEAD ? PJ_KS / 2 : 2
+    for (int kk = 0; kk < PJ_KS; kk += 2) {
+      const cf a = sh[am][kk + kl], b = su[bt][kk + kl];
+      p1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, p1, 0, 0, 0);
+      p2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, p2, 0, 0, 0);
+      p3 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x + a.y, b.x + b.y, p3, 0, 0, 0);
+    }
+    __syncthreads();
+  }
+  if (bt >= T) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + (wave & 1) * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
+    const double d1 = p1[r], d2 = p2[r], d3 = p3[r];
+    if (m < M) part[((size_t)kc * T + bt) * M + m] = mk<cd>(d1 - d2, d3 - d1 - d2);
+  }
+}
+
+__global__ void __launch_bounds__(256) k_project_f32(const cf *H, const float *f, const cf *u, cd *part, int M, int N,
+                                                     int T) {
+  __shared__ PjRow32 sh[64], su[64];
+  project_tile_f32<true>(H, f, u, part, M, N, T, sh, su);
+}
+
 template <typename OFF>   // holds 64 N
 __global__ void __launch_bounds__(256, 3) k_project_bf16(const cf *H, const float *f, const cf *u, cd *part, int M,
                                                          int N, int T) {
   constexpr int PER = 64 * PJ_KS / 2 / 256;   // pixel pairs per thread and operand
   __shared__ __attribute__((aligned(16))) unsigned short sh[64][PJ_ROW], su[64][PJ_ROW];
+  static_assert(sizeof(sh) >= 64 * sizeof(PjRow32), "the FP32 tile uses the same LDS");
+  auto f32_tile = [&] {
+    project_tile_f32<false>(H, f, u, part, M, N, T, reinterpret_cast<PjRow32 *>(sh), reinterpret_cast<PjRow32 *>(su));
+  };
   const int m0 = blockIdx.x * 64, kc = blockIdx.z;
   const int k0 = kc * PJ_KCHUNK;
   const int kend = min(k0 + PJ_KCHUNK, N);
@@ -264,7 +349,7 @@ __global__ void __launch_bounds__(256, 3) k_project_bf16(const cf *H, const floa
     const cf z = mk<cf>(0, 0);
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-      const cf x0 = cscale(ru[e].v[0], rf[0]), x1 = cscale(ru[e].v[1], rf[1]);
+      const cf x0 = cscale(ru[e].v[0], rf[0] * BF16_UP), x1 = cscale(ru[e].v[1], rf[1] * BF16_UP);
       put(sh[row + RS * e], ok0 ? rh[e].v[0] : z, ok1 ? rh[e].v[1] : z);
       put(su[row + RS * e], ok0 ? x0 : z, ok1 ? x1 : z);
     }
@@ -292,12 +377,15 @@ __global__ void __launch_bounds__(256, 3) k_project_bf16(const cf *H, const floa
     }
     __syncthreads();
   }
+  if (block_any(split_finite(re, res) + split_finite(im, ims) != 0.0f)) return f32_tile();
   const int t = wt * 32 + (lane & 31);
   if (t >= T) return;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int m = m0 + wm * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-    if (m < M) part[((size_t)kc * T + t) * M + m] = mk<cd>((double)re[r] + (double)res[r], (double)im[r] + (double)ims[r]);
+    if (m < M)
+      part[((size_t)kc * T + t) * M + m] = cscale(mk<cd>((double)re[r] + (double)res[r], (double)im[r] + (double)ims[r]),
+                                                           (double)BF16_DOWN);
   }
 }
 
@@ -450,8 +538,8 @@ int launch_project(Ctx &c, const R *f, const cplx_t<R> *u, const cplx_t<R> *y_me
       dim3 g((c.M + 63) / 64, 1, kchunks);
       // 32-bit row offsets below 2^26 pixels: 64-bit ones cost 20 spilled registers
       // (90.4 against 89.2 us at 256^2 x 60 x 360)
-      hipLaunchKernelGGL(c.N < PJ_OFF32_N ? k_project_bf16<unsigned> : k_project_bf16<size_t>, g, dim3(256), 0,
-                         c.stream, (const cf *)c.H, f, u, part, c.M, c.N, c.T);
+      const auto kern = !c.h_split ? k_project_f32 : c.N < PJ_OFF32_N ? k_project_bf16<unsigned> : k_project_bf16<size_t>;
+      hipLaunchKernelGGL(kern, g, dim3(256), 0, c.stream, (const cf *)c.H, f, u, part, c.M, c.N, c.T);
     } else {
       launch_project_f64<float>(c, f, u, part, kchunks);
     }
@@ -574,11 +662,99 @@ constexpr int BP_WROW = 2 * BS_PARTS * BP_MS + 16;   // BF16 elements per transm
 // banks) each, so that the four rows of a transposing read miss each other's banks.
 __device__ __forceinline__ int bp_pos(int m, int k) { return (k + 32 * (m & 3)) & (BP_PT - 1); }
 
+// The tile of k_backproject_bf16 from FP32 products, P1 = Wr Hr, P2 = Wi Hi and
+// P3 = (Wr + Wi)(Hr - Hi): Re = P1 + P2, Im = P3 - P1 + P2 (lane layout as in
+// project_tile_f32).
+typedef cf BpWRow32[BP_MS + 1];
+typedef cf BpHRow32[BP_PT + 1];
+template <bool AHEAD>
+__device__ __forceinline__ void backproject_tile_f32(const cf *H, const cf *w, cf *q, const float *f, cf *b, int M,
+                                                     int N, int T, BpWRow32 *sw, BpHRow32 *shh) {
+  constexpr int PW = BP_TT * BP_MS / 256, PH = BP_MS * BP_PT / 256;
+  const int k0 = blockIdx.x * BP_PT, t0 = blockIdx.y * BP_TT;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wt = wave & 1, wp = wave >> 1, kl = lane >> 5;
+  floatx16 p1[2] = {{0}, {0}}, p2[2] = {{0}, {0}}, p3[2] = {{0}, {0}};
+  cf rw[PW], rh[PH];
+  auto load_w = [&](int m0, int e) {
+    const int i = threadIdx.x + 256 * e, t = t0 + i / BP_MS, m = m0 + i % BP_MS;
+    rw[AHEAD ? e : 0] = (t < T && m < M) ? w[(size_t)t * M + m] : mk<cf>(0, 0);
+  };
+  auto load_h = [&](int m0, int e) {
+    const int i = threadIdx.x + 256 * e, m = m0 + i / BP_PT, k = k0 + i % BP_PT;
+    rh[AHEAD ? e : 0] = (m < M && k < N) ? H[(size_t)m * N + k] : mk<cf>(0, 0);
+  };
+  auto load_ahead = [&](int m0) {
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int e = 0; e < PW; ++e) load_w(m0, e);
+#pragma unroll
+      for (int e = 0; e < PH; ++e) load_h(m0, e);
+    }
+  };
+  load_ahead(0);
+  for (int m0 = 0; m0 < M; m0 += BP_MS) {
+#pragma unroll AHEAD ? PW : 1
+    for (int e = 0; e < PW; ++e) {
+      if constexpr (!AHEAD) load_w(m0, e);
+      const int i = threadIdx.x + 256 * e;
+      sw[i / BP_MS][i % BP_MS] = rw[AHEAD ? e : 0];
+    }
+#pragma unroll AHEAD ? PH : 1
+    for (int e = 0; e < PH; ++e) {
+      if constexpr (!AHEAD) load_h(m0, e);
+      const int i = threadIdx.x + 256 * e;
+      shh[i / BP_PT][i % BP_PT] = rh[AHEAD ? e : 0];
+    }
+    __syncthreads();
+    if (m0 + BP_MS < M) load_ahead(m0 + BP_MS);
+#pragma unroll AHEAD ? BP_MS / 2 : 1
+    for (int mm = 0; mm < BP_MS; mm += 2) {
+      const cf a = sw[wt * 32 + (lane & 31)][mm + kl];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const cf h = shh[mm + kl][wp * 64 + j * 32 + (lane & 31)];
+        p1[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, h.x, p1[j], 0, 0, 0);
+        p2[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, h.y, p2[j], 0, 0, 0);
+        p3[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x + a.y, h.x - h.y, p3[j], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int k = k0 + wp * 64 + j * 32 + (lane & 31);
+    if (k >= N) continue;
+    const float fk = b ? f[k] : 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int t = t0 + wt * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
+      if (t >= T) continue;
+      const double d1 = p1[j][r], d2 = p2[j][r], d3 = p3[j][r];
+      const cf val = mk<cf>((float)(d1 + d2), (float)(d3 - d1 + d2));
+      q[(size_t)t * N + k] = val;
+      if (b) b[(size_t)t * N + k] = mk<cf>(val.x * fk, val.y * fk);
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256) k_backproject_f32(const cf *H, const cf *w, cf *q, const float *f, cf *b, int M,
+                                                         int N, int T) {
+  __shared__ BpWRow32 sw[BP_TT];
+  __shared__ BpHRow32 shh[BP_MS];
+  backproject_tile_f32<true>(H, w, q, f, b, M, N, T, sw, shh);
+}
+
 __global__ void __launch_bounds__(256, 2) k_backproject_bf16(const cf *H, const cf *w, cf *q, const float *f, cf *b,
                                                           int M, int N, int T) {
   constexpr int PW = BP_TT * BP_MS / 2 / 256, PH = BP_MS * BP_PT / 2 / 256;   // pairs per thread
   __shared__ __attribute__((aligned(16))) unsigned short sw2[2][BP_TT][BP_WROW];
   __shared__ __attribute__((aligned(16))) unsigned short sh2[2][2 * BS_PARTS][BP_MS][BP_PT];
+  static_assert(sizeof(sw2) >= BP_TT * sizeof(BpWRow32) && sizeof(sh2) >= BP_MS * sizeof(BpHRow32),
+                "the FP32 tile uses the same LDS");
+  auto f32_tile = [&] {
+    backproject_tile_f32<false>(H, w, q, f, b, M, N, T, reinterpret_cast<BpWRow32 *>(sw2), reinterpret_cast<BpHRow32 *>(sh2));
+  };
   const int k0 = blockIdx.x * BP_PT, t0 = blockIdx.y * BP_TT;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wt = wave & 1, wp = wave >> 1;
@@ -617,7 +793,7 @@ __global__ void __launch_bounds__(256, 2) k_backproject_bf16(const cf *H, const 
 #pragma unroll
     for (int e = 0; e < PW; ++e) {
       const int m = m0 + 2 * wpair;
-      const cf a0 = m < M ? rw[e][0] : z, a1 = m + 1 < M ? rw[e][1] : z;
+      const cf a0 = m < M ? cscale(rw[e][0], BF16_UP) : z, a1 = m + 1 < M ? cscale(rw[e][1], BF16_UP) : z;
       bf16_split(a0.x, a1.x, p);
       bf16_split(a0.y, a1.y, r);
       unsigned short *dst = sw[wr + e * (512 / BP_MS)] + 2 * wpair;
@@ -683,6 +859,9 @@ __global__ void __launch_bounds__(256, 2) k_backproject_bf16(const cf *H, const 
       __syncthreads();
     }
   }
+  const float fin = split_finite(re[0], res[0]) + split_finite(re[1], res[1]) + split_finite(im[0], ims[0]) +
+                    split_finite(im[1], ims[1]);
+  if (block_any(fin != 0.0f)) return f32_tile();
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int k = k0 + wp * 64 + j * 32 + (lane & 31);
@@ -692,7 +871,7 @@ __global__ void __launch_bounds__(256, 2) k_backproject_bf16(const cf *H, const 
     for (int r = 0; r < 16; ++r) {
       const int t = t0 + wt * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
       if (t >= T) continue;
-      const cf val = mk<cf>(re[j][r] + res[j][r], im[j][r] + ims[j][r]);
+      const cf val = cscale(mk<cf>(re[j][r] + res[j][r], im[j][r] + ims[j][r]), BF16_DOWN);
       q[(size_t)t * N + k] = val;
       if (b) b[(size_t)t * N + k] = mk<cf>(val.x * fk, val.y * fk);
     }
@@ -778,7 +957,8 @@ int launch_backproject(Ctx &c, const cplx_t<R> *w, cplx_t<R> *q, const R *f, cpl
       return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
     }
     dim3 g((c.N + BP_PT - 1) / BP_PT, (c.T + BP_TT - 1) / BP_TT);
-    hipLaunchKernelGGL(k_backproject_bf16, g, dim3(256), 0, c.stream, (const cf *)c.H, w, q, f, b, c.M, c.N, c.T);
+    hipLaunchKernelGGL(c.h_split ? k_backproject_bf16 : k_backproject_f32, g, dim3(256), 0, c.stream, (const cf *)c.H, w,
+                       q, f, b, c.M, c.N, c.T);
   } else {
     launch_backproject_f64(c, w, q, f, b);
   }

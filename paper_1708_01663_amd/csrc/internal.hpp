@@ -39,6 +39,9 @@ constexpr int PROJ_REDUCE_OUT = 32;  // projection outputs per block of the spli
 // Doubles of the projection's D scratch for M*T outputs: one partial per
 // split-K-sum block, plus the slot that receives D.
 inline size_t proj_dpart_slots(size_t MT) { return (MT + PROJ_REDUCE_OUT - 1) / PROJ_REDUCE_OUT + 1; }
+// Non-zero FP32 numbers of at least this magnitude have three BF16 parts that are
+// zero or normal numbers (see gemm.hip).
+constexpr float BF16_SPLIT_MIN = 0x1p-103f;
 constexpr int UPD_EPT = 4;        // elements per thread of the update kernel
 constexpr int UPD_THREADS = 256;
 
@@ -181,7 +184,9 @@ struct Ctx {
   // five N-vectors (y, gradient, gradient step, z and v estimates)
   void *apg_A1 = nullptr, *apg_A2 = nullptr, *apg_buf = nullptr;
   int apg_fields = 0;               // 1 / 2: apg_A1 / apg_A2 holds the forward fields of x_k
-  // projection GEMM
+  // projection GEMM; h_split: every component of H is zero or at least
+  // BF16_SPLIT_MIN and finite (complex64)
+  bool h_split = true;
   void *gemm_part = nullptr;        // split-K partials
   int gemm_kchunks = 0;
   double *dpart = nullptr;          // FP64 block partials of D

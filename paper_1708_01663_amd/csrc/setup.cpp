@@ -15,6 +15,7 @@
 // outgoing solution consistent with the 3D exp(+j k r) convention is +i/4,
 // which is the one used here.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <complex>
 #include <functional>
@@ -123,6 +124,12 @@ template <typename R> static int upload(Ctx &c, void *dst, const std::vector<cdb
   return CISOR_OK;
 }
 
+// Whether both components may be split in three BF16 parts (see Ctx::h_split).
+static bool splits(cdbl v) {
+  auto one = [](double x) { return x == 0.0 || (std::fabs(x) >= BF16_SPLIT_MIN && std::fabs(x) < 0x1p127); };
+  return one(v.real()) && one(v.imag());
+}
+
 static void parallel_for(int n, const std::function<void(int, int)> &fn) {
   int nth = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
   nth = std::min(nth, std::max(1, n));
@@ -179,6 +186,7 @@ template <typename R> static int upload_H3(Ctx &c, const cisor_geometry &g, cons
   const int chunk = 32;
   std::vector<cplx_t<R>> buf((size_t)chunk * N);
   bool bad = false;
+  std::atomic<bool> split{true};
   for (int m0 = 0; m0 < M; m0 += chunk) {
     const int m1 = std::min(M, m0 + chunk);
     parallel_for(m1 - m0, [&](int lo, int hi) {
@@ -192,6 +200,7 @@ template <typename R> static int upload_H3(Ctx &c, const cisor_geometry &g, cons
               const double rho = std::sqrt(dx * dx + dy * dy + dz * dz);
               if (rho < ker.a) bad = true;
               const cdbl v = ker(rho);
+              if (!splits(v)) split = false;
               buf[(size_t)mm * N + ((size_t)i * n + j) * n + l] = mk<cplx_t<R>>((R)v.real(), (R)v.imag());
             }
       }
@@ -200,6 +209,7 @@ template <typename R> static int upload_H3(Ctx &c, const cisor_geometry &g, cons
     CISOR_HIP_CHECK(hipMemcpy((cplx_t<R> *)c.H + (size_t)m0 * N, buf.data(), sizeof(cplx_t<R>) * (m1 - m0) * N,
                               hipMemcpyHostToDevice));
   }
+  c.h_split = split;
   return CISOR_OK;
 }
 
@@ -332,6 +342,7 @@ int build_geometry(Ctx &c, const cisor_geometry &g, bool spectrum) {
   // receiver matrix
   std::vector<cdbl> H((size_t)M * N);
   bool bad = false;
+  std::atomic<bool> split{true};
   parallel_for(M, [&](int a, int b) {
     for (int m = a; m < b; ++m) {
       const double rx = g.rx_pos[2 * m], ry = g.rx_pos[2 * m + 1];
@@ -339,11 +350,14 @@ int build_geometry(Ctx &c, const cisor_geometry &g, bool spectrum) {
         for (int j = 0; j < n; ++j) {
           const double rho = std::hypot(rx - ax[i], ry - ax[j]);
           if (rho < ker.a) bad = true;
-          H[(size_t)m * N + (size_t)i * n + j] = ker(rho);
+          const cdbl v = ker(rho);
+          if (!splits(v)) split = false;
+          H[(size_t)m * N + (size_t)i * n + j] = v;
         }
     }
   });
   if (bad) return CISOR_E_ARG;
+  c.h_split = split;
   // twiddles exp(-2 pi i m / P)
   std::vector<cdbl> tw(P);
   for (int m = 0; m < P; ++m) tw[m] = std::polar(1.0, -2.0 * kPi * m / P);

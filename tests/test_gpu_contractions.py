@@ -90,3 +90,80 @@ def test_split_contractions_extremes():
     # one product per output: the dropped parts and one rounding
     assert float((q[5].to(torch.complex128) - want).abs().max()) <= 4 * 2.0 ** -24 * float(want.abs().max())
     assert float(q[:5].abs().max()) == 0.0
+
+
+def _rel(a, b):
+    a, b = torch.view_as_real(a.to(torch.complex128)), torch.view_as_real(b)
+    s = float(b.abs().max())
+    return float(torch.linalg.vector_norm((a - b) / s) / torch.linalg.vector_norm(b / s))
+
+
+# the same sizes with a bar that a lost or misplaced part product does not pass: the six kept part
+# products leave less than 2^-24 per product, and the long sum rounds once per 16 receivers
+@pytest.mark.parametrize("n,T,M", [(3, 17, 1), (16, 32, 16), (23, 33, 33), (32, 64, 64), (61, 60, 130), (40, 130, 360)])
+def test_split_backprojection_keeps_every_part(n, T, M):
+    print(f"split back-projection {n} {T} {M}", flush=True)
+    op = Cisor(n, 0.1, plane_wave_dirs(T), ring(M, n * 0.1), precision="c64")
+    rng = np.random.default_rng(n + T)
+    w = torch.as_tensor(rng.standard_normal((T, M)) + 1j * rng.standard_normal((T, M))).to(op.cdtype)
+    q = op.backproject(w.cuda()).cpu()
+    assert _rel(q, w.to(torch.complex128) @ op.H().cpu().to(torch.complex128).conj()) <= 8 * 2.0 ** -24
+
+
+# operands below 2^-103, whose BF16 parts are no longer exact, take FP32 products: the bars of FP32
+# sums hold down to the smallest normal numbers, in a block that has only such operands and in one
+# that has a single one
+@pytest.mark.parametrize("scale", [1e-31, 1e-33, 1e-35, 1e-37])
+def test_split_contractions_small_operands(scale):
+    n, T, M = 45, 33, 50
+    print(f"small operands {scale}", flush=True)
+    op = Cisor(n, 0.1, plane_wave_dirs(T), ring(M, n * 0.1), precision="c64")
+    rng = np.random.default_rng(5)
+
+    def cplx(*s):
+        return torch.as_tensor(scale * (rng.standard_normal(s) + 1j * rng.standard_normal(s))).to(op.cdtype)
+
+    f = torch.ones(op.N, dtype=op.rdtype).cuda()
+    H = op.H().cpu().to(torch.complex128)
+    u, w = cplx(T, op.N), cplx(T, M)
+    eps = 2.0 ** -24
+    assert _rel(op.project(f, u.cuda()).cpu(), u.to(torch.complex128) @ H.T) <= 4 * 64 ** 0.5 * eps
+    assert _rel(op.backproject(w.cuda()).cpu(), w.to(torch.complex128) @ H.conj()) <= 16 * eps
+    one_u, one_w = torch.zeros_like(u), torch.zeros_like(w)
+    one_u[20, 700] = u[20, 700]
+    one_w[20, 31] = w[20, 31]
+    y, q = op.project(f, one_u.cuda()).cpu(), op.backproject(one_w.cuda()).cpu()
+    # one complex product an output, from three real ones of up to four times its size, and at 1e-37
+    # half a unit of the smallest subnormal number in each
+    assert _rel(y, one_u.to(torch.complex128) @ H.T) <= 16 * eps
+    assert _rel(q, one_w.to(torch.complex128) @ H.conj()) <= 16 * eps
+
+
+def test_split_contractions_small_receiver_matrix():
+    """A pixel side so small that H itself lies below 2^-103."""
+    n, T, M = 20, 20, 40
+    op = Cisor(n, 1e-18, plane_wave_dirs(T), ring(M, 0.7), precision="c64")
+    H = op.H().cpu().to(torch.complex128)
+    assert 1e-36 < float(H.abs().max()) < 2.0 ** -103
+    rng = np.random.default_rng(6)
+    cplx = lambda *s: torch.as_tensor(rng.standard_normal(s) + 1j * rng.standard_normal(s)).to(op.cdtype)
+    u, w = cplx(T, op.N), cplx(T, M)
+    y = op.project(torch.ones(op.N, dtype=op.rdtype).cuda(), u.cuda()).cpu()
+    eps = 2.0 ** -24
+    assert _rel(y, u.to(torch.complex128) @ H.T) <= 4 * 64 ** 0.5 * eps
+    assert _rel(op.backproject(w.cuda()).cpu(), w.to(torch.complex128) @ H.conj()) <= 16 * eps
+
+
+def test_split_contractions_infinite_operand_keeps_its_real_part():
+    """The real part of an infinite real operand's products is infinite, as in FP32 products."""
+    n, T, M = 23, 33, 33
+    op = Cisor(n, 0.1, plane_wave_dirs(T), ring(M, n * 0.1), precision="c64")
+    H = op.H().cpu()
+    u = torch.ones(T, op.N, dtype=op.cdtype)
+    w = torch.ones(T, M, dtype=op.cdtype)
+    u[32, op.N - 1] = float("inf")
+    w[32, M - 1] = float("inf")
+    y = op.project(torch.ones(op.N, dtype=op.rdtype).cuda(), u.cuda()).cpu()
+    q = op.backproject(w.cuda()).cpu()
+    assert torch.equal(y[32].real, float("inf") * H[:, op.N - 1].real.sign())
+    assert torch.equal(q[32].real, float("inf") * H[M - 1].real.sign())
