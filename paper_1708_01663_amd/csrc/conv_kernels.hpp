@@ -12,6 +12,15 @@ namespace cisor {
 
 template <typename C> __device__ __forceinline__ C czero() { return mk<C>(0, 0); }
 
+// The contrast of system t, as a pointer that is known to point to global memory:
+// chosen between an argument and a pointer from memory, and captured by a lambda, a
+// plain one is read with flat loads, each of which waits for the LDS as well.
+template <typename R> using GlobalPtr = const __attribute__((address_space(1))) R *;
+template <typename A> __device__ __forceinline__ auto contrast_of(const A &a, int t) {
+  using R = std::remove_const_t<std::remove_pointer_t<decltype(a.f)>>;
+  return (GlobalPtr<R>)(a.frow ? a.frow[t] : a.f);
+}
+
 // ---------------------------------------------------------------- stage 1
 // LDS elements of a row kernel: the rows' transforms, and with PM (plane-major
 // layout of the intermediates, 3D plane path) the transposition of the block's
@@ -22,19 +31,32 @@ template <int P, bool PM> constexpr int row_lds() {
 }
 
 // First-radix groups of a thread's elements whose operands, `bytes` a group, the
-// row kernels hold at once: as many as ROW_HOLD bytes take, a divisor of the groups.
-constexpr int ROW_HOLD = 384;
-template <int GROUPS> constexpr int row_batch(int bytes) {
+// row kernels hold at once: as many as `hold` bytes take, a divisor of the groups.
+// What they hold is chosen so that no wave per SIMD is lost for it where traffic
+// bounds the kernel: 384 bytes (96 registers) beside the 40 to 150 of the other
+// transforms, 256 beside a full one (row_full), 128 for y = A^H x of 24 points in
+// FP32 (120 registers, four waves; 140 and three with 384).
+template <int GROUPS> constexpr int row_batch(int bytes, int hold) {
   int n = GROUPS;
-  while (n > 1 && (n * bytes > ROW_HOLD || GROUPS % n)) --n;
+  while (n > 1 && (n * bytes > hold || GROUPS % n)) --n;
   return n;
+}
+// FP64 transforms of 24 points a thread take 200 to 250 registers by themselves.
+template <typename Rc, int P> constexpr bool row_full() { return P / RowCfg<P>::NT * 2 * sizeof(Rc) > 256; }
+// Element e of an array that e may point anywhere into, or of one field: at most
+// 512^3 values, so that 32 bits hold its byte offset (one register beside a
+// uniform base instead of an address of two).
+template <typename T> __device__ __forceinline__ T &at_elem(T *a, size_t e) { return a[e]; }
+template <typename T> __device__ __forceinline__ T &at_elem(T *a, unsigned e) {
+  using B = std::conditional_t<std::is_const<T>::value, const char, char>;
+  return *reinterpret_cast<T *>(reinterpret_cast<B *>(a) + e * (unsigned)sizeof(T));
 }
 // PM: X1 is written plane-major, X1[t][k][row] (3D: the n^2 rows of one kz
 // together) instead of X1[t][row][k].  EXACT (2D, power-of-two P = 2n, rows a
 // multiple of the block's): every row is valid and column j + r P/R0 < n
 // exactly when r < R0/2, so the element checks are decided at compile time.
 template <typename Rs, typename Rc, int P, int PRO, bool MULF, bool PM = false, bool EXACT = false>
-__global__ void __launch_bounds__(256) k_row_fwd(ConvArgs<Rs, Rc> a) {
+__global__ void __launch_bounds__(256, (PRO == PRO_X && row_full<Rc, P>() ? 2 : 1)) k_row_fwd(ConvArgs<Rs, Rc> a) {
   using Cs = cplx_t<Rs>;
   using Cc = cplx_t<Rc>;
   using PL = Plan<P>;
@@ -44,7 +66,7 @@ __global__ void __launch_bounds__(256) k_row_fwd(ConvArgs<Rs, Rc> a) {
   const int t = blockIdx.y;
   if (a.st && !(a.st[t].flags & a.flag)) return;
   if (a.fmask && !a.fmask[t]) return;
-  const Rs *fr = a.frow ? a.frow[t] : a.f;
+  const GlobalPtr<Rs> fr = contrast_of(a, t);
   constexpr int SPAN = RowCfg<P>::SPAN;
   __shared__ Cc lds[row_lds<P, PM>()];
   const int lr = threadIdx.x / NT, tid = threadIdx.x % NT;
@@ -73,27 +95,46 @@ __global__ void __launch_bounds__(256) k_row_fwd(ConvArgs<Rs, Rc> a) {
   // first store.  Element by element, a load would wait for the store before it
   // (nothing tells the compiler that the vectors are distinct), a memory latency
   // each: the p update took 10.7 us so and takes 8.0 at 125^2 x 25, 36.5 and 33.0
-  // at 256^2 x 60, where memory traffic bounds it
+  // at 256^2 x 60, where memory traffic bounds it.  The plain input (PRO_X) stores
+  // nothing in between; held ahead where the contrast multiplies it on other grids
+  // than n = P/2 (the operator at 192^2 x 60: 69 us, 77 with wide offsets, 79 element
+  // by element), else read element by element (held, A^H x in FP64 at 384^2 x 25
+  // spent 61 us in it instead of 41, with one wave per SIMD instead of two)
   constexpr int RV = (R0 + 1) / 2;   // the column of a later r is at least P/2 >= n
   constexpr int NLD = PRO == PRO_PUPD ? 5 : PRO == PRO_SUPD ? 3 : 1;
-  constexpr int BB = row_batch<V / R0>(RV * NLD * (int)sizeof(Cs));
+  constexpr bool FULL = row_full<Rc, P>();
+  constexpr bool AHEAD = PRO != PRO_X || (MULF && !EXACT), NARROW = PRO == PRO_X && AHEAD;
+  constexpr int BB = NARROW ? row_batch<V / R0>(RV * (int)(sizeof(Cs) + sizeof(Rs)), FULL ? 256 : 384)
+                            : row_batch<V / R0>(RV * NLD * (int)sizeof(Cs), 384);
   Cc v[V];
+  const size_t field = (size_t)t * a.N;
+  auto base = [&](auto *x) { return NARROW ? x + field : x; };
+  auto col_of = [&](int b, int r) { return tid + b * NT + r * (P / R0); };
+  auto ok = [&](int b, int r) { return EXACT ? r < R0 / 2 : vr && col_of(b, r) < a.n; };
+  auto elem = [&](int b, int r) {
+    if constexpr (NARROW) return (unsigned)(row * a.n + col_of(b, r));
+    else return rowoff + col_of(b, r);
+  };
+  using El = decltype(elem(0, 0));
+  const El first = NARROW ? El(0) : El(field);
+  auto f_at = [&](El e) {   // the contrast at a field's element
+    if constexpr (NARROW) return *(GlobalPtr<Rs>)((GlobalPtr<char>)fr + e * (unsigned)sizeof(Rs));
+    else return fr[e - field];
+  };
 #pragma unroll
   for (int b0 = 0; b0 < V / R0; b0 += BB) {
     Cs la[BB][RV], lb[BB][RV], lc[BB][RV], ld[BB][RV], le[BB][RV];
     Rs lf[BB][RV];
     // columns past n are read from the system's first element and not used
-    auto col_of = [&](int b, int r) { return tid + (b0 + b) * NT + r * (P / R0); };
-    auto ok = [&](int b, int r) { return EXACT ? r < R0 / 2 : vr && col_of(b, r) < a.n; };
-    auto at = [&](int b, int r) { return ok(b, r) ? rowoff + col_of(b, r) : (size_t)t * a.N; };
+    auto at = [&](int b, int r) { return ok(b0 + b, r) ? elem(b0 + b, r) : first; };
     auto load = [&](Cs(&dst)[BB][RV], const Cs *src) {
 #pragma unroll
       for (int b = 0; b < BB; ++b)
 #pragma unroll
-        for (int r = 0; r < RV; ++r) dst[b][r] = src[at(b, r)];
+        for (int r = 0; r < RV; ++r) dst[b][r] = at_elem(base(src), at(b, r));
     };
     if constexpr (PRO == PRO_X) {
-      load(la, a.x);
+      if constexpr (AHEAD) load(la, a.x);
     } else {
       if (PRO == PRO_SUPD || !bz) load(ld, a.v);
       if (PRO == PRO_PUPD && (pend || !bz)) load(lb, a.p);
@@ -105,21 +146,21 @@ __global__ void __launch_bounds__(256) k_row_fwd(ConvArgs<Rs, Rc> a) {
         if (PRO == PRO_PUPD && pend) load(le, a.xw);
       }
     }
-    if constexpr (MULF) {
+    if constexpr (MULF && AHEAD) {
 #pragma unroll
       for (int b = 0; b < BB; ++b)
 #pragma unroll
-        for (int r = 0; r < RV; ++r) lf[b][r] = fr[at(b, r) - (size_t)t * a.N];
+        for (int r = 0; r < RV; ++r) lf[b][r] = f_at(at(b, r));
     }
 #pragma unroll
     for (int b = 0; b < BB; ++b) {
 #pragma unroll
       for (int r = 0; r < R0; ++r) {
         Cc val = czero<Cc>();
-        if (r < RV && ok(b, r)) {
-          const size_t e = rowoff + col_of(b, r);
+        if (r < RV && ok(b0 + b, r)) {
+          const El e = elem(b0 + b, r);
           if constexpr (PRO == PRO_X) {
-            val = ccast<Cc>(la[b][r]);
+            val = ccast<Cc>(AHEAD ? la[b][r] : a.x[e]);
           } else if constexpr (PRO == PRO_PUPD) {
             // x += alpha p + omega s (last iteration); p = r + beta (p - omega v),
             // which is p = r when beta = 0: p and v are then not read, so a
@@ -140,7 +181,7 @@ __global__ void __launch_bounds__(256) k_row_fwd(ConvArgs<Rs, Rc> a) {
             val = csub(rr, cmul(al, ccast<Cc>(ld[b][r])));
             a.s[e] = ccast<Cs>(val);
           }
-          if constexpr (MULF) val = cscale(val, static_cast<Rc>(lf[b][r]));
+          if constexpr (MULF) val = cscale(val, static_cast<Rc>(AHEAD ? lf[b][r] : f_at(e)));
         }
         v[(b0 + b) * R0 + r] = val;
       }
@@ -508,7 +549,7 @@ __global__ void __launch_bounds__(256) k_row_inv(ConvArgs<Rs, Rc> a) {
   const int t = blockIdx.y;
   if (a.st && !(a.st[t].flags & a.flag)) return;
   if (a.fmask && !a.fmask[t]) return;
-  const Rs *fr = a.frow ? a.frow[t] : a.f;
+  const GlobalPtr<Rs> fr = contrast_of(a, t);
   constexpr int SPAN = RowCfg<P>::SPAN;
   __shared__ Cc lds[row_lds<P, PM>()];
   __shared__ double scratch[16 * NA];
@@ -550,18 +591,36 @@ __global__ void __launch_bounds__(256) k_row_inv(ConvArgs<Rs, Rc> a) {
   // their latency: with the products of t, 8.9 us before and 7.0 at 125^2 x 25,
   // 24.8 and 22.8 at 256^2 x 60 (memory traffic).  Not for y = A x, whose one
   // operand arrives no later after the transform (the operator at 256^2 x 60:
-  // 72.3 us with the early loads, 72.1 without)
+  // 72.3 us with the early loads, 72.1 without).  Narrow offsets where they measure
+  // faster: A^H x at 192^2 x 60 in FP32 67.8 us (73.1 with wide ones), in FP64 132 us
+  // (159, and 141 element by element)
   constexpr int RV = (RL + 1) / 2;   // the column of a later r is at least P/2 >= n
   constexpr int NLD = EPI == EPI_AX ? 1 : (EPI == EPI_G || EPI == EPI_GF) ? 0 : 2;
   constexpr bool EARLY = sizeof(Cs) == 8 && EPI != EPI_AX;
-  constexpr int BB = EARLY ? V / RL : row_batch<V / RL>(RV * NLD * (int)sizeof(Cs) + 1);
+  constexpr bool FULL = row_full<Rc, P>();
+  constexpr bool NARROW = EPI == EPI_AX && !EXACT && (P > 128 || sizeof(Cs) == 16);
+  constexpr int BB = EARLY ? V / RL
+                           : row_batch<V / RL>(RV * (NLD * (int)sizeof(Cs) + (NARROW && MULF ? (int)sizeof(Rs) : 0)) + 1,
+                                               FULL && (NARROW || MULF) ? 256 : NARROW && MULF && V == 24 ? 128 : 384);
   Cs l1[BB][RV], l2[BB][RV];
   Rs lf[BB][RV];
+  const size_t field = (size_t)t * a.N;
+  auto base = [&](auto *x) { return NARROW ? x + field : x; };
   auto col_of = [&](int b, int r) { return tid + b * NT + r * (P / RL); };
   auto ok = [&](int b, int r) { return EXACT ? r < RL / 2 : vr && col_of(b, r) < a.n; };
+  auto elem = [&](int b, int r) {
+    if constexpr (NARROW) return (unsigned)(row * a.n + col_of(b, r));
+    else return rowoff + col_of(b, r);
+  };
+  using El = decltype(elem(0, 0));
+  const El first = NARROW ? El(0) : El(field);
+  auto f_at = [&](El e) {   // the contrast at a field's element
+    if constexpr (NARROW) return *(GlobalPtr<Rs>)((GlobalPtr<char>)fr + e * (unsigned)sizeof(Rs));
+    else return fr[e - field];
+  };
   auto load = [&](int b0) {
     // columns past n are read from the system's first element and not used
-    auto at = [&](int b, int r) { return ok(b0 + b, r) ? rowoff + col_of(b0 + b, r) : (size_t)t * a.N; };
+    auto at = [&](int b, int r) { return ok(b0 + b, r) ? elem(b0 + b, r) : first; };
     const Cs *p1 = nullptr, *p2 = nullptr;
     if constexpr (EPI == EPI_AX) p1 = a.x;
     else if constexpr (EPI == EPI_V) p1 = a.p, p2 = a.rhat;
@@ -572,9 +631,9 @@ __global__ void __launch_bounds__(256) k_row_inv(ConvArgs<Rs, Rc> a) {
     for (int b = 0; b < BB; ++b)
 #pragma unroll
       for (int r = 0; r < RV; ++r) {
-        if constexpr (NLD >= 1) l1[b][r] = p1[at(b, r)];
-        if constexpr (NLD >= 2) l2[b][r] = p2[at(b, r)];
-        if constexpr (MULF) lf[b][r] = fr[at(b, r) - (size_t)t * a.N];
+        if constexpr (NLD >= 1) l1[b][r] = at_elem(base(p1), at(b, r));
+        if constexpr (NLD >= 2) l2[b][r] = at_elem(base(p2), at(b, r));
+        if constexpr (MULF) lf[b][r] = f_at(at(b, r));
       }
   };
   if constexpr (EARLY) load(0);
@@ -592,11 +651,11 @@ __global__ void __launch_bounds__(256) k_row_inv(ConvArgs<Rs, Rc> a) {
     for (int br = 0; br < BB * RV; ++br) {
       const int bi = br / RV, r = br % RV, b = b0 + bi;
       if (!ok(b, r)) continue;
-      const size_t e = rowoff + col_of(b, r);
+      const El e = elem(b, r);
       Cc cv = cscale(v[b * RL + r], scale);
       if constexpr (MULF) cv = cscale(cv, static_cast<Rc>(lf[bi][r]));
       if constexpr (EPI == EPI_AX) {
-        a.y[e] = ccast<Cs>(csub(ccast<Cc>(l1[bi][r]), cv));
+        at_elem(base(a.y), e) = ccast<Cs>(csub(ccast<Cc>(l1[bi][r]), cv));
       } else if constexpr (EPI == EPI_G || EPI == EPI_GF) {
         a.y[e] = ccast<Cs>(cv);
       } else if constexpr (EPI == EPI_V) {
@@ -924,7 +983,7 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_conv_small(ConvAr
   __shared__ C stw[P];
   for (int i = threadIdx.x; i < P; i += CF::THREADS) stw[i] = a.tw[i];
   __syncthreads();
-  const R *f = a.frow ? a.frow[t] : a.f;
+  const GlobalPtr<R> f = contrast_of(a, t);
   const size_t base = (size_t)t * a.N;
   const R scale = static_cast<R>(a.scale);
   PlaneSpectrum<CF, R, P, ADJ> g(a.Ghat);
@@ -990,7 +1049,7 @@ __global__ void __launch_bounds__((SmallCfg<R, P>::THREADS)) k_solve_small(Small
   constexpr int R0 = FirstRadix<typename Plan<P>::fwd>::value;
   auto col = [&](int i) __attribute__((always_inline)) { return tk + (i / (R0 / 2)) * NT + (i % (R0 / 2)) * (P / R0); };
   const size_t base = (size_t)t * a.N;
-  const R *fr = a.frow ? a.frow[t] : a.f;
+  const GlobalPtr<R> fr = contrast_of(a, t);
   C xr[LEAN ? 1 : OWN], hr[LEAN ? 1 : OWN], p[OWN], v[OWN], s[OWN], tt[OWN];
   R f[OWN];
   unsigned e[OWN];   // element within the field

@@ -4,9 +4,9 @@ FP64 residual, forward and adjoint, with the vectors' loads of every batching.""
 import numpy as np
 import pytest
 
-from gpu_common import make_pair, say, to_dev, to_np
+from gpu_common import make_pair, rel, say, to_dev, to_np
 from oracle import operators
-from synth import ellipses_2d
+from synth import disks_2d, ellipses_2d, random_field
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +35,18 @@ def test_solutions_meet_the_fp64_residual(prec, n, T, adjoint):
         r = np.linalg.norm(b[t] - apply(prob.Ghat, f, xn[t])) / np.linalg.norm(b[t])
         # the stop test is on the FP64 residual; f and x are what the device holds, f rounded in c64
         assert r <= (1.05 * tol if prec == "c128" else 1.5 * tol), (t, its)
+
+
+# the operator's own rows: every transform length that is no small grid, a side that leaves columns and
+# rows over (the last one before the next length, and the first after the previous)
+@pytest.mark.parametrize("prec", ["c64", "c128"])
+@pytest.mark.parametrize("n", [33, 63, 65, 96, 97, 127, 129, 192, 193, 255, 257, 384, 385, 511])
+def test_operator_rows_match_oracle(n, prec):
+    T = 2
+    say(f"operator rows n={n} {prec}")
+    prob, op = make_pair(n, 0.1, T, 3, precision=prec)
+    f, x = disks_2d(n, n, count=2, radius_px=(n / 8, n / 4), eps_range=(1.2, 1.6)), random_field((T, n, n), n)
+    fd, xd = to_dev(f.ravel(), op, real=True), to_dev(x.reshape(T, -1), op)
+    for adj in (False, True):
+        ref = (operators.apply_AH if adj else operators.apply_A)(prob.Ghat, f, x)
+        assert rel(to_np(op.apply_A(fd, xd, adjoint=adj)).reshape(T, n, n), ref) < (2e-6 if prec == "c64" else 1e-12)
