@@ -887,12 +887,55 @@ __device__ __forceinline__ void plane_conv(cplx_t<Rc> *B, cplx_t<Rc> *E, const c
   }
 }
 
+// The fields that take part in a masked launch (by their system's flags and by the
+// field mask, each of which may be null), in order.  A wave reads 64 at once; the
+// first 256 are kept.
+struct RunningFields {
+  const TxState *st;
+  const int *fmask;
+  int flag, T;
+  unsigned long long h0 = 0, h1 = 0, h2 = 0, h3 = 0, word = 0;   // word: those of 64 w + i not yet taken
+  int w = 0;
+  __device__ __forceinline__ bool runs(int i) const {
+    const int f = 64 * i + (int)(threadIdx.x & 63), g = min(f, T - 1);
+    bool r = f < T;
+    if (st) r = r && (st[g].flags & flag);
+    if (fmask) r = r && fmask[g];
+    return r;
+  }
+  __device__ __forceinline__ unsigned long long at(int i) const {
+    return i == 0 ? h0 : i == 1 ? h1 : i == 2 ? h2 : i == 3 ? h3 : __ballot(runs(i));
+  }
+  __device__ __forceinline__ int count() {
+    const bool r0 = runs(0), r1 = runs(1), r2 = runs(2), r3 = runs(3);
+    h0 = __ballot(r0), h1 = __ballot(r1), h2 = __ballot(r2), h3 = __ballot(r3);
+    int total = 0;
+    for (int i = 0; 64 * i < T; ++i) total += __popcll(at(i));
+    return total;
+  }
+  // After count(): the running field of rank `rank`, and the one after the last given.
+  __device__ __forceinline__ int first(int rank) {
+    for (word = h0; __popcll(word) <= rank && 64 * (w + 1) < T; word = at(++w)) rank -= __popcll(word);
+    for (; rank > 0; --rank) word &= word - 1;
+    return next();
+  }
+  __device__ __forceinline__ int next() {
+    while (!word && 64 * (w + 1) < T) word = at(++w);
+    const int f = 64 * w + (word ? __builtin_ctzll(word) : 0);
+    word &= word - 1;
+    return min(f, T - 1);
+  }
+};
+
 // A block convolves the plane kz of a.pf fields one after the other: the
 // spectrum (four times a field's samples in bytes at n = P/2) is read once for
 // them, and a field's samples are requested while the one before is
 // transformed.  Operator at 64^3 x 16 in FP32, one block a CU: 178 us with one
 // field a block, 166 with 2, 154 with 4, 147 with 8 (256 blocks); the FP64
-// planes of 243 fields at 32^3: 199 us a launch with one, 183 with 4.
+// planes of 243 fields at 32^3: 199 us a launch with one, 183 to 186 with 4 to 16.
+// With fields masked out the blocks share those that run.  Solves whose last
+// three systems of 81 run alone (vectorial, 32^3): 3.75 ms with a field a block,
+// 4.41 with a fixed range of fields a block, 3.29 so.
 template <typename Rs, typename Rc, int P, bool CONJ, bool MASK>
 __global__ void __launch_bounds__((PlaneCfg<Rc, P>::THREADS)) k_plane(ConvArgs<Rs, Rc> a) {
   using Cc = cplx_t<Rc>;
@@ -900,17 +943,18 @@ __global__ void __launch_bounds__((PlaneCfg<Rc, P>::THREADS)) k_plane(ConvArgs<R
   constexpr int NT = CF::NT, OWN = P / (2 * NT);
   constexpr int R0 = FirstRadix<typename Plan<P>::fwd>::value;
   const int kz = blockIdx.x, n = a.n;
-  // a field takes part unless its system is masked out
-  auto runs = [&](int t) {
-    if constexpr (MASK) {
-      if (!(a.st[t].flags & a.flag)) return false;
-    }
-    return !(a.fmask && !a.fmask[t]);
-  };
-  const int t1 = min(((int)blockIdx.y + 1) * a.pf, a.T);
-  int t = blockIdx.y * a.pf;
-  while (t < t1 && !runs(t)) ++t;
-  if (t == t1) return;
+  // The block's fields: t, and `left` in all.  Where systems are masked out the
+  // blocks of a plane share the fields that run evenly, in order, so that a block
+  // never convolves one after the other what others could beside it.
+  const bool masked = MASK || a.fmask;
+  RunningFields run{MASK ? a.st : nullptr, a.fmask, a.flag, a.T};
+  int t = blockIdx.y * a.pf, left = min(a.pf, a.T - t);
+  if (masked) {
+    const int total = run.count(), per = (total + (int)gridDim.y - 1) / (int)gridDim.y;
+    left = min(per, total - (int)blockIdx.y * per);
+    if (left <= 0) return;
+    t = run.first(blockIdx.y * per);
+  }
   __shared__ Cc B[CF::NROW * CF::SPAN];
   __shared__ Cc E[P * CF::LINES];
   __shared__ Cc stw[P];
@@ -929,13 +973,15 @@ __global__ void __launch_bounds__((PlaneCfg<Rc, P>::THREADS)) k_plane(ConvArgs<R
   request(t);
   PlaneSpectrum<CF, Rc, P, CONJ> g(a.Gpm + (size_t)kz * P * P);
   __syncthreads();
-  while (t < t1) {
+  for (; left > 0; --left) {
     Cc cur[OWN];
 #pragma unroll
     for (int i = 0; i < OWN; ++i) cur[i] = next[i];
     int u = t + 1;
-    while (u < t1 && !runs(u)) ++u;
-    if (u < t1) request(u);
+    if (left > 1) {
+      if (masked) u = run.next();
+      request(u);
+    }
     Cc *out = a.cout + ((size_t)t * P + kz) * nn;
     plane_conv<CF, Rc, P, CONJ>(
         B, E, stw, g, n, [&](int i, int, int) { return cur[i]; },
@@ -1222,9 +1268,13 @@ template <int P> static bool row_exact(const Ctx &c, int rows) {
 }
 // Fields per block of k_plane: the count whose blocks, in whole rounds of what
 // 256 CUs hold at once, take the least time; a block's own start counts as
-// half a field.
+// half a field.  One where four blocks share a CU (FP32 at P = 64): they hide
+// each other's start, and rounds that do not come out even cost more (operator
+// at 31^3 x 40: 41.3 us with one field, 46.1 with three; at 32^3 x 64 in whole
+// rounds 53.7 and 56.5 with four).
 template <typename Rc, int P> static int plane_fields(int T) {
-  constexpr int slots = 256 * (int)(160 * 1024 / PlaneCfg<Rc, P>::LDS_BYTES);
+  constexpr int per_cu = (int)(160 * 1024 / PlaneCfg<Rc, P>::LDS_BYTES), slots = 256 * per_cu;
+  if (per_cu > 2) return 1;
   int best = 1;
   long long least = 0;
   for (int f = 1; f <= 16 && f <= T; ++f) {

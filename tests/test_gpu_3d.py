@@ -132,3 +132,51 @@ def test_64cube_vjp_matches_oracle_on_a_sampled_transmitter():
     g, _, _ = op.vjp(fd, u, to_dev(w, op), SolveOpts(tol=1e-7))
     g_ref, _ = ocisor.gradient(prob, f, y_ref - w, tol=1e-9)
     assert rel(to_np(g).reshape(g_ref.shape), g_ref) < 2e-4
+
+
+# several fields per block of the plane kernel: short last blocks at transform length 128 (three to
+# seven fields a block) and one field a block at 64
+@pytest.mark.parametrize("n,T", [(33, 5), (40, 13), (12, 17)])
+def test_apply_A_3d_many_fields_matches_oracle(n, T):
+    say(f"3d apply_A n={n} T={T}")
+    prob, op = make_pair3(n, 1 / 6, T, 2, "c64")
+    f = ellipsoids_3d(n, n, axes=(0.2, 0.45))
+    x = random_field((T, n, n, n), 2)
+    for adj in (False, True):
+        ref = (operators.apply_AH if adj else operators.apply_A)(prob.Ghat, f, x)
+        y = op.apply_A(to_dev(f.ravel(), op, real=True), to_dev(x.reshape(T, -1), op), adjoint=adj)
+        for t in range(T):
+            assert rel(to_np(y)[t].reshape(n, n, n), ref[t]) < 2e-6
+
+
+# systems that have converged or have no right-hand side are left out of the plane kernel, at the
+# start, in the middle and at the end of a block's fields, and in a second word of flags; the others
+# meet the tolerance in the oracle's FP64 residual
+@pytest.mark.parametrize("n,T,prec", [(33, 13, "c64"), (40, 5, "c64"), (12, 17, "c64"), (8, 300, "c64"),
+                                      (12, 40, "c128"), (8, 300, "c128")])
+def test_masked_solves_3d_meet_the_fp64_residual(n, T, prec):
+    from paper_1708_01663_amd.cisor import SolveOpts
+    say(f"3d masked solves n={n} T={T} {prec}")
+    prob, op = make_pair3(n, 1 / 6, T, 2, prec)
+    f = ellipsoids_3d(n, 3, axes=(0.25, 0.45))
+    b = random_field((T, n, n, n), 7)
+    b[2] = 0.0
+    fd, bd = to_dev(f.ravel(), op, real=True), to_dev(b.reshape(T, -1), op)
+    b = to_np(bd).reshape(T, n, n, n)
+    tol = 1e-6 if prec == "c64" else 1e-10
+    done, _, code = op.solve(fd, bd, opts=SolveOpts(tol=tol))
+    assert code == 0
+    x0 = done.clone()
+    open_ = [t for t in (0, 3, 4, T // 2, T - 1, 70, 259) if t < T and t != 2]
+    for i, t in enumerate(open_):
+        x0[t] *= 1.0 + 10.0 ** (-i % 4)      # further off: more iterations
+    x, its, code = op.solve(fd, bd, opts=SolveOpts(tol=1.2 * tol, start=2), x0=x0)
+    assert code == 0 and all(its[t] > 0 for t in open_)
+    x = to_np(x).reshape(T, n, n, n)
+    assert np.abs(x[2]).max() == 0.0
+    r = b - operators.apply_A(prob.Ghat, f, x)
+    for t in range(T):
+        if t in open_:
+            assert np.linalg.norm(r[t]) <= (1.3 if prec == "c128" else 1.8) * tol * np.linalg.norm(b[t]), (t, its[t])
+        elif t != 2:
+            assert its[t] == 0 and np.array_equal(x[t], to_np(done[t]).reshape(n, n, n))
