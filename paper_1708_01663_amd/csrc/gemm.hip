@@ -628,7 +628,10 @@ __global__ void __launch_bounds__(256, 2) k_backproject_f64(const cd *H, const c
   }
 }
 
-// Two pixel tiles a wave where that still gives 2048 waves (two per SIMD).
+// Two pixel tiles a wave where that still gives 2048 waves (two per SIMD); three
+// transmitter tiles only where they are all there are, else two: at 240^2 x 300
+// receivers 104 us for a pass over H with two and 193 with three, so four take
+// 181 us in two passes of two (377 with three and one of three; 336 with FMA sums).
 static void launch_backproject_f64(Ctx &c, const cd *w, cd *q, const double *f, cd *b) {
   const int tt = (c.T + 15) / 16;
   auto go = [&](auto tb, auto ka) {
@@ -639,8 +642,8 @@ static void launch_backproject_f64(Ctx &c, const cd *w, cd *q, const double *f, 
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
   using I3 = std::integral_constant<int, 3>;
-  const bool wide = (long long)(c.N / 32) * ((tt + 2) / 3) >= 2048;
-  if (wide) return tt >= 3 ? go(I3{}, I2{}) : tt == 2 ? go(I2{}, I2{}) : go(I1{}, I2{});
+  const bool wide = (long long)(c.N / 32) * (tt == 3 ? 1 : (tt + 1) / 2) >= 2048;
+  if (wide) return tt == 3 ? go(I3{}, I2{}) : tt >= 2 ? go(I2{}, I2{}) : go(I1{}, I2{});
   go(I1{}, I1{});
 }
 

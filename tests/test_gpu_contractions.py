@@ -167,3 +167,15 @@ def test_split_contractions_infinite_operand_keeps_its_real_part():
     q = op.backproject(w.cuda()).cpu()
     assert torch.equal(y[32].real, float("inf") * H[:, op.N - 1].real.sign())
     assert torch.equal(q[32].real, float("inf") * H[M - 1].real.sign())
+
+
+# complex128 back-projection with two pixel tiles a wave: one, two, three and more tiles of 16
+# transmitters, the last one cut, a pixel count that cuts the last wave's tiles
+@pytest.mark.parametrize("T", [9, 31, 40, 60, 70])
+def test_wide_fp64_backprojection_matches_fp64(T):
+    n, M = (300, 7) if T < 17 else (259, 7)
+    print(f"wide back-projection {T}", flush=True)
+    op = Cisor(n, 0.1, plane_wave_dirs(T), ring(M, n * 0.1), precision="c128")
+    rng = np.random.default_rng(T)
+    w = torch.as_tensor(rng.standard_normal((T, M)) + 1j * rng.standard_normal((T, M)))
+    assert _rel(op.backproject(w.cuda()).cpu(), w @ op.H().cpu().conj()) <= 16 * M ** 0.5 * 2.0 ** -53
