@@ -413,19 +413,23 @@ __global__ void __launch_bounds__(256) k_project_mfma16(const cf *H, const float
   const int kend = min(k0 + PJ_KCHUNK, N);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   floatx4 acc1 = {0}, acc2 = {0}, acc3 = {0};   // Gauss's three products
-  // raw loads ahead of the MFMAs: forming f u here would wait for them
+  // raw loads ahead of the MFMAs: forming f u here would wait for them.  Rows past M
+  // or T are skipped: a step of a small problem is bound by the loads it issues
+  // (32^2 x 1 x 32 receivers 18.3 us, 19.8 with the last row repeated)
   static_assert(256 % KS == 0, "one pixel per thread and step");
   const int kk = threadIdx.x % KS, row = threadIdx.x / KS;
   constexpr int RS = 256 / KS;
-  cf rh[PH], ru[PU];
+  cf rh[PH] = {}, ru[PU] = {};
   float rf = 0.0f;
   auto load = [&](int kb) {
     const int k = min(kb + kk, N - 1);
     rf = f[k];
 #pragma unroll
-    for (int e = 0; e < PH; ++e) rh[e] = H[(size_t)min(m0 + row + RS * e, M - 1) * N + k];
+    for (int e = 0; e < PH; ++e)
+      if (m0 + row + RS * e < M) rh[e] = H[(size_t)(m0 + row + RS * e) * N + k];
 #pragma unroll
-    for (int e = 0; e < PU; ++e) ru[e] = u[(size_t)min(row + RS * e, T - 1) * N + k];
+    for (int e = 0; e < PU; ++e)
+      if (row + RS * e < T) ru[e] = u[(size_t)(row + RS * e) * N + k];
   };
   load(k0);
   for (int kb = k0; kb < kend; kb += KS) {

@@ -179,3 +179,20 @@ def test_wide_fp64_backprojection_matches_fp64(T):
     rng = np.random.default_rng(T)
     w = torch.as_tensor(rng.standard_normal((T, M)) + 1j * rng.standard_normal((T, M)))
     assert _rel(op.backproject(w.cuda()).cpu(), w @ op.H().cpu().conj()) <= 16 * M ** 0.5 * 2.0 ** -53
+
+
+# at most 16 transmitters in complex64: one and several in both halves of the tile, receivers that
+# fill it in part, exactly and with a remainder, pixel counts around a step and a chunk
+@pytest.mark.parametrize("T", [1, 8, 9, 16])
+@pytest.mark.parametrize("n,M", [(4, 1), (23, 33), (32, 64), (45, 70)])
+def test_narrow_projection_matches_fp64(n, T, M):
+    print(f"narrow projection {n} {T} {M}", flush=True)
+    op = Cisor(n, 0.1, plane_wave_dirs(T), ring(M, n * 0.1), precision="c64")
+    rng = np.random.default_rng(n + T)
+    u = torch.as_tensor(rng.standard_normal((T, op.N)) + 1j * rng.standard_normal((T, op.N))).to(op.cdtype)
+    f = torch.as_tensor(rng.uniform(0, 1, op.N)).to(op.rdtype)
+    y = op.project(f.cuda(), u.cuda()).cpu()
+    want = (u.to(torch.complex128) * f.double()) @ op.H().cpu().to(torch.complex128).T
+    # f u rounded once, then 128 sums of 4 products per chunk of 512 pixels and component, each rounded
+    # in FP32, of three products (Gauss) of up to four times the size
+    assert _rel(y, want) <= 4 * 128 ** 0.5 * 2.0 ** -24
