@@ -599,6 +599,7 @@ __device__ __forceinline__ bf16x8 tr_frag(const bf16_t *p) {
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+template <typename OFF>   // holds the element offsets of an image
 __global__ void __launch_bounds__(64 * WG_WAVES, 2) k_conv3x3_wgrad(WgArgs a) {
   constexpr int XB = (WG_RB * WG_XP * 4 + 63) / 64;   // x pieces (16 bytes) per lane and batch
   constexpr int XP = (2 * WG_XP * 4 + 63) / 64;       // of the two rows above a task's first batch
@@ -625,7 +626,7 @@ __global__ void __launch_bounds__(64 * WG_WAVES, 2) k_conv3x3_wgrad(WgArgs a) {
     const int y = yy + row, xx = x0 - 1 + (rem >> 2);
     u32x4 v = u32x4{0, 0, 0, 0};
     if (row < nr && y >= 0 && y < H && xx >= 0 && xx < W)
-      v = *reinterpret_cast<const u32x4 *>(xi + (unsigned)(((y >> sh) * Ws + (xx >> sh)) * Cx + (rem & 3) * 8));
+      v = *reinterpret_cast<const u32x4 *>(xi + (((OFF)(y >> sh) * Ws + (xx >> sh)) * Cx + (rem & 3) * 8));
     return v;
   };
   u32x4 rx[XB], rd[WG_RB];
@@ -637,7 +638,7 @@ __global__ void __launch_bounds__(64 * WG_WAVES, 2) k_conv3x3_wgrad(WgArgs a) {
       const int xx = x0 + (lane >> 2);
       rd[k] = u32x4{0, 0, 0, 0};
       if (yb + k < y1 && xx < W)
-        rd[k] = *reinterpret_cast<const u32x4 *>(di + (unsigned)(((yb + k) * W + xx) * a.Co + (lane & 3) * 8));
+        rd[k] = *reinterpret_cast<const u32x4 *>(di + (((OFF)(yb + k) * W + xx) * a.Co + (lane & 3) * 8));
     }
   };
   for (int task = blockIdx.z * WG_WAVES + wave; task < a.tasks; task += gridDim.z * WG_WAVES) {
@@ -1220,7 +1221,9 @@ static int conv_wgrad(hipStream_t s, const bf16_t *x, const bf16_t *dy, float *p
   a.segs = (H + a.rh - 1) / a.rh;
   a.tasks = B * a.strips * a.segs;
   splits = std::min(splits, (a.tasks + WG_WAVES - 1) / WG_WAVES);
-  hipLaunchKernelGGL(k_conv3x3_wgrad, dim3(Ci / 32, Co / 32, splits), dim3(64 * WG_WAVES), 0, s, a);
+  const bool narrow = (double)H * W * std::max(Ci, Co) < 4294967296.0;
+  hipLaunchKernelGGL(narrow ? k_conv3x3_wgrad<unsigned> : k_conv3x3_wgrad<size_t>, dim3(Ci / 32, Co / 32, splits),
+                     dim3(64 * WG_WAVES), 0, s, a);
   return splits;
 }
 
