@@ -346,12 +346,13 @@ def paper_geometry_leg(log, steps=50):
     return out
 
 
-def vec_bytes_per_tx_iteration(n, P, N):
+def vec_bytes_per_tx_iteration(n, P, N, adjoint=False):
     """Modelled HBM bytes of one BiCGSTAB iteration of one transmitter's
     vectorial system (3N complex128 unknowns): two convolutions of the three
-    component fields and 23 field streams of the fused vector kernels (p update
-    + f p: 5, v = A p with <rhat, v>: 4, s update + f s: 4, t = A s with its
-    dots: 3, x and r update with its dots: 7).  A convolution streams 2 + 4 rho
+    component fields and 21 field streams of the fused vector kernels (p update:
+    4, v = A p with <rhat, v>: 4, s update: 3, t = A s with its dots: 3, x and r
+    update with its dots: 7); the adjoint also reads p and s and writes each
+    convolution's input, 25 in all.  A convolution streams 2 + 4 rho
     field-sized arrays (rho = P / n) where the y- and x-passes run fused per kz
     plane (power-of-two P up to 64 in FP64: the z-transforms in and out, the
     plane kernel's n^2 P read and write), else 2 + 4 rho + 4 rho^2 (the y- and
@@ -359,7 +360,7 @@ def vec_bytes_per_tx_iteration(n, P, N):
     rho = P / n
     plane = P in (64,)
     conv = 2 + 4 * rho + (0 if plane else 4 * rho * rho)
-    return int(3 * N * 16 * (2 * conv + 23))
+    return int(3 * N * 16 * (2 * conv + (25 if adjoint else 21)))
 
 
 def vectorial_3d_leg(log, reps=5):
@@ -396,7 +397,8 @@ def vectorial_3d_leg(log, reps=5):
     tx_iters = int(its.sum())
     P = 64 if n <= 32 else 2 * n
     bpi = vec_bytes_per_tx_iteration(n, P, n ** 3)
-    gbs = bpi * tx_iters / dt / 1e9
+    gbs = (bpi * int(its[:op.T].sum())
+           + vec_bytes_per_tx_iteration(n, P, n ** 3, adjoint=True) * int(its[op.T:].sum())) / dt / 1e9
     g2 = op.grad(f, y_meas, SolveOpts(tol=1e-6, maxit=20000, start=2))
     # CISOR iterations on the vectorial model: relaxed FISTA with the 3D TV/box
     # prox from f_0 = 0, step half the Cauchy step of the Born linearisation at
