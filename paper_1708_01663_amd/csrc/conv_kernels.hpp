@@ -599,9 +599,9 @@ __global__ void __launch_bounds__(256) k_row_inv(ConvArgs<Rs, Rc> a) {
   constexpr bool EARLY = sizeof(Cs) == 8 && EPI != EPI_AX;
   constexpr bool FULL = row_full<Rc, P>();
   constexpr bool NARROW = EPI == EPI_AX && !EXACT && (P > 128 || sizeof(Cs) == 16);
-  constexpr int BB = EARLY ? V / RL
-                           : row_batch<V / RL>(RV * (NLD * (int)sizeof(Cs) + (NARROW && MULF ? (int)sizeof(Rs) : 0)) + 1,
-                                               FULL && (NARROW || MULF) ? 256 : NARROW && MULF && V == 24 ? 128 : 384);
+  constexpr int BYTES = RV * (NLD * (int)sizeof(Cs) + (NARROW && MULF ? (int)sizeof(Rs) : 0)) + 1;
+  constexpr int HOLD = FULL && (NARROW || MULF) ? 256 : NARROW && MULF && V == 24 ? 128 : 384;
+  constexpr int BB = EARLY ? V / RL : row_batch<V / RL>(BYTES, HOLD);
   Cs l1[BB][RV], l2[BB][RV];
   Rs lf[BB][RV];
   const size_t field = (size_t)t * a.N;

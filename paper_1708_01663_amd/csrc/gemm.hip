@@ -383,9 +383,8 @@ __global__ void __launch_bounds__(256, 3) k_project_bf16(const cf *H, const floa
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int m = m0 + wm * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-    if (m < M)
-      part[((size_t)kc * T + t) * M + m] = cscale(mk<cd>((double)re[r] + (double)res[r], (double)im[r] + (double)ims[r]),
-                                                           (double)BF16_DOWN);
+    const cd sum = mk<cd>((double)re[r] + (double)res[r], (double)im[r] + (double)ims[r]);
+    if (m < M) part[((size_t)kc * T + t) * M + m] = cscale(sum, (double)BF16_DOWN);
   }
 }
 
@@ -542,7 +541,9 @@ int launch_project(Ctx &c, const R *f, const cplx_t<R> *u, const cplx_t<R> *y_me
       dim3 g((c.M + 63) / 64, 1, kchunks);
       // 32-bit row offsets below 2^26 pixels: 64-bit ones cost 20 spilled registers
       // (90.4 against 89.2 us at 256^2 x 60 x 360)
-      const auto kern = !c.h_split ? k_project_f32 : c.N < PJ_OFF32_N ? k_project_bf16<unsigned> : k_project_bf16<size_t>;
+      const auto kern = !c.h_split           ? k_project_f32
+                        : c.N < PJ_OFF32_N ? k_project_bf16<unsigned>
+                                           : k_project_bf16<size_t>;
       hipLaunchKernelGGL(kern, g, dim3(256), 0, c.stream, (const cf *)c.H, f, u, part, c.M, c.N, c.T);
     } else {
       launch_project_f64<float>(c, f, u, part, kchunks);
@@ -760,7 +761,8 @@ __global__ void __launch_bounds__(256, 2) k_backproject_bf16(const cf *H, const 
   static_assert(sizeof(sw2) >= BP_TT * sizeof(BpWRow32) && sizeof(sh2) >= BP_MS * sizeof(BpHRow32),
                 "the FP32 tile uses the same LDS");
   auto f32_tile = [&] {
-    backproject_tile_f32<false>(H, w, q, f, b, M, N, T, reinterpret_cast<BpWRow32 *>(sw2), reinterpret_cast<BpHRow32 *>(sh2));
+    backproject_tile_f32<false>(H, w, q, f, b, M, N, T, reinterpret_cast<BpWRow32 *>(sw2),
+                                reinterpret_cast<BpHRow32 *>(sh2));
   };
   const int k0 = blockIdx.x * BP_PT, t0 = blockIdx.y * BP_TT;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -964,8 +966,8 @@ int launch_backproject(Ctx &c, const cplx_t<R> *w, cplx_t<R> *q, const R *f, cpl
       return hipGetLastError() == hipSuccess ? CISOR_OK : CISOR_E_DEVICE;
     }
     dim3 g((c.N + BP_PT - 1) / BP_PT, (c.T + BP_TT - 1) / BP_TT);
-    hipLaunchKernelGGL(c.h_split ? k_backproject_bf16 : k_backproject_f32, g, dim3(256), 0, c.stream, (const cf *)c.H, w,
-                       q, f, b, c.M, c.N, c.T);
+    hipLaunchKernelGGL(c.h_split ? k_backproject_bf16 : k_backproject_f32, g, dim3(256), 0, c.stream, (const cf *)c.H,
+                       w, q, f, b, c.M, c.N, c.T);
   } else {
     launch_backproject_f64(c, w, q, f, b);
   }

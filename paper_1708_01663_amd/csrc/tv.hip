@@ -88,8 +88,9 @@ __device__ __forceinline__ void tv_disk(float &a, float &b) {
 // only the vertical ones (one value of r, one of x) go through LDS: four LDS
 // operations and two barriers an iteration.  With every value in LDS (17
 // operations an iteration) a launch of eight iterations at 256^2 took
-// 10.4 us, now 6.0 us; bound by the dependent chain of an iteration
-// (square root and two divisions) over 16 waves a CU.
+// 10.4 us, now 6.0 us; bound by the dependent chain of an iteration (two
+// barriers, the LDS reads and the projection onto the disk: a reciprocal root
+// with a Newton step in FP32, a root and two divisions in FP64) over 16 waves a CU.
 // Values outside the image are zero and stay zero, and r1 (r2) is zero in the
 // last row (column) from the start on, so div r needs no boundary test.
 template <typename R, bool WHOLE, bool FIRST, int NW>
